@@ -38,7 +38,8 @@
  *    (N = number of sequences), the orientation of the paper's recurrent
  *    pseudocode (Appendix B.1).
  *  - q, k, v, beta, beta_tilde and dO have dtype shape->in_dtype (bf16 or
- *    fp32); g (log alpha), d, states and every output are fp32.
+ *    fp32); g (log alpha), d, states and every output are fp32 (comba_train.h
+ *    has a backward with gradients in in_dtype).
  *  - Head sizes: dk, dv in {64, 128}; with bf16 inputs also dk, dv in {128, 256}
  *    (256, the paper's models, for every chunk entry point).  fp32 inputs: 64.
  *  - beta_tilde [B,T,H] may be NULL: beta~ = beta.  The backward's dbeta_tilde

@@ -84,6 +84,8 @@ def load_library():
             lib.comba_chunk_fwd_save.restype = I
             lib.comba_chunk_bwd_saved.argtypes = [SP] + [P] * 18 + [P, Z, P]
             lib.comba_chunk_bwd_saved.restype = I
+            lib.comba_chunk_bwd_saved_in_dtype.argtypes = [SP] + [P] * 18 + [P, Z, P]
+            lib.comba_chunk_bwd_saved_in_dtype.restype = I
             lib.comba_chunk_fwd_noalloc.argtypes = [SP] + [P] * 10 + [P]
             lib.comba_chunk_fwd_noalloc.restype = I
             lib.comba_noalloc_scratch_bytes.argtypes = []
@@ -474,7 +476,7 @@ def comba_gate_bwd(o, z, dy, *, stream=None):
 
 
 def _bwd(saved, q, k, v, g, beta, d, h0, dO, dht, cu_seqlens, need_dh0, workspace, stream,
-         beta_tilde, cu_seqlens_host=None):
+         beta_tilde, cu_seqlens_host=None, in_dtype=False):
     import torch
 
     lib = load_library()
@@ -488,13 +490,14 @@ def _bwd(saved, q, k, v, g, beta, d, h0, dO, dht, cu_seqlens, need_dh0, workspac
         raise CombaError("comba: dO must be [B,T,H,dv]")
     dev = q.device
     f32 = torch.float32
+    gt = q.dtype if in_dtype else f32  # in_dtype: comba_chunk_bwd_saved_in_dtype
     out = {
-        "dq": torch.empty((B, T, H, dk), dtype=f32, device=dev),
-        "dk": torch.empty((B, T, H, dk), dtype=f32, device=dev),
-        "dv": torch.empty((B, T, H, dv), dtype=f32, device=dev),
+        "dq": torch.empty((B, T, H, dk), dtype=gt, device=dev),
+        "dk": torch.empty((B, T, H, dk), dtype=gt, device=dev),
+        "dv": torch.empty((B, T, H, dv), dtype=gt, device=dev),
         "dg": torch.empty((B, T, H), dtype=f32, device=dev),
-        "dbeta": torch.empty((B, T, H), dtype=f32, device=dev),
-        "dbeta_tilde": None if beta_tilde is None else torch.empty((B, T, H), dtype=f32,
+        "dbeta": torch.empty((B, T, H), dtype=gt, device=dev),
+        "dbeta_tilde": None if beta_tilde is None else torch.empty((B, T, H), dtype=gt,
                                                                    device=dev),
         "dd": torch.empty((H,), dtype=f32, device=dev),
         "dh0": torch.empty((N, H, dk, dv), dtype=f32, device=dev) if need_dh0 else None,
@@ -508,7 +511,8 @@ def _bwd(saved, q, k, v, g, beta, d, h0, dO, dht, cu_seqlens, need_dh0, workspac
                              "comba_chunk_fwd_save")
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
     st = torch.cuda.current_stream(dev).cuda_stream if stream is None else stream
-    fn = lib.comba_chunk_bwd_saved if saved else lib.comba_chunk_bwd
+    fn = lib.comba_chunk_bwd_saved_in_dtype if in_dtype else \
+        lib.comba_chunk_bwd_saved if saved else lib.comba_chunk_bwd
     _check(fn(ctypes.byref(shp), _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(beta),
               _ptr(beta_tilde), _ptr(d), _ptr(h0), _ptr(dO), _ptr(dht), _ptr(out["dq"]),
               _ptr(out["dk"]), _ptr(out["dv"]), _ptr(out["dg"]), _ptr(out["dbeta"]),
@@ -541,7 +545,8 @@ def _autograd_function():
     class _ChunkComba(torch.autograd.Function):
         """The training pair as one differentiable op: comba_chunk_fwd_save in
         the forward (its workspace kept for the backward), comba_chunk_bwd_saved
-        in the backward.  Gradients come back in the inputs' dtypes; the
+        in the backward.  Gradients come back in the inputs' dtypes, written so
+        by the kernels (comba_chunk_bwd_saved_in_dtype); the
         upstream gradient of o is rounded to the inputs' dtype (the kernels
         take dO in in_dtype)."""
 
@@ -562,13 +567,10 @@ def _autograd_function():
                 do = torch.zeros(q.shape[:3] + (v.shape[-1],), dtype=torch.float32,
                                  device=q.device)
             need = ctx.needs_input_grad
-            gr = comba_chunk_bwd_saved(q, k, v, g, beta, d, h0,
-                                       do.to(q.dtype).contiguous(),
-                                       None if dht is None else dht.float().contiguous(),
-                                       workspace=ws, beta_tilde=beta_tilde,
-                                       cu_seqlens=cu_seqlens,
-                                       cu_seqlens_host=ctx.cu_seqlens_host,
-                                       need_dh0=h0 is not None and need[6])
+            gr = _bwd(True, q, k, v, g, beta, d, h0, do.to(q.dtype).contiguous(),
+                      None if dht is None else dht.float().contiguous(), cu_seqlens,
+                      h0 is not None and need[6], ws, None, beta_tilde, ctx.cu_seqlens_host,
+                      in_dtype=True)
 
             def cast(x, like, i):
                 return None if (x is None or not need[i]) else x.to(like.dtype)

@@ -9,6 +9,7 @@
 
 #include "comba.h"
 #include "comba_launch.h"
+#include "comba_train.h"
 
 namespace {
 
@@ -361,11 +362,12 @@ comba_status chunk_fwd(bool save, const comba_shape* shape, const void* q, const
   return comba::launch_fwd(a) == hipSuccess ? COMBA_OK : COMBA_ERR_HIP;
 }
 
-comba_status chunk_bwd(bool saved, const comba_shape* shape, const void* q, const void* k,
-                       const void* v, const float* g, const void* beta, const void* beta_tilde,
-                       const float* d, const float* h0, const void* dO, const float* dht,
-                       float* dq, float* dk, float* dv, float* dg, float* dbeta,
-                       float* dbeta_tilde, float* dd, float* dh0, void* ws, size_t ws_bytes,
+// cast: dq, dk, dv, dbeta and dbeta_tilde in the inputs' dtype instead of fp32.
+comba_status chunk_bwd(bool saved, bool cast, const comba_shape* shape, const void* q,
+                       const void* k, const void* v, const float* g, const void* beta,
+                       const void* beta_tilde, const float* d, const float* h0, const void* dO,
+                       const float* dht, void* dq, void* dk, void* dv, float* dg, void* dbeta,
+                       void* dbeta_tilde, float* dd, float* dh0, void* ws, size_t ws_bytes,
                        void* stream) {
   Dims dm;
   comba_status st = check_shape(shape, &dm, true);
@@ -379,10 +381,11 @@ comba_status chunk_bwd(bool saved, const comba_shape* shape, const void* q, cons
     return COMBA_ERR_NULL;
   if (!aligned(q, 16) || !aligned(k, 16) || !aligned(v, 16) || !aligned(dO, 16) ||
       !aligned(ws, kAlign) || !aligned(g, 4) || !aligned(d, 4) || !aligned(dq, 16) ||
-      !aligned(dk, 16) || !aligned(dv, 16) || !aligned(dg, 4) || !aligned(dbeta, 4) ||
+      !aligned(dk, 16) || !aligned(dv, 16) || !aligned(dg, 4) ||
+      !aligned(dbeta, cast && dm.bf16 ? 2 : 4) ||
       !aligned(dd, 4) || (h0 && !aligned(h0, 16)) || (dht && !aligned(dht, 16)) ||
       (dh0 && !aligned(dh0, 16)) || !aligned(beta, dm.bf16 ? 2 : 4) ||
-      !aligned(beta_tilde, dm.bf16 ? 2 : 4) || !aligned(dbeta_tilde, 4))
+      !aligned(beta_tilde, dm.bf16 ? 2 : 4) || !aligned(dbeta_tilde, cast && dm.bf16 ? 2 : 4))
     return COMBA_ERR_ALIGN;
   // segmented as the forward of the pair was (the same shape, device and
   // COMBA_SCAN_SEGMENTS give the same choice and the same workspace layout)
@@ -396,6 +399,7 @@ comba_status chunk_bwd(bool saved, const comba_shape* shape, const void* q, cons
   comba::LaunchArgs a{};
   fill_common(a, dm, shape);
   a.saved = saved;
+  a.grad_bf16 = cast && dm.bf16;
   a.q = q;
   a.k = k;
   a.v = v;
@@ -654,7 +658,7 @@ comba_status comba_chunk_bwd(const comba_shape* shape, const void* q, const void
                              float* dq, float* dk, float* dv, float* dg, float* dbeta,
                              float* dbeta_tilde, float* dd, float* dh0, void* ws, size_t ws_bytes,
                              void* stream) {
-  return chunk_bwd(false, shape, q, k, v, g, beta, beta_tilde, d, h0, dO, dht, dq, dk, dv, dg,
+  return chunk_bwd(false, false, shape, q, k, v, g, beta, beta_tilde, d, h0, dO, dht, dq, dk, dv, dg,
                    dbeta, dbeta_tilde, dd, dh0, ws, ws_bytes, stream);
 }
 
@@ -665,7 +669,18 @@ comba_status comba_chunk_bwd_saved(const comba_shape* shape, const void* q, cons
                                    float* dv, float* dg, float* dbeta, float* dbeta_tilde,
                                    float* dd, float* dh0, void* ws, size_t ws_bytes,
                                    void* stream) {
-  return chunk_bwd(true, shape, q, k, v, g, beta, beta_tilde, d, h0, dO, dht, dq, dk, dv, dg,
+  return chunk_bwd(true, false, shape, q, k, v, g, beta, beta_tilde, d, h0, dO, dht, dq, dk, dv, dg,
+                   dbeta, dbeta_tilde, dd, dh0, ws, ws_bytes, stream);
+}
+
+comba_status comba_chunk_bwd_saved_in_dtype(const comba_shape* shape, const void* q, const void* k,
+                                            const void* v, const float* g, const void* beta,
+                                            const void* beta_tilde, const float* d,
+                                            const float* h0, const void* dO, const float* dht,
+                                            void* dq, void* dk, void* dv, float* dg, void* dbeta,
+                                            void* dbeta_tilde, float* dd, float* dh0, void* ws,
+                                            size_t ws_bytes, void* stream) {
+  return chunk_bwd(true, true, shape, q, k, v, g, beta, beta_tilde, d, h0, dO, dht, dq, dk, dv, dg,
                    dbeta, dbeta_tilde, dd, dh0, ws, ws_bytes, stream);
 }
 

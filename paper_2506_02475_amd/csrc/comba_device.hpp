@@ -218,7 +218,7 @@ __device__ __forceinline__ const T& at(const T* base, unsigned byte_off) {
 // no branch around their stores (g 4-byte aligned).  The record count is an
 // unsigned 32-bit field: a chunk's rows at H <= 65535 heads of up to 256
 // values span less than 2^32 bytes.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t clip_rsrc(float* g, unsigned nbytes) {
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t clip_rsrc(void* g, unsigned nbytes) {
   return __builtin_amdgcn_make_buffer_rsrc(g, 0, (int)nbytes, 0x00020000);
 }
 __device__ __forceinline__ void store_clip(float x, __amdgpu_buffer_rsrc_t rs, unsigned byte_off) {
@@ -228,6 +228,52 @@ __device__ __forceinline__ void store_clip4(const floatx4& x, __amdgpu_buffer_rs
   typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
   const u32x4_t u = {__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])};
   __builtin_amdgcn_raw_buffer_store_b128(u, rs, byte_off, 0, 0);
+}
+
+// The same for gradients of type T (float, or bf16 rounded to nearest even).
+// store_grad4: four consecutive values of a row, at element offset `elem`.
+template <typename T>
+__device__ __forceinline__ void store_grad4(const floatx4& x, __amdgpu_buffer_rsrc_t rs, unsigned elem) {
+  if constexpr (is_f32<T>::value) {
+    store_clip4(x, rs, 4u * elem);
+  } else {
+    typedef float f32x4v __attribute__((ext_vector_type(4)));
+    typedef __bf16 bf16x4v __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
+    const bf16x4v b = __builtin_convertvector((f32x4v){x[0], x[1], x[2], x[3]}, bf16x4v);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2v, b), rs, 2u * elem, 0, 0);
+  }
+}
+// store_grad_rows: an accumulator's four rows, one column per lane; row e at
+// element offset elem + e * ld (elem counts this lane's column, whose parity is
+// the lane's).  bf16: lane pairs exchange values so that the even lane stores
+// both columns of rows 0 and 2, the odd lane those of rows 1 and 3: half the
+// stores, four bytes each.
+template <typename T>
+__device__ __forceinline__ void store_grad_rows(const floatx4& x, __amdgpu_buffer_rsrc_t rs, unsigned elem,
+                                                unsigned ld) {
+  if constexpr (is_f32<T>::value) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) store_clip(x[e], rs, 4u * (elem + e * ld));
+  } else {
+    typedef float f32x2v __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+    const bool odd = lane_id() & 1;
+    const unsigned at0 = 2u * (odd ? elem - 1 + ld : elem);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const float mine = odd ? x[2 * p + 1] : x[2 * p];
+      const float got = dpp_quad<0xB1>(odd ? x[2 * p] : x[2 * p + 1]);  // of lane ^ 1
+      const bf16x2v b = __builtin_convertvector((f32x2v){odd ? got : mine, odd ? mine : got}, bf16x2v);
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, b), rs, at0 + 4u * p * ld, 0, 0);
+    }
+  }
+}
+// One gradient value at element offset `elem`.
+template <typename T>
+__device__ __forceinline__ void put_grad(T* p, unsigned elem, float x) {
+  if constexpr (is_f32<T>::value) at(p, 4u * elem) = x;
+  else at(p, 2u * elem) = __builtin_bit_cast(bf16_t, (__bf16)x);
 }
 
 // Max over the four lanes r16, r16 + 16, r16 + 32, r16 + 48 (the lanes that

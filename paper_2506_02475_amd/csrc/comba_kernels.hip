@@ -2151,7 +2151,7 @@ __device__ __forceinline__ GateTerms gate_terms(int r, int c, const RowVals& rv,
   return t;
 }
 
-template <int DK, int DV>
+template <int DK, int DV, typename TG>
 __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_bf(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ dO, const bf16_t* __restrict__ beta,
@@ -2159,8 +2159,8 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_bf(
     const ChunkInfo* __restrict__ cmap, int Tfix, int H, const float* __restrict__ Gw,
     const int16_t* __restrict__ Xq, const float* __restrict__ Xs, const int16_t* __restrict__ Dq,
     const float* __restrict__ Ds, const int16_t* __restrict__ Yq, const float* __restrict__ Ys,
-    const int16_t* __restrict__ dRq, const float* __restrict__ dRs, int ncmax, float* __restrict__ dq, float* __restrict__ dk,
-    float* __restrict__ dv, float* __restrict__ dbeta, float* __restrict__ dbeta_tilde,
+    const int16_t* __restrict__ dRq, const float* __restrict__ dRs, int ncmax, TG* __restrict__ dq, TG* __restrict__ dk,
+    TG* __restrict__ dv, TG* __restrict__ dbeta, TG* __restrict__ dbeta_tilde,
     float* __restrict__ dg, float* __restrict__ ddp) {
   using SM = IntraBwdBfSmem<DK>;
   constexpr int VB = SM::VB, LDB = SM::LDB, LDK = SM::LDK, LDC = SM::LDC;
@@ -2278,7 +2278,7 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_bf(
   float Fpart = 0.f, bv = 0.f;
   float4 fdr;  // this thread's dR piece, kept for <v_r, dR_r> after the barrier
   // this chunk's dv rows (row r at r H DV), bounded at row len
-  const __amdgpu_buffer_rsrc_t rdv = clip_rsrc(dv + tok * DV, (unsigned)len * (unsigned)(H * DV * 4));
+  const __amdgpu_buffer_rsrc_t rdv = clip_rsrc(dv + tok * DV, (unsigned)len * (unsigned)(H * DV * sizeof(TG)));
   auto put = [&](int vb) {
     const int j = vb * VB;
     if (pb == (vb & 1)) {
@@ -2307,8 +2307,8 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_bf(
     }
     // dv = Diag(beta) dR
     const float b = Bs[pf_r];
-    store_clip4(floatx4{b * fdr.x, b * fdr.y, b * fdr.z, b * fdr.w}, rdv,
-                4u * ((unsigned)pf_r * (H * DV) + j + pf_c));  // rows >= len dropped
+    store_grad4<TG>(floatx4{b * fdr.x, b * fdr.y, b * fdr.z, b * fdr.w}, rdv,
+                    (unsigned)pf_r * (H * DV) + j + pf_c);  // rows >= len dropped
   };
 
   floatx4 T1[NTW], T2[NTW], T3[NTW], dA[2], dL[2];
@@ -2598,10 +2598,10 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_bf(
     if (r < len) {
       at(dg + tok, 4u * (r * H)) = dgr;
       if (dbeta_tilde) {
-        at(dbeta + tok, 4u * (r * H)) = rowB[r];
-        at(dbeta_tilde + tok, 4u * (r * H)) = rowbt;
+        put_grad(dbeta + tok, r * H, rowB[r]);
+        put_grad(dbeta_tilde + tok, r * H, rowbt);
       } else {
-        at(dbeta + tok, 4u * (r * H)) = rowB[r] + rowbt;
+        put_grad(dbeta + tok, r * H, rowB[r] + rowbt);
       }
     }
   }
@@ -2647,8 +2647,8 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_bf(
   }
   float ddpart = 0.f;
   // this chunk's rows (row r at r H DK), bounded at row len
-  const __amdgpu_buffer_rsrc_t rq = clip_rsrc(dq + tok * DK, (unsigned)len * (unsigned)(H * DK * 4));
-  const __amdgpu_buffer_rsrc_t rk = clip_rsrc(dk + tok * DK, (unsigned)len * (unsigned)(H * DK * 4));
+  const __amdgpu_buffer_rsrc_t rq = clip_rsrc(dq + tok * DK, (unsigned)len * (unsigned)(H * DK * sizeof(TG)));
+  const __amdgpu_buffer_rsrc_t rk = clip_rsrc(dk + tok * DK, (unsigned)len * (unsigned)(H * DK * sizeof(TG)));
 #pragma unroll
   for (int j = 0; j < NTW; ++j) {
     floatx4 dkv;
@@ -2661,13 +2661,9 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_bf(
     }
     // straight from the accumulators (16 lanes write 64 contiguous bytes of a
     // row): transposing to 16-byte pieces first costs more VALU than it saves
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int r = 16 * rt + 4 * g4 + e;
-      const unsigned off = 4u * ((unsigned)r * (H * DK) + 16 * (ch * NTW + j) + r16);
-      store_clip(T1[j][e], rq, off);  // rows r >= len dropped
-      store_clip(dkv[e], rk, off);
-    }
+    const unsigned off = (unsigned)(16 * rt + 4 * g4) * (H * DK) + 16 * (ch * NTW + j) + r16;
+    store_grad_rows<TG>(T1[j], rq, off, H * DK);  // rows >= len dropped
+    store_grad_rows<TG>(dkv, rk, off, H * DK);
   }
   {
     // The next item's gates and beta, after this item's last loads and stores:
@@ -2709,7 +2705,7 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_bf(
 // dv do not involve dk and are formed in the first pass.  One workgroup per
 // chunk-head (no persistent loop, no next-item copy).
 // ---------------------------------------------------------------------------
-template <int DK, int DV>
+template <int DK, int DV, typename TG>
 __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_wide(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ dO, const bf16_t* __restrict__ beta,
@@ -2717,9 +2713,9 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_wide(
     const ChunkInfo* __restrict__ cmap, int Tfix, int H, const float* __restrict__ Gw,
     const int16_t* __restrict__ Xq, const float* __restrict__ Xs, const int16_t* __restrict__ Dq,
     const float* __restrict__ Ds, const int16_t* __restrict__ Yq, const float* __restrict__ Ys,
-    const int16_t* __restrict__ dRq, const float* __restrict__ dRs, float* __restrict__ dq,
-    float* __restrict__ dk, float* __restrict__ dv, float* __restrict__ dbeta,
-    float* __restrict__ dbeta_tilde, float* __restrict__ dg, float* __restrict__ ddp) {
+    const int16_t* __restrict__ dRq, const float* __restrict__ dRs, TG* __restrict__ dq,
+    TG* __restrict__ dk, TG* __restrict__ dv, TG* __restrict__ dbeta,
+    TG* __restrict__ dbeta_tilde, float* __restrict__ dg, float* __restrict__ ddp) {
   constexpr int DKP = 128, KP = DK / DKP;
   static_assert(DK % DKP == 0, "dk slices");
   using SM = IntraBwdBfSmem<DKP>;
@@ -2781,10 +2777,10 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_wide(
   const float* Xs_i = Xs + chh * NB * DK;
   const float* Ys_i = Ys + chh * NB * DK;
   // this chunk's dv rows (row r at r H DV), bounded at row len
-  const __amdgpu_buffer_rsrc_t rdv = clip_rsrc(dv + tok * DV, (unsigned)len * (unsigned)(H * DV * 4));
+  const __amdgpu_buffer_rsrc_t rdv = clip_rsrc(dv + tok * DV, (unsigned)len * (unsigned)(H * DV * sizeof(TG)));
   // this chunk's rows (row r at r H DK), bounded at row len
-  const __amdgpu_buffer_rsrc_t rq = clip_rsrc(dq + tok * DK, (unsigned)len * (unsigned)(H * DK * 4));
-  const __amdgpu_buffer_rsrc_t rk = clip_rsrc(dk + tok * DK, (unsigned)len * (unsigned)(H * DK * 4));
+  const __amdgpu_buffer_rsrc_t rq = clip_rsrc(dq + tok * DK, (unsigned)len * (unsigned)(H * DK * sizeof(TG)));
+  const __amdgpu_buffer_rsrc_t rk = clip_rsrc(dk + tok * DK, (unsigned)len * (unsigned)(H * DK * sizeof(TG)));
   floatx4 dA[2], dL[2];
   dA[0] = dA[1] = dL[0] = dL[1] = zero4();
   float bv = 0.f;
@@ -2845,8 +2841,8 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_wide(
       }
       if (kh == 0) {  // dv = Diag(beta) dR, once
         const float b = Bs[pf_r];
-        store_clip4(floatx4{b * fdr.x, b * fdr.y, b * fdr.z, b * fdr.w}, rdv,
-                    4u * ((unsigned)pf_r * (H * DV) + j + pf_c));  // rows >= len dropped
+        store_grad4<TG>(floatx4{b * fdr.x, b * fdr.y, b * fdr.z, b * fdr.w}, rdv,
+                        (unsigned)pf_r * (H * DV) + j + pf_c);  // rows >= len dropped
       }
     };
 
@@ -3042,13 +3038,9 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_wide(
         ddpart += (float)k4[e] * dqt;
         dkv[e] = T2[j][e] - dh * dqt;
       }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = 16 * rt + 4 * g4 + e;
-        const unsigned off = 4u * ((unsigned)r * (H * DK) + c0 + 16 * (ch * NTW + j) + r16);
-        store_clip(T1[j][e], rq, off);  // rows r >= len dropped
-        store_clip(dkv[e], rk, off);
-      }
+      const unsigned off = (unsigned)(16 * rt + 4 * g4) * (H * DK) + c0 + 16 * (ch * NTW + j) + r16;
+      store_grad_rows<TG>(T1[j], rq, off, H * DK);  // rows >= len dropped
+      store_grad_rows<TG>(dkv, rk, off, H * DK);
     }
     ddpart = wave_sum(ddpart);
     if (lane == 0) scal[kh][w][1] = ddpart;
@@ -3093,10 +3085,10 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_wide(
     if (r < len) {
       at(dg + tok, 4u * (r * H)) = dgr;
       if (dbeta_tilde) {
-        at(dbeta + tok, 4u * (r * H)) = rowB[r];
-        at(dbeta_tilde + tok, 4u * (r * H)) = rowbt;
+        put_grad(dbeta + tok, r * H, rowB[r]);
+        put_grad(dbeta_tilde + tok, r * H, rowbt);
       } else {
-        at(dbeta + tok, 4u * (r * H)) = rowB[r] + rowbt;
+        put_grad(dbeta + tok, r * H, rowB[r] + rowbt);
       }
     }
     if (lane == 0) ddp[chh] = -dds;
@@ -3257,8 +3249,9 @@ static hipError_t run_bwd(const LaunchArgs& a) {
   a.stage("intra_bwd");
   if (a.ncmax > 0)
     k_intra_bwd<Tin, DK, DV><<<dim3(a.ncmax, a.H), NTHR, 0, st>>>(
-        q, k, v, dO, beta, bt, a.d, a.cmap, a.H, a.Gw, a.Xw, a.Dw, a.Yw, a.dRw, a.dq, a.dk_, a.dv_,
-        a.dbeta, a.dbeta_tilde, a.dg, a.ddp);
+        q, k, v, dO, beta, bt, a.d, a.cmap, a.H, a.Gw, a.Xw, a.Dw, a.Yw, a.dRw,
+        static_cast<float*>(a.dq), static_cast<float*>(a.dk_), static_cast<float*>(a.dv_),
+        static_cast<float*>(a.dbeta), static_cast<float*>(a.dbeta_tilde), a.dg, a.ddp);
   a.stage("reduce_dd");
   k_reduce_dd<<<a.H, RDD_THR, 0, st>>>(a.ddp, a.ncmax, a.H, a.dd);
   a.stage(nullptr);
@@ -3369,6 +3362,25 @@ static hipError_t run_fwd_bf(const LaunchArgs& a) {
   return hipGetLastError();
 }
 
+// The gradient kernel, with dq, dk, dv, dbeta (, dbeta~) of type TG.
+template <int DK, int DV, typename TG>
+static void launch_intra_bwd(const LaunchArgs& a, const bf16_t* q, const bf16_t* k, const bf16_t* v,
+                             const bf16_t* dO, const bf16_t* beta, const bf16_t* bt, int Tfix) {
+  TG *dq = static_cast<TG*>(a.dq), *dk = static_cast<TG*>(a.dk_), *dv = static_cast<TG*>(a.dv_);
+  TG *db = static_cast<TG*>(a.dbeta), *dbt = static_cast<TG*>(a.dbeta_tilde);
+  if constexpr (DK > 128 || DV > 128) {
+    // head dim 256: passes of 128 dk columns, one workgroup per chunk-head (at
+    // dv = 256 the persistent kernel spills; this one is 25% faster there)
+    k_intra_bwd_wide<DK, DV, TG><<<dim3(a.ncmax, a.H), IB_THR, 0, a.stream>>>(
+        q, k, v, dO, beta, bt, a.d, a.cmap, Tfix, a.H, a.Gw, a.Xq, a.Xs, a.Dq, a.Ds, a.Yq, a.Ys,
+        a.dRq, a.dRs, dq, dk, dv, db, dbt, a.dg, a.ddp);
+  } else {
+    k_intra_bwd_bf<DK, DV, TG><<<dim3(intra_bwd_grid((long)a.ncmax * a.H)), IB_THR, 0, a.stream>>>(
+        q, k, v, dO, beta, bt, a.d, a.cmap, Tfix, a.H, a.Gw, a.Xq, a.Xs, a.Dq, a.Ds, a.Yq, a.Ys, a.dRq,
+        a.dRs, a.ncmax, dq, dk, dv, db, dbt, a.dg, a.ddp);
+  }
+}
+
 template <int DK, int DV>
 static hipError_t run_bwd_bf(const LaunchArgs& a) {
   hipStream_t st = a.stream;
@@ -3460,18 +3472,9 @@ static hipError_t run_bwd_bf(const LaunchArgs& a) {
         a.Ys, a.dRq, a.dRs);
   }
   a.stage("intra_bwd");
-  if constexpr (DK > 128 || DV > 128) {
-    // head dim 256: passes of 128 dk columns, one workgroup per chunk-head (at
-    // dv = 256 the persistent kernel spills; this one is 25% faster there)
-    if (a.ncmax > 0)
-      k_intra_bwd_wide<DK, DV><<<dim3(a.ncmax, a.H), IB_THR, 0, st>>>(
-          q, k, v, dO, beta, bt, a.d, a.cmap, Tfix, a.H, a.Gw, a.Xq, a.Xs, a.Dq, a.Ds, a.Yq, a.Ys,
-          a.dRq, a.dRs, a.dq, a.dk_, a.dv_, a.dbeta, a.dbeta_tilde, a.dg, a.ddp);
-  } else {
-    if (a.ncmax > 0)
-      k_intra_bwd_bf<DK, DV><<<dim3(intra_bwd_grid((long)a.ncmax * a.H)), IB_THR, 0, st>>>(
-          q, k, v, dO, beta, bt, a.d, a.cmap, Tfix, a.H, a.Gw, a.Xq, a.Xs, a.Dq, a.Ds, a.Yq, a.Ys, a.dRq,
-          a.dRs, a.ncmax, a.dq, a.dk_, a.dv_, a.dbeta, a.dbeta_tilde, a.dg, a.ddp);
+  if (a.ncmax > 0) {
+    if (a.grad_bf16) launch_intra_bwd<DK, DV, bf16_t>(a, q, k, v, dO, beta, bt, Tfix);
+    else launch_intra_bwd<DK, DV, float>(a, q, k, v, dO, beta, bt, Tfix);
   }
   a.stage("reduce_dd");
   k_reduce_dd<<<a.H, RDD_THR, 0, st>>>(a.ddp, a.ncmax, a.H, a.dd);

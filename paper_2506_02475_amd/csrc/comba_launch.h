@@ -38,7 +38,10 @@ struct LaunchArgs {
   const void *q, *k, *v, *beta, *beta_tilde, *dO;
   const float *g, *d, *h0, *dht;
   float *o, *ht;
-  float *dq, *dk_, *dv_, *dg, *dbeta, *dbeta_tilde, *dd, *dh0;
+  // dq, dk, dv, dbeta, dbeta_tilde: fp32, or bf16 with grad_bf16 (bf16 inputs)
+  bool grad_bf16;
+  void *dq, *dk_, *dv_, *dbeta, *dbeta_tilde;
+  float *dg, *dd, *dh0;
   // workspace views
   ChunkInfo* cmap;
   SeqInfo* smap;

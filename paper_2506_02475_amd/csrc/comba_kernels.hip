@@ -4,8 +4,8 @@
 //   G_r   in-chunk cumulative log-gate sum_{j<=r} g_j; Gm_r = G_{r-1} (Gm_0 = 0)
 //   X     state entering the chunk, H = S^T in R^{dk x dv} (the paper's S_[t])
 //   L     strictly lower, L_ri = beta_r exp(Gm_r - G_i) k_r.k_i       (Eq. prepare-WY_M)
-//   M     (I + L)^{-1} in fp32 (Section 3.3): forward substitution (fp32 path);
-//         blocked, substitution in the 16x16 diagonal blocks and MFMA for the rest (bf16 path)
+//   M     (I + L)^{-1} in fp32 (Section 3.3), blocked: substitution in the 16x16
+//         diagonal blocks, fp32 MFMA for the rest
 //   A     (Q - d K) K^T masked to r >= i and scaled by exp(G_r - G_i)
 //   R     Diag(beta) V - Diag(beta exp(Gm)) K X
 //   D     M R = U - W X, the pseudo-value term of the matrix form
@@ -24,11 +24,12 @@
 //
 // Kernels, in launch order:
 //   k_seq_map, k_chunk_fill  sequence/chunk tables from cu_seqlens (fixed-length rows too)
-//   k_prep       per chunk-head: G, A, M                        (chunk-parallel)
-//   k_scan_fwd   per (sequence, head, 32-column slice of dv): the sequential
+// (bf16 names; the fp32 path's own list stands at its kernels)
+//   k_prep_bf       per chunk-head: G, A, M                     (chunk-parallel)
+//   k_scan_fwd_bf   per (sequence, head, 32-column slice of dv): the sequential
 //                state recurrence over chunks, fused with the output
-//   k_scan_bwd   the reverse recurrence of the state gradient
-//   k_intra_bwd  per chunk-head gradients dq, dk, dv, dbeta (, dbeta~), dg, partial dd
+//   k_scan_bwd_bf   the reverse recurrence of the state gradient
+//   k_intra_bwd_bf  per chunk-head gradients dq, dk, dv, dbeta (, dbeta~), dg, partial dd
 //   k_reduce_dd  deterministic sum of the partial dd over chunks
 #include <hip/hip_runtime.h>
 
@@ -169,433 +170,584 @@ __global__ __launch_bounds__(NTHR) void k_chunk_fill(const SeqInfo* __restrict__
   }
 }
 
-// ---------------------------------------------------------------------------
-// k_prep: per chunk-head, cumulative gates G, the masked score matrix A and the
-// UT-transform inverse M = (I + L)^{-1} (Eq. prepare-WY_M), all fp32.
-// ---------------------------------------------------------------------------
-template <typename Tin, int DK>
-__global__ __launch_bounds__(NTHR) void k_prep(const Tin* __restrict__ q, const Tin* __restrict__ k,
-                                               const float* __restrict__ g,
-                                               const Tin* __restrict__ beta_tilde,
-                                               const float* __restrict__ d,
-                                               const ChunkInfo* __restrict__ cmap, int H,
-                                               float* __restrict__ Mw, float* __restrict__ Aw,
-                                               float* __restrict__ Gw) {
-  constexpr bool F32 = is_f32<Tin>::value;
-  constexpr int LDK = DK + Pad<Tin>::value;
-  constexpr int LDL = CH + 4;
-  __shared__ __align__(16) Tin Ks[CH * LDK];
-  __shared__ __align__(16) Tin Qs[CH * LDK];
-  __shared__ __align__(16) float Ls[CH * LDL];
-  __shared__ float Gs[CH], Bs[CH];
+// Chunk and sequence tables of the kernels: for fixed-length rows
+// (Tfix >= 0 tokens each) in closed form, for packed sequences (Tfix < 0) from
+// the tables of k_seq_map and k_chunk_fill.
+__device__ __forceinline__ ChunkInfo chunk_at(const ChunkInfo* cmap, int c, int Tfix) {
+  if (Tfix >= 0) {
+    const int ncs = max(1, (Tfix + CH - 1) / CH), s = c / ncs, i = c - s * ncs;
+    return ChunkInfo{s * Tfix + i * CH, min(CH, Tfix - i * CH), s, 0};
+  }
+  return cmap[c];
+}
+__device__ __forceinline__ SeqInfo seq_at(const SeqInfo* smap, int s, int Tfix) {
+  if (Tfix >= 0) {
+    const int ncs = (Tfix + CH - 1) / CH;
+    return SeqInfo{s * ncs, ncs, s * Tfix, Tfix};
+  }
+  return smap[s];
+}
 
-  const ChunkInfo ci = cmap[blockIdx.x];
+// D_jb = (I + L_jb,jb)^{-1} of the 16 x 16 diagonal block jb of L (LDS, stride
+// LDL): replaces the block and is left in every mb[i] in the accumulator layout.
+template <int LDL>
+__device__ __forceinline__ void invert_diagonal(float* Ls, int jb, floatx4 (&mb)[4]) {
+  const int lane = lane_id(), r16 = lane & 15, g4 = lane >> 4;
+  // lane (g4, r16) solves column r16 of the diagonal block by forward
+  // substitution in fp32 (the four 16-lane groups redundantly)
+  float* Lb = Ls + 16 * jb * LDL + 16 * jb;
+  float x[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) x[i] = (i == r16) ? 1.f : 0.f;
+#pragma unroll
+  for (int i = 1; i < 16; ++i) {
+    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+#pragma unroll
+    for (int m = 0; m < i; m += 4) {
+      const float4 lv = *reinterpret_cast<const float4*>(Lb + i * LDL + m);
+      s0 += lv.x * x[m];
+      if (m + 1 < i) s1 += lv.y * x[m + 1];
+      if (m + 2 < i) s2 += lv.z * x[m + 2];
+      if (m + 3 < i) s3 += lv.w * x[m + 3];
+    }
+    if (i > r16) x[i] = -((s0 + s1) + (s2 + s3));
+  }
+  // D_jb in the accumulator layout (rows 4 g4 + e of column r16) replaces
+  // L_jb,jb in LDS; only this wave reads that block, and its reads are done
+  floatx4 dm;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    dm[e] = g4 == 0 ? x[e] : g4 == 1 ? x[4 + e] : g4 == 2 ? x[8 + e] : x[12 + e];
+    Lb[(4 * g4 + e) * LDL + r16] = dm[e];
+  }
+  mb[0] = mb[1] = mb[2] = mb[3] = dm;
+}
+
+// Block column J of M = (I + L)^{-1} below the diagonal, in the accumulator
+// layout of the 16x16 fp32 MFMA: on entry mb[J] = D_J; on exit mb[i] = M_iJ for
+// i > J.  The L_ik and D_i blocks come from LDS (row-major, stride LDL, D_i in
+// the diagonal blocks).  Each product runs its k index in the order
+// 4 (lane / 16) + e at step e, so that an accumulator is directly the B operand
+// of the next product and the A operand of a step is one 16-byte LDS read.
+template <int J, int LDL>
+__device__ __forceinline__ void solve_block_column(const float* Ls, floatx4 (&mb)[4]) {
+  const int lane = lane_id(), r16 = lane & 15, g4 = lane >> 4;
+#pragma unroll
+  for (int i = J + 1; i < 4; ++i) {
+    floatx4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kb = J; kb < i; ++kb) {
+      const float4 a = *reinterpret_cast<const float4*>(Ls + (16 * i + r16) * LDL + 16 * kb + 4 * g4);
+      t = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, mb[kb][0], t, 0, 0, 0);
+      t = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, mb[kb][1], t, 0, 0, 0);
+      t = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, mb[kb][2], t, 0, 0, 0);
+      t = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, mb[kb][3], t, 0, 0, 0);
+    }
+    const float4 dd = *reinterpret_cast<const float4*>(Ls + (16 * i + r16) * LDL + 16 * i + 4 * g4);
+    floatx4 u = {0.f, 0.f, 0.f, 0.f};
+    u = __builtin_amdgcn_mfma_f32_16x16x4f32(dd.x, t[0], u, 0, 0, 0);
+    u = __builtin_amdgcn_mfma_f32_16x16x4f32(dd.y, t[1], u, 0, 0, 0);
+    u = __builtin_amdgcn_mfma_f32_16x16x4f32(dd.z, t[2], u, 0, 0, 0);
+    u = __builtin_amdgcn_mfma_f32_16x16x4f32(dd.w, t[3], u, 0, 0, 0);
+    mb[i] = -u;
+  }
+}
+
+// Block column J of M (mb as left by solve_block_column) into LDS over L.
+template <int J, int LDL>
+__device__ __forceinline__ void put_block_column(float* Ls, const floatx4 (&mb)[4]) {
+  const int lane = lane_id(), r16 = lane & 15, g4 = lane >> 4;
+#pragma unroll
+  for (int i = J + 1; i < 4; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) Ls[(16 * i + 4 * g4 + e) * LDL + 16 * J + r16] = mb[i][e];
+}
+
+// ===========================================================================
+// fp32 path (dk = dv = 64).  fp32 MFMA throughout (16x16x4, 32 cycles), so a
+// chain step is bound by its products; only those that the next state waits
+// for stay on the chain.  With W = M Diag(s) K and U = M Diag(beta) V
+// (s = beta~ e^{Gm}), D = U - W X and X' = e^{G_63} X + K~^T D: two products
+// per step instead of five, everything else chunk-parallel.  Backward, with
+// dD0 = A^T dO and P = (Q - d K)^T Diag(e^G) dO: dD = dD0 + K~ Y,
+// Y' = e^{G_63} Y + P - W^T dD, and dR = M^T dD afterwards.
+// Kernels: k_prep (G, M, W, U), k_out, k_bprep (dD0, P), k_states (the forward
+// and the reverse chain, side by side in one grid), k_dr, k_intra_bwd.
+// Forward + stateless backward at B2 T1000 H8: 324 -> 132 us; the tiny forward
+// (B1 T256 H1): 42 -> 26 us (before: five products per step and a one-wave
+// substitution of 64 rows; a step took 5.3 us, now 1.4).  Errors against 64
+// bits are unchanged (2.4e-6 dg, 3.5e-7 o).
+//
+// A product's k index runs 16 kb + 4 (lane / 16) + e at step e of block kb, so
+// that an operand with k contiguous is one 16-byte read for four steps.
+// ===========================================================================
+constexpr int FD = 64;        // head size
+constexpr int FLD = FD + 4;   // LDS row stride (floats): 16-byte rows, conflict-free both ways
+constexpr int FT = FD * FD;   // elements of one 64 x 64 tile
+
+__device__ __forceinline__ floatx4 mfma4(float a, float b, const floatx4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+// Operand fetch at block kb for this lane's row / column x (16 t + lane % 16):
+// rows with k contiguous, or k down the rows.
+struct RowOp {
+  const float* p;
+  __device__ __forceinline__ floatx4 get(int x, int kb) const {
+    const float4 v = *reinterpret_cast<const float4*>(p + x * FLD + 16 * kb + 4 * (lane_id() >> 4));
+    return floatx4{v.x, v.y, v.z, v.w};
+  }
+};
+struct ColOp {
+  const float* p;
+  __device__ __forceinline__ floatx4 get(int x, int kb) const {
+    const float* c = p + (16 * kb + 4 * (lane_id() >> 4)) * FLD + x;
+    return floatx4{c[0], c[FLD], c[2 * FLD], c[3 * FLD]};
+  }
+};
+// acc[nt] += A(rows 16 w ..) B(columns 16 nt ..) over k blocks kb0 .. kb1 - 1
+template <typename OA, typename OB>
+__device__ __forceinline__ void fmm(floatx4 (&acc)[4], const OA& A, const OB& B, int w, int kb0 = 0, int kb1 = 4) {
+  const int r16 = lane_id() & 15;
+  for (int kb = kb0; kb < kb1; ++kb) {
+    const floatx4 a = A.get(16 * w + r16, kb);
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+      const floatx4 b = B.get(16 * nt + r16, kb);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[nt] = mfma4(a[e], b[e], acc[nt]);
+    }
+  }
+}
+__device__ __forceinline__ void fzero(floatx4 (&acc)[4]) { acc[0] = acc[1] = acc[2] = acc[3] = zero4(); }
+// W is stored in the order its rows are consumed as the operand of W X: lane
+// (g, i)'s four values of row 16 rt + i, columns 16 kb + 4 g .. are 16 bytes at
+// ((4 rt + kb) 64 + lane) 16.
+__device__ __forceinline__ int wfrag(int r, int c) {
+  return ((((r >> 4) * 4 + (c >> 4)) * 64 + ((c >> 2) & 3) * 16 + (r & 15)) << 2) + (c & 3);
+}
+
+// A tile of up to 64 rows (zero past `len`) into LDS, rows of 64 floats at stride gs.
+struct FTile {
+  float4 r[4];
+  __device__ __forceinline__ void load(const float* g, long gs, int len) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = (threadIdx.x >> 4) + 16 * i, c = (threadIdx.x & 15) * 4;
+      r[i] = row < len ? *reinterpret_cast<const float4*>(g + (long)row * gs + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+  __device__ __forceinline__ void store(float* s) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<float4*>(s + ((threadIdx.x >> 4) + 16 * i) * FLD + (threadIdx.x & 15) * 4) = r[i];
+  }
+};
+
+// Per chunk-head: G, M = (I + L)^{-1}, W and U.  Mw may be NULL (forward only).
+// U goes to rows of stride us at U + (row 0): the D slots of the workspace, or
+// the output rows of the forward (rows past the chunk end not written).
+__global__ __launch_bounds__(NTHR) void k_prep(const float* __restrict__ k, const float* __restrict__ v,
+                                               const float* __restrict__ g, const float* __restrict__ beta,
+                                               const float* __restrict__ beta_tilde,
+                                               const ChunkInfo* __restrict__ cmap, int Tfix, int H,
+                                               float* __restrict__ Mw, float* __restrict__ Ww,
+                                               float* __restrict__ Gw, float* __restrict__ U, bool u_rows) {
+  __shared__ __align__(16) float Ks[CH * FLD], Vs[CH * FLD], Ls[CH * FLD];
+  __shared__ float Gs[CH], Bts[CH];
+  const ChunkInfo ci = chunk_at(cmap, blockIdx.x, Tfix);
   if (ci.len <= 0) return;
   const int h = blockIdx.y;
-  const long chh = (long)blockIdx.x * H + h;
-  const long tok = (long)ci.tok0 * H + h;
-  const int w = wave_id(), lane = lane_id();
-
+  const long chh = (long)blockIdx.x * H + h, tok = (long)ci.tok0 * H + h;
+  const int w = wave_id(), lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
+  const long grow = tok + (long)min(lane, ci.len - 1) * H;
+  const float g_in = g[grow], bt_in = beta_tilde[grow], b_in = beta[grow];
+  FTile kr, vr;
+  kr.load(k + tok * FD, (long)H * FD, ci.len);
+  vr.load(v + tok * FD, (long)H * FD, ci.len);
+  // every wave forms the row values (same values, no branch)
+  const float G = wave_prefix_sum(lane < ci.len ? g_in : 0.f);
+  const float bt = lane < ci.len ? bt_in : 0.f, bb = lane < ci.len ? b_in : 0.f;
+  Gs[lane] = G;
+  Bts[lane] = bt;
+  if (w == 0) Gw[chh * CH + lane] = G;
+  kr.store(Ks);
+  vr.store(Vs);
+  __syncthreads();
   {
-    TileRegs<Tin, CH, DK> kr, qr;
-    kr.load(k + tok * DK, (long)H * DK, ci.len);
-    qr.load(q + tok * DK, (long)H * DK, ci.len);
-    kr.store(Ks, LDK);
-    qr.store(Qs, LDK);
-  }
-  if (w == 0) {
-    const float gr = lane < ci.len ? g[tok + (long)lane * H] : 0.f;
-    const float G = wave_prefix_sum(gr);
-    Gs[lane] = G;
-    Bs[lane] = lane < ci.len ? to_f(beta_tilde[tok + (long)lane * H]) : 0.f;  // feedback strength
-    Gw[chh * CH + lane] = G;
+    floatx4 kk[4];
+    fzero(kk);
+    fmm(kk, RowOp{Ks}, RowOp{Ks}, w);
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = 16 * w + 4 * g4 + e, c = 16 * nt + r16;
+        Ls[r * FLD + c] = r > c ? Bts[r] * __expf(Gs[r - 1] - Gs[c]) * kk[nt][e] : 0.f;
+      }
   }
   __syncthreads();
-
-  // A_kk = K K^T and A_qk = Q K^T for rows 16w..16w+15
-  floatx4 akk[1][4], aqk[1][4];
-  zero_acc(akk);
-  zero_acc(aqk);
-  mma<F32, 1, 4, DK>(akk, Ks + 16 * w * LDK, LDK, Ks, LDK);
-  mma<F32, 1, 4, DK>(aqk, Qs + 16 * w * LDK, LDK, Ks, LDK);
-  const float dh = d[h];
+  // M by 16x16 blocks, one block column per wave (see the bf16 path's k_prep_bf)
+  floatx4 mb[4];
+  invert_diagonal<FLD>(Ls, w, mb);
+  __syncthreads();
+  switch (w) {
+    case 0: solve_block_column<0, FLD>(Ls, mb); break;
+    case 1: solve_block_column<1, FLD>(Ls, mb); break;
+    case 2: solve_block_column<2, FLD>(Ls, mb); break;
+    default: break;
+  }
+  __syncthreads();
+  switch (w) {
+    case 0: put_block_column<0, FLD>(Ls, mb); break;
+    case 1: put_block_column<1, FLD>(Ls, mb); break;
+    case 2: put_block_column<2, FLD>(Ls, mb); break;
+    default: break;
+  }
+  // Diag(s) K and Diag(beta) V in place, for the products below
+  {
+    const float s = bt * (lane > 0 ? __expf(Gs[max(lane - 1, 0)]) : 1.f);
+#pragma unroll
+    for (int c = 16 * w; c < 16 * w + 16; c += 4) {
+      float4* kp = reinterpret_cast<float4*>(Ks + lane * FLD + c);
+      float4* vp = reinterpret_cast<float4*>(Vs + lane * FLD + c);
+      const float4 kv = *kp, vv = *vp;
+      *kp = make_float4(s * kv.x, s * kv.y, s * kv.z, s * kv.w);
+      *vp = make_float4(bb * vv.x, bb * vv.y, bb * vv.z, bb * vv.w);
+    }
+  }
+  __syncthreads();
+  if (Mw) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = (threadIdx.x >> 4) + 16 * i, c = (threadIdx.x & 15) * 4;
+      *reinterpret_cast<float4*>(Mw + chh * FT + row * FD + c) = *reinterpret_cast<const float4*>(Ls + row * FLD + c);
+    }
+  }
+  // M is lower triangular: k blocks up to the row tile
+  floatx4 wa[4], ua[4];
+  fzero(wa);
+  fzero(ua);
+  fmm(wa, RowOp{Ls}, ColOp{Ks}, w, 0, w + 1);
+  fmm(ua, RowOp{Ls}, ColOp{Vs}, w, 0, w + 1);
+  float* ub = u_rows ? U + tok * FD : U + chh * FT;
+  const long us = u_rows ? (long)H * FD : FD;
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int r = 16 * w + acc_row(0, e), c = acc_col(nt);
-      const float kk = akk[0][nt][e];
-      float a = 0.f, l = 0.f;
-      if (r >= c) a = (aqk[0][nt][e] - dh * kk) * __expf(Gs[r] - Gs[c]);
-      if (r > c) {
-        const float gm = Gs[r - 1];
-        l = Bs[r] * __expf(gm - Gs[c]) * kk;
-      }
-      Aw[chh * CH * CH + r * CH + c] = a;
-      Ls[r * LDL + c] = l;
+      const int r = 16 * w + 4 * g4 + e, c = 16 * nt + r16;
+      Ww[chh * FT + wfrag(r, c)] = wa[nt][e];
+      if (!u_rows || r < ci.len) ub[r * us + c] = ua[nt][e];
     }
+}
+
+// The masked scores A = (Q - d K) K^T o e^{G_r - G_c} (r >= c) into LDS; Qt
+// holds Q - d K.  Ends with the wave's own rows written (no barrier).
+__device__ __forceinline__ void f32_scores(float* As, const float* Qt, const float* Ks, const float* Gs, int w) {
+  const int lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
+  floatx4 a[4];
+  fzero(a);
+  fmm(a, RowOp{Qt}, RowOp{Ks}, w);
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = 16 * w + 4 * g4 + e, c = 16 * nt + r16;
+      As[r * FLD + c] = r >= c ? a[nt][e] * __expf(Gs[r] - Gs[c]) : 0.f;
+    }
+}
+__device__ __forceinline__ void f32_qt(float* Qt, const FTile& qr, const FTile& kr, float dh) {
+  FTile t;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    t.r[i] = make_float4(qr.r[i].x - dh * kr.r[i].x, qr.r[i].y - dh * kr.r[i].y, qr.r[i].z - dh * kr.r[i].z,
+                         qr.r[i].w - dh * kr.r[i].w);
+  t.store(Qt);
+}
+
+// O = Diag(e^G)(Q - d K) X + A D per chunk-head.  D comes from the rows of o
+// themselves (d_rows: left there by the scan) or from the workspace.
+__global__ __launch_bounds__(NTHR) void k_out(const float* __restrict__ q, const float* __restrict__ k,
+                                              const float* __restrict__ d, const ChunkInfo* __restrict__ cmap,
+                                              int Tfix, int H, const float* __restrict__ Gw,
+                                              const float* __restrict__ Xw, const float* Dw, float* o,
+                                              bool d_rows) {
+  __shared__ __align__(16) float Ks[CH * FLD], Qt[CH * FLD], Xs[CH * FLD], Ds[CH * FLD], As[CH * FLD];
+  __shared__ float Gs[CH];
+  const ChunkInfo ci = chunk_at(cmap, blockIdx.x, Tfix);
+  if (ci.len <= 0) return;
+  const int h = blockIdx.y;
+  const long chh = (long)blockIdx.x * H + h, tok = (long)ci.tok0 * H + h;
+  const int w = wave_id(), lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
+  FTile kr, qr, xr, dr;
+  kr.load(k + tok * FD, (long)H * FD, ci.len);
+  qr.load(q + tok * FD, (long)H * FD, ci.len);
+  xr.load(Xw + chh * FT, FD, CH);
+  if (d_rows) dr.load(o + tok * FD, (long)H * FD, ci.len);
+  else dr.load(Dw + chh * FT, FD, CH);
+  if (w == 0) Gs[lane] = Gw[chh * CH + lane];
+  kr.store(Ks);
+  f32_qt(Qt, qr, kr, d[h]);
+  xr.store(Xs);
+  dr.store(Ds);
   __syncthreads();
-
-  // M = (I + L)^{-1}: lane j solves column j by forward substitution,
-  // x_i = -sum_{j <= m < i} L_im x_m, with x_j = 1 (rows processed in order).
-  if (w == 0) {
-    const int j = lane;
-    float x[CH];
+  f32_scores(As, Qt, Ks, Gs, w);
+  floatx4 acc[4];
+  fzero(acc);
+  fmm(acc, RowOp{Qt}, ColOp{Xs}, w);
 #pragma unroll
-    for (int i = 0; i < CH; ++i) x[i] = (i == j) ? 1.f : 0.f;
+  for (int e = 0; e < 4; ++e) {
+    const float eg = __expf(Gs[16 * w + 4 * g4 + e]);
 #pragma unroll
-    for (int i = 1; i < CH; ++i) {
-      float s = 0.f;
-#pragma unroll
-      for (int m = 0; m < i; m += 4) {
-        const float4 lv = *reinterpret_cast<const float4*>(Ls + i * LDL + m);
-        s += lv.x * x[m];
-        if (m + 1 < i) s += lv.y * x[m + 1];
-        if (m + 2 < i) s += lv.z * x[m + 2];
-        if (m + 3 < i) s += lv.w * x[m + 3];
-      }
-      if (i > j) x[i] = -s;
-    }
-    float* Mo = Mw + chh * CH * CH;
-#pragma unroll
-    for (int i = 0; i < CH; ++i) Mo[i * CH + j] = x[i];
+    for (int nt = 0; nt < 4; ++nt) acc[nt][e] *= eg;
   }
+  // only this wave's rows of A are read: no barrier
+  fmm(acc, RowOp{As}, ColOp{Ds}, w, 0, w + 1);
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = 16 * w + 4 * g4 + e;
+      if (r < ci.len) o[(tok + (long)r * H) * FD + 16 * nt + r16] = acc[nt][e];
+    }
 }
 
-// ---------------------------------------------------------------------------
-// k_scan_fwd: one workgroup per (sequence, head, 32-wide dv slice) walks the
-// chunks of its sequence in order, keeping its dk x 32 state slice in fp32.
-//   OUT   : write the outputs o (forward entry point)
-//   STORE : save the entering state X and D per chunk (backward recompute)
-// ---------------------------------------------------------------------------
-template <typename Tin, int DK, int DV, bool OUT, bool STORE>
-__global__ __launch_bounds__(NTHR, 1) void k_scan_fwd(
-    const Tin* __restrict__ q, const Tin* __restrict__ k, const Tin* __restrict__ v,
-    const Tin* __restrict__ beta, const Tin* __restrict__ beta_tilde, const float* __restrict__ d,
-    const float* __restrict__ h0, const ChunkInfo* __restrict__ cmap,
-    const SeqInfo* __restrict__ smap, int H, const float* __restrict__ Mw,
-    const float* __restrict__ Aw, const float* __restrict__ Gw, float* __restrict__ o,
-    float* __restrict__ ht, float* __restrict__ Xw, float* __restrict__ Dw) {
-  constexpr bool F32 = is_f32<Tin>::value;
-  constexpr int BV = 32, NTV = BV / 16, XMT = DK / 64;
-  constexpr int PI = Pad<Tin>::value;
-  constexpr int LDK = DK + PI, LDC = CH + PI, LDV = BV + PI;
-  constexpr int LDF = CH + 4, LDX = DK + 4;
-  __shared__ __align__(16) Tin Ks[CH * LDK];
-  __shared__ __align__(16) Tin KsT[DK * LDC];
-  __shared__ __align__(16) Tin Qs[OUT ? CH * LDK : 8];
-  __shared__ __align__(16) Tin Vs[CH * LDV];
-  __shared__ __align__(16) float Ms[CH * LDF];
-  __shared__ __align__(16) float As[OUT ? CH * LDF : 4];
-  __shared__ __align__(16) float XT[BV * LDX];
-  __shared__ __align__(16) float RT[BV * LDF];
-  __shared__ __align__(16) float DT[OUT ? BV * LDF : 4];
-  __shared__ __align__(16) float DgT[BV * LDF];
-  __shared__ float Gs[CH], Bs[CH], Bts[CH];
-
-  const int s = blockIdx.x, h = blockIdx.y, j0 = blockIdx.z * BV;
-  const SeqInfo si = smap[s];
-  const int w = wave_id();
-  const long soff = ((long)s * H + h) * DK * DV;
-  const float dh = d[h];
-
-  floatx4 X[XMT][NTV];
+// dD0 = A^T dO and P = (Q - d K)^T Diag(e^G) dO per chunk-head, into the dR and Y slots.
+__global__ __launch_bounds__(NTHR) void k_bprep(const float* __restrict__ q, const float* __restrict__ k,
+                                                const float* __restrict__ dO, const float* __restrict__ d,
+                                                const ChunkInfo* __restrict__ cmap, int Tfix, int H,
+                                                const float* __restrict__ Gw, float* __restrict__ dRw,
+                                                float* __restrict__ Yw) {
+  __shared__ __align__(16) float Ks[CH * FLD], Qt[CH * FLD], Os[CH * FLD], As[CH * FLD];
+  __shared__ float Gs[CH];
+  const ChunkInfo ci = chunk_at(cmap, blockIdx.x, Tfix);
+  if (ci.len <= 0) return;
+  const int h = blockIdx.y;
+  const long chh = (long)blockIdx.x * H + h, tok = (long)ci.tok0 * H + h;
+  const int w = wave_id(), lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
+  FTile kr, qr, dr;
+  kr.load(k + tok * FD, (long)H * FD, ci.len);
+  qr.load(q + tok * FD, (long)H * FD, ci.len);
+  dr.load(dO + tok * FD, (long)H * FD, ci.len);
+  if (w == 0) Gs[lane] = Gw[chh * CH + lane];
+  kr.store(Ks);
+  f32_qt(Qt, qr, kr, d[h]);
+  dr.store(Os);
+  __syncthreads();
+  f32_scores(As, Qt, Ks, Gs, w);
+  __syncthreads();
+  // A is lower triangular: A^T's k blocks from the row tile on
+  floatx4 acc[4];
+  fzero(acc);
+  fmm(acc, ColOp{As}, ColOp{Os}, w, w, 4);
 #pragma unroll
-  for (int mt = 0; mt < XMT; ++mt)
+  for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
-    for (int nt = 0; nt < NTV; ++nt)
+    for (int e = 0; e < 4; ++e) dRw[chh * FT + (16 * w + 4 * g4 + e) * FD + 16 * nt + r16] = acc[nt][e];
+  // rows of Q - d K scaled by e^G (K's tile is free: every wave is past the scores)
+  {
+    const float eg = __expf(Gs[lane]);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int i = (DK / 4) * w + acc_row(mt, e), jj = acc_col(nt);
-        X[mt][nt][e] = h0 ? h0[soff + (long)i * DV + j0 + jj] : 0.f;
-        XT[jj * LDX + i] = X[mt][nt][e];
-      }
-
-  // registers holding the next chunk's tiles (loaded one chunk ahead)
-  TileRegs<Tin, CH, DK> pk, pq;
-  TileRegs<Tin, CH, BV> pv;
-  TileRegs<float, CH, CH> pm, pa;
-  float pg = 0.f, pb = 0.f, pbt = 0.f;
-  auto issue = [&](int cc) {
-    const int len = min(CH, si.len - cc * CH);
-    const long chh = (long)(si.chunk0 + cc) * H + h;
-    const long tok = (long)(si.tok0 + cc * CH) * H + h;
-    pk.load(k + tok * DK, (long)H * DK, len);
-    if constexpr (OUT) pq.load(q + tok * DK, (long)H * DK, len);
-    pv.load(v + tok * DV + j0, (long)H * DV, len);
-    pm.load(Mw + chh * CH * CH, CH, CH);
-    if constexpr (OUT) pa.load(Aw + chh * CH * CH, CH, CH);
-    if (threadIdx.x < CH) {
-      const int r = threadIdx.x;
-      pg = Gw[chh * CH + r];
-      pb = r < len ? to_f(beta[tok + (long)r * H]) : 0.f;
-      pbt = r < len ? to_f(beta_tilde[tok + (long)r * H]) : 0.f;
+    for (int c = 16 * w; c < 16 * w + 16; c += 4) {
+      const float4 x = *reinterpret_cast<const float4*>(Qt + lane * FLD + c);
+      *reinterpret_cast<float4*>(Ks + lane * FLD + c) = make_float4(eg * x.x, eg * x.y, eg * x.z, eg * x.w);
     }
-  };
-  if (si.nchunks > 0) issue(0);
-
-  for (int cc = 0; cc < si.nchunks; ++cc) {
-    const long chh = (long)(si.chunk0 + cc) * H + h;
-    const long tok = (long)(si.tok0 + cc * CH) * H + h;
-    ChunkInfo ci;
-    ci.len = min(CH, si.len - cc * CH);
-    __syncthreads();
-    pk.store(Ks, LDK);
-    pk.store_t(KsT, LDC);
-    if constexpr (OUT) pq.store(Qs, LDK);
-    pv.store(Vs, LDV);
-    pm.store(Ms, LDF);
-    if constexpr (OUT) pa.store(As, LDF);
-    if (threadIdx.x < CH) {
-      Gs[threadIdx.x] = pg;
-      Bs[threadIdx.x] = pb;
-      Bts[threadIdx.x] = pbt;
-    }
-    if constexpr (STORE) {
-#pragma unroll
-      for (int mt = 0; mt < XMT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NTV; ++nt)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int i = (DK / 4) * w + acc_row(mt, e), jj = acc_col(nt);
-            Xw[chh * DK * DV + (long)i * DV + j0 + jj] = X[mt][nt][e];
-          }
-    }
-    __syncthreads();
-    if (cc + 1 < si.nchunks) issue(cc + 1);
-    const float Glast = Gs[CH - 1];
-
-    // K X and Q X for rows 16w..16w+15; R = Diag(beta) V - Diag(beta~ exp Gm) K X
-    floatx4 kx[1][NTV], qx[1][NTV];
-    zero_acc(kx);
-    mma<F32, 1, NTV, DK>(kx, Ks + 16 * w * LDK, LDK, XT, LDX);
-    if constexpr (OUT) {
-      zero_acc(qx);
-      mma<F32, 1, NTV, DK>(qx, Qs + 16 * w * LDK, LDK, XT, LDX);
-    }
-    floatx4 oacc[1][NTV];
-#pragma unroll
-    for (int nt = 0; nt < NTV; ++nt)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = 16 * w + acc_row(0, e), jj = acc_col(nt);
-        const float kxv = kx[0][nt][e];
-        const float gm = r > 0 ? Gs[r - 1] : 0.f;
-        RT[jj * LDF + r] = Bs[r] * to_f(Vs[r * LDV + jj]) - Bts[r] * __expf(gm) * kxv;
-        if constexpr (OUT) oacc[0][nt][e] = __expf(Gs[r]) * (qx[0][nt][e] - dh * kxv);
-      }
-    __syncthreads();
-
-    // D = M R
-    floatx4 dl[1][NTV];
-    zero_acc(dl);
-    mma<F32, 1, NTV, CH>(dl, Ms + 16 * w * LDF, LDF, RT, LDF);
-#pragma unroll
-    for (int nt = 0; nt < NTV; ++nt)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = 16 * w + acc_row(0, e), jj = acc_col(nt);
-        const float dv = dl[0][nt][e];
-        if constexpr (OUT) DT[jj * LDF + r] = dv;
-        DgT[jj * LDF + r] = __expf(Glast - Gs[r]) * dv;
-        if constexpr (STORE) Dw[chh * CH * DV + (long)r * DV + j0 + jj] = dv;
-      }
-    __syncthreads();
-
-    // X' = exp(G_63) X + K^T Diag(exp(G_63 - G)) D
-    const float gC = __expf(Glast);
-#pragma unroll
-    for (int mt = 0; mt < XMT; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < NTV; ++nt) X[mt][nt] *= gC;
-    mma<F32, XMT, NTV, CH>(X, KsT + (DK / 4) * w * LDC, LDC, DgT, LDF);
-
-    // O = Diag(exp G)(Q - d K) X + A D
-    if constexpr (OUT) {
-      mma<F32, 1, NTV, CH>(oacc, As + 16 * w * LDF, LDF, DT, LDF);
-#pragma unroll
-      for (int nt = 0; nt < NTV; ++nt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = 16 * w + acc_row(0, e), jj = acc_col(nt);
-          if (r < ci.len) o[(tok + (long)r * H) * DV + j0 + jj] = oacc[0][nt][e];
-        }
-    }
-#pragma unroll
-    for (int mt = 0; mt < XMT; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < NTV; ++nt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          XT[acc_col(nt) * LDX + (DK / 4) * w + acc_row(mt, e)] = X[mt][nt][e];
   }
-  if (ht) {
+  __syncthreads();
+  fzero(acc);
+  fmm(acc, ColOp{Ks}, ColOp{Os}, w);
 #pragma unroll
-    for (int mt = 0; mt < XMT; ++mt)
+  for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
-      for (int nt = 0; nt < NTV; ++nt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int i = (DK / 4) * w + acc_row(mt, e), jj = acc_col(nt);
-          ht[soff + (long)i * DV + j0 + jj] = X[mt][nt][e];
-        }
-  }
+    for (int e = 0; e < 4; ++e) Yw[chh * FT + (16 * w + 4 * g4 + e) * FD + 16 * nt + r16] = acc[nt][e];
 }
 
-// ---------------------------------------------------------------------------
-// k_scan_bwd: reverse recurrence of Y = dL/d(state leaving the chunk).
-// Saves Y (as seen by each chunk) and dR = M^T dD per chunk for k_intra_bwd.
-// ---------------------------------------------------------------------------
-template <typename Tin, int DK, int DV>
-__global__ __launch_bounds__(NTHR, 1) void k_scan_bwd(
-    const Tin* __restrict__ q, const Tin* __restrict__ k, const Tin* __restrict__ dO,
-    const Tin* __restrict__ beta_tilde, const float* __restrict__ d, const float* __restrict__ dht,
-    const ChunkInfo* __restrict__ cmap, const SeqInfo* __restrict__ smap, int H,
-    const float* __restrict__ Mw, const float* __restrict__ Aw, const float* __restrict__ Gw,
-    float* __restrict__ dh0, float* __restrict__ Yw, float* __restrict__ dRw) {
-  constexpr bool F32 = is_f32<Tin>::value;
-  constexpr int BV = 32, NTV = BV / 16, XMT = DK / 64;
-  constexpr int PI = Pad<Tin>::value;
-  constexpr int LDK = DK + PI, LDC = CH + PI;
-  constexpr int LDF = CH + 4, LDX = DK + 4;
-  __shared__ __align__(16) Tin Ks[CH * LDK];
-  __shared__ __align__(16) Tin KsT[DK * LDC];
-  __shared__ __align__(16) Tin QsT[DK * LDC];
-  __shared__ __align__(16) Tin dOT[BV * LDC];
-  __shared__ __align__(16) float AsT[CH * LDF];
-  __shared__ __align__(16) float MsT[CH * LDF];
-  __shared__ __align__(16) float YT[BV * LDX];
-  __shared__ __align__(16) float dDT[BV * LDF];
-  __shared__ __align__(16) float PgT[BV * LDF];
-  __shared__ __align__(16) float W2T[BV * LDF];
-  __shared__ float Gs[CH], Bs[CH];
-
-  const int s = blockIdx.x, h = blockIdx.y, j0 = blockIdx.z * BV;
-  const SeqInfo si = smap[s];
-  const int w = wave_id();
-  const long soff = ((long)s * H + h) * DK * DV;
-  const float dh = d[h];
-
-  floatx4 Y[XMT][NTV];
+// dR = M^T dD per chunk-head, in place.
+__global__ __launch_bounds__(NTHR) void k_dr(const ChunkInfo* __restrict__ cmap, int Tfix, int H,
+                                             const float* __restrict__ Mw, float* __restrict__ dRw) {
+  __shared__ __align__(16) float Ms[CH * FLD], Ds[CH * FLD];
+  const ChunkInfo ci = chunk_at(cmap, blockIdx.x, Tfix);
+  if (ci.len <= 0) return;
+  const long chh = (long)blockIdx.x * H + blockIdx.y;
+  const int w = wave_id(), lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
+  FTile mr, dr;
+  mr.load(Mw + chh * FT, FD, CH);
+  dr.load(dRw + chh * FT, FD, CH);
+  mr.store(Ms);
+  dr.store(Ds);
+  __syncthreads();
+  floatx4 acc[4];
+  fzero(acc);
+  fmm(acc, ColOp{Ms}, ColOp{Ds}, w, w, 4);
 #pragma unroll
-  for (int mt = 0; mt < XMT; ++mt)
+  for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
-    for (int nt = 0; nt < NTV; ++nt)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int i = (DK / 4) * w + acc_row(mt, e), jj = acc_col(nt);
-        Y[mt][nt][e] = dht ? dht[soff + (long)i * DV + j0 + jj] : 0.f;
-        YT[jj * LDX + i] = Y[mt][nt][e];
-      }
+    for (int e = 0; e < 4; ++e) dRw[chh * FT + (16 * w + 4 * g4 + e) * FD + 16 * nt + r16] = acc[nt][e];
+}
 
-  TileRegs<Tin, CH, DK> pk, pq;
-  TileRegs<Tin, CH, BV> pdo;
-  TileRegs<float, CH, CH> pm, pa;
-  float pg = 0.f, pb = 0.f;
-  auto issue = [&](int cc) {
-    const int len = min(CH, si.len - cc * CH);
-    const long chh = (long)(si.chunk0 + cc) * H + h;
-    const long tok = (long)(si.tok0 + cc * CH) * H + h;
-    pk.load(k + tok * DK, (long)H * DK, len);
-    pq.load(q + tok * DK, (long)H * DK, len);
-    pdo.load(dO + tok * DV + j0, (long)H * DV, len);
-    pa.load(Aw + chh * CH * CH, CH, CH);
-    pm.load(Mw + chh * CH * CH, CH, CH);
-    if (threadIdx.x < CH) {
-      const int r = threadIdx.x;
-      pg = Gw[chh * CH + r];
-      pb = r < len ? to_f(beta_tilde[tok + (long)r * H]) : 0.f;
-    }
+// The chains.  One workgroup per (sequence, head, 16-column slice) and
+// direction; wave w owns rows 16 w .. of the chunk products and of the state.
+//   forward:  X_c out (entering state), D = U - W X, X' = e^{G_63} X + K~^T D
+//   reverse:  Y_c out (state gradient leaving the chunk, over P in place),
+//             dD = dD0 + K~ Y, Y' = e^{G_63} Y + P - W^T dD
+// 16 columns per workgroup keep the few chains of an fp32 call on four times
+// as many CUs as 64 would; the operands of the next chunk load during this one.
+struct StatesArgs {
+  const float *k, *Ww, *Gw;
+  const float *h0, *dht;
+  float *ht, *dh0;
+  float *Xw, *Dw, *Yw, *dRw;
+  float* urows;  // forward: U and D in the rows of o instead of Dw (or NULL)
+};
+template <bool REV>
+__device__ __forceinline__ void f32_chain(const StatesArgs& a, const SeqInfo& si, int s, int h, int H, int j0,
+                                          float (&XT)[16 * FLD], float (&DT)[16 * FLD]) {
+  const int w = wave_id(), lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
+  const int row4 = 16 * w + 4 * g4, c = j0 + r16;
+  const long soff = ((long)s * H + h) * FT;
+  const int n = si.nchunks;
+  const float* s0 = REV ? a.dht : a.h0;
+  floatx4 X;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) X[e] = s0 ? s0[soff + (row4 + e) * FD + c] : 0.f;
+  // operands of a chunk: W (forward: rows; reverse: columns), K (forward:
+  // columns; reverse: rows), gates of this lane's rows, U / dD0 and P rows.
+  // Chunk bases are scalar, lane offsets do not change from chunk to chunk;
+  // token rows past the chunk end fall past the buffer's records and read zero.
+  floatx4 wo[4], ko[4], uo = zero4(), po = zero4();
+  float4 gr;
+  float gl;
+  const unsigned ks = 4u * H * FD;                                 // bytes from token row to token row
+  const unsigned off = 4u * (row4 * FD + c);                       // this lane's rows of a 64 x 64 tile
+  const unsigned koff = REV ? (16 * w + r16) * ks + 16 * g4 : 4 * g4 * ks + 4 * (16 * w + r16);
+  const unsigned woff = REV ? 4u * wfrag(4 * g4, 16 * w + r16) : 16u * (4 * w * 64 + lane);
+  const unsigned uoff = row4 * ks + 4 * c;
+  auto c_len = [&](int cc) { return min(CH, si.len - cc * CH); };
+  auto c_tok = [&](int cc) { return (long)__builtin_amdgcn_readfirstlane(si.tok0 + cc * CH) * H + h; };
+  auto c_chh = [&](int cc) { return (long)__builtin_amdgcn_readfirstlane(si.chunk0 + cc) * H + h; };
+  auto rows = [&](const float* p, int cc) {  // the chunk's token rows of p
+    return clip_rsrc(const_cast<float*>(p) + c_tok(cc) * FD, (unsigned)(c_len(cc) - 1) * ks + 4u * FD);
   };
-  if (si.nchunks > 0) issue(si.nchunks - 1);
-
-  for (int cc = si.nchunks - 1; cc >= 0; --cc) {
-    const long chh = (long)(si.chunk0 + cc) * H + h;
-    __syncthreads();
-    pk.store(Ks, LDK);
-    pk.store_t(KsT, LDC);
-    pq.store_t(QsT, LDC);
-    pdo.store_t(dOT, LDC);
-    pa.store_t(AsT, LDF);
-    pm.store_t(MsT, LDF);
-    if (threadIdx.x < CH) {
-      Gs[threadIdx.x] = pg;
-      Bs[threadIdx.x] = pb;
-    }
+  auto load = [&](int cc) {
+    const long chh = c_chh(cc);
+    const float* wp = a.Ww + chh * FT;
+    const __amdgpu_buffer_rsrc_t rk = rows(a.k, cc);
 #pragma unroll
-    for (int mt = 0; mt < XMT; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < NTV; ++nt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int i = (DK / 4) * w + acc_row(mt, e), jj = acc_col(nt);
-          Yw[chh * DK * DV + (long)i * DV + j0 + jj] = Y[mt][nt][e];
-        }
-    __syncthreads();
-    if (cc > 0) issue(cc - 1);
-    const float Glast = Gs[CH - 1];
-
-    // dD = A^T dO + Diag(exp(G_63 - G)) K Y
-    floatx4 ky[1][NTV], ad[1][NTV];
-    zero_acc(ky);
-    zero_acc(ad);
-    mma<F32, 1, NTV, DK>(ky, Ks + 16 * w * LDK, LDK, YT, LDX);
-    mma<F32, 1, NTV, CH>(ad, AsT + 16 * w * LDF, LDF, dOT, LDC);
-#pragma unroll
-    for (int nt = 0; nt < NTV; ++nt)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = 16 * w + acc_row(0, e), jj = acc_col(nt);
-        dDT[jj * LDF + r] = ad[0][nt][e] + __expf(Glast - Gs[r]) * ky[0][nt][e];
-      }
-    __syncthreads();
-
-    // dR = M^T dD;  Pg = Diag(exp G) dO;  W2 = -d Pg - Diag(beta~ exp Gm) dR
-    floatx4 dr[1][NTV];
-    zero_acc(dr);
-    mma<F32, 1, NTV, CH>(dr, MsT + 16 * w * LDF, LDF, dDT, LDF);
-#pragma unroll
-    for (int nt = 0; nt < NTV; ++nt)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = 16 * w + acc_row(0, e), jj = acc_col(nt);
-        const float drv = dr[0][nt][e];
-        dRw[chh * CH * DV + (long)r * DV + j0 + jj] = drv;
-        const float pg = __expf(Gs[r]) * to_f(dOT[jj * LDC + r]);
-        const float gm = r > 0 ? Gs[r - 1] : 0.f;
-        PgT[jj * LDF + r] = pg;
-        W2T[jj * LDF + r] = -dh * pg - Bs[r] * __expf(gm) * drv;
-      }
-    __syncthreads();
-
-    // Y <- exp(G_63) Y + Q^T Pg + K^T W2
-    const float gC = __expf(Glast);
-#pragma unroll
-    for (int mt = 0; mt < XMT; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < NTV; ++nt) Y[mt][nt] *= gC;
-    mma<F32, XMT, NTV, CH>(Y, QsT + (DK / 4) * w * LDC, LDC, PgT, LDF);
-    mma<F32, XMT, NTV, CH>(Y, KsT + (DK / 4) * w * LDC, LDC, W2T, LDF);
-#pragma unroll
-    for (int mt = 0; mt < XMT; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < NTV; ++nt)
+    for (int kb = 0; kb < 4; ++kb) {
+      if constexpr (!REV) {
+        wo[kb] = at(reinterpret_cast<const floatx4*>(wp), woff + 1024u * kb);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          YT[acc_col(nt) * LDX + (DK / 4) * w + acc_row(mt, e)] = Y[mt][nt][e];
+          ko[kb][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rk, koff + (16 * kb + e) * ks, 0, 0));
+      } else {
+        // wfrag(16 kb + 4 g4 + e, 16 w + r16): row tile kb is 1024 floats on, row e 4
+#pragma unroll
+        for (int e = 0; e < 4; ++e) wo[kb][e] = at(wp, woff + 4096u * kb + 16u * e);
+        ko[kb] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rk, koff + 64u * kb, 0, 0));
+      }
+    }
+    gl = a.Gw[chh * CH + CH - 1];
+    gr = at(reinterpret_cast<const float4*>(a.Gw + chh * CH), 4u * row4);
+    if (!REV && a.urows) {
+      const __amdgpu_buffer_rsrc_t ru = rows(a.urows, cc);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) uo[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ru, uoff + e * ks, 0, 0));
+    } else {
+      const float* up = (REV ? a.dRw : a.Dw) + chh * FT;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) uo[e] = at(up, off + 4u * e * FD);
+    }
+    if constexpr (REV) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) po[e] = at(a.Yw + chh * FT, off + 4u * e * FD);
+    }
+  };
+  auto put = [&](float (&T)[16 * FLD], const floatx4& x) { store4(T + r16 * FLD + row4, x); };
+  auto get = [&](const float (&T)[16 * FLD], int kb) {
+    const float4 x = *reinterpret_cast<const float4*>(T + r16 * FLD + 16 * kb + 4 * g4);
+    return floatx4{x.x, x.y, x.z, x.w};
+  };
+  if (n > 0) load(REV ? n - 1 : 0);
+  put(XT, X);
+  __syncthreads();
+  for (int i = 0; i < n; ++i) {
+    const int cc = REV ? n - 1 - i : i;
+    const int len = c_len(cc);
+    const long chh = c_chh(cc);
+    floatx4 wc[4], kc[4];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      wc[kb] = wo[kb];
+      kc[kb] = ko[kb];
+    }
+    const floatx4 u = uo, p = po;
+    const float gC = __expf(gl);
+    float dec[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) dec[e] = __expf(gl - (e == 0 ? gr.x : e == 1 ? gr.y : e == 2 ? gr.z : gr.w));
+    load(i + 1 < n ? (REV ? cc - 1 : cc + 1) : cc);
+    // the product on the state: W X, resp. K Y (two accumulators: half the chain)
+    floatx4 t0 = zero4(), t1 = zero4();
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      const floatx4 x = get(XT, kb);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (e & 1) t1 = mfma4(REV ? kc[kb][e] : wc[kb][e], x[e], t1);
+        else t0 = mfma4(REV ? kc[kb][e] : wc[kb][e], x[e], t0);
+      }
+    }
+    const floatx4 t = t0 + t1;
+    floatx4 D, Dk;  // the stored D or dD, and the factor of the state update
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      // rows past the chunk end: zero
+      D[e] = row4 + e < len ? (REV ? u[e] + dec[e] * t[e] : u[e] - t[e]) : 0.f;
+      Dk[e] = REV ? -D[e] : dec[e] * D[e];
+    }
+    put(DT, Dk);
+    float* xp = (REV ? a.Yw : a.Xw) + chh * FT;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) at(xp, off + 4u * e * FD) = X[e];
+    if (!REV && a.urows) {
+      const __amdgpu_buffer_rsrc_t ru = rows(a.urows, cc);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) store_clip(D[e], ru, uoff + e * ks);
+    } else {
+      float* dp = (REV ? a.dRw : a.Dw) + chh * FT;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) at(dp, off + 4u * e * FD) = D[e];
+    }
+    __syncthreads();
+    X *= gC;
+    if constexpr (REV) X += p;
+    floatx4 y = zero4();
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      const floatx4 x = get(DT, kb);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (e & 1) y = mfma4(REV ? wc[kb][e] : kc[kb][e], x[e], y);
+        else X = mfma4(REV ? wc[kb][e] : kc[kb][e], x[e], X);
+      }
+    }
+    X += y;
+    put(XT, X);
+    __syncthreads();
   }
-  if (dh0) {
+  float* s1 = REV ? a.dh0 : a.ht;
+  if (s1)
 #pragma unroll
-    for (int mt = 0; mt < XMT; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < NTV; ++nt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int i = (DK / 4) * w + acc_row(mt, e), jj = acc_col(nt);
-          dh0[soff + (long)i * DV + j0 + jj] = Y[mt][nt][e];
-        }
-  }
+    for (int e = 0; e < 4; ++e) s1[soff + (row4 + e) * FD + c] = X[e];
+}
+// blockIdx.z: slice, then (BOTH) direction; REV alone runs the reverse chain.
+template <bool FWD, bool REV>
+__global__ __launch_bounds__(NTHR) void k_states(StatesArgs a, const SeqInfo* __restrict__ smap, int Tfix, int H) {
+  __shared__ __align__(16) float XT[16 * FLD], DT[16 * FLD];
+  const int s = blockIdx.x, h = blockIdx.y, j0 = 16 * (blockIdx.z & 3);
+  const SeqInfo si = seq_at(smap, s, Tfix);
+  if (FWD && (!REV || blockIdx.z < 4)) f32_chain<false>(a, si, s, h, H, j0, XT, DT);
+  else f32_chain<true>(a, si, s, h, H, j0, XT, DT);
 }
 
 // ---------------------------------------------------------------------------
@@ -625,7 +777,7 @@ template <typename Tin, int DK, int DV>
 __global__ __launch_bounds__(NTHR, 1) void k_intra_bwd(
     const Tin* __restrict__ q, const Tin* __restrict__ k, const Tin* __restrict__ v,
     const Tin* __restrict__ dO, const Tin* __restrict__ beta, const Tin* __restrict__ beta_tilde,
-    const float* __restrict__ d, const ChunkInfo* __restrict__ cmap, int H,
+    const float* __restrict__ d, const ChunkInfo* __restrict__ cmap, int Tfix, int H,
     const float* __restrict__ Gw, const float* __restrict__ Xw, const float* __restrict__ Dw,
     const float* __restrict__ Yw, const float* __restrict__ dRw, float* __restrict__ dq,
     float* __restrict__ dk, float* __restrict__ dv, float* __restrict__ dbeta,
@@ -644,7 +796,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_intra_bwd(
 
   const int h = blockIdx.y;
   const long chh = (long)blockIdx.x * H + h;
-  const ChunkInfo ci = cmap[blockIdx.x];
+  const ChunkInfo ci = chunk_at(cmap, blockIdx.x, Tfix);
   if (ci.len <= 0) {
     if (threadIdx.x == 0) ddp[chh] = 0.f;
     return;
@@ -944,24 +1096,6 @@ __device__ __forceinline__ floatx4 mfma16(const bf16x8& a, const bf16x8& b, cons
 __device__ __forceinline__ bf16x8 ld8(const bf16_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
 __device__ __forceinline__ bf16x8 zero8() { return __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u}); }
 
-// Chunk and sequence tables of the bf16 kernels: for fixed-length rows
-// (Tfix >= 0 tokens each) in closed form, for packed sequences (Tfix < 0) from
-// the tables of k_seq_map and k_chunk_fill.
-__device__ __forceinline__ ChunkInfo chunk_at(const ChunkInfo* cmap, int c, int Tfix) {
-  if (Tfix >= 0) {
-    const int ncs = max(1, (Tfix + CH - 1) / CH), s = c / ncs, i = c - s * ncs;
-    return ChunkInfo{s * Tfix + i * CH, min(CH, Tfix - i * CH), s, 0};
-  }
-  return cmap[c];
-}
-__device__ __forceinline__ SeqInfo seq_at(const SeqInfo* smap, int s, int Tfix) {
-  if (Tfix >= 0) {
-    const int ncs = (Tfix + CH - 1) / CH;
-    return SeqInfo{s * ncs, ncs, s * Tfix, Tfix};
-  }
-  return smap[s];
-}
-
 // Element (row, col) of a 64-column operand tile that prep stores in MFMA
 // fragment order (M, A, Q^T): the 16 bytes lane (g, i) of wave w
 // loads for k-step ks (row 16 w + i, columns 32 ks + 8 g .. +7) sit at
@@ -1010,46 +1144,6 @@ __device__ __forceinline__ void put_t4(bf16_t* hi, bf16_t* lo, int off, const fl
   split4(x, h, l);
   *reinterpret_cast<bf16x4*>(hi + off) = h;
   *reinterpret_cast<bf16x4*>(lo + off) = l;
-}
-
-// Block column J of M = (I + L)^{-1} below the diagonal, in the accumulator
-// layout of the 16x16 fp32 MFMA: on entry mb[J] = D_J; on exit mb[i] = M_iJ for
-// i > J.  The L_ik and D_i blocks come from LDS (row-major, stride LDL, D_i in
-// the diagonal blocks).  Each product runs its k index in the order
-// 4 (lane / 16) + e at step e, so that an accumulator is directly the B operand
-// of the next product and the A operand of a step is one 16-byte LDS read.
-template <int J, int LDL>
-__device__ __forceinline__ void solve_block_column(const float* Ls, floatx4 (&mb)[4]) {
-  const int lane = lane_id(), r16 = lane & 15, g4 = lane >> 4;
-#pragma unroll
-  for (int i = J + 1; i < 4; ++i) {
-    floatx4 t = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kb = J; kb < i; ++kb) {
-      const float4 a = *reinterpret_cast<const float4*>(Ls + (16 * i + r16) * LDL + 16 * kb + 4 * g4);
-      t = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, mb[kb][0], t, 0, 0, 0);
-      t = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, mb[kb][1], t, 0, 0, 0);
-      t = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, mb[kb][2], t, 0, 0, 0);
-      t = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, mb[kb][3], t, 0, 0, 0);
-    }
-    const float4 dd = *reinterpret_cast<const float4*>(Ls + (16 * i + r16) * LDL + 16 * i + 4 * g4);
-    floatx4 u = {0.f, 0.f, 0.f, 0.f};
-    u = __builtin_amdgcn_mfma_f32_16x16x4f32(dd.x, t[0], u, 0, 0, 0);
-    u = __builtin_amdgcn_mfma_f32_16x16x4f32(dd.y, t[1], u, 0, 0, 0);
-    u = __builtin_amdgcn_mfma_f32_16x16x4f32(dd.z, t[2], u, 0, 0, 0);
-    u = __builtin_amdgcn_mfma_f32_16x16x4f32(dd.w, t[3], u, 0, 0, 0);
-    mb[i] = -u;
-  }
-}
-
-// Block column J of M (mb as left by solve_block_column) into LDS over L.
-template <int J, int LDL>
-__device__ __forceinline__ void put_block_column(float* Ls, const floatx4 (&mb)[4]) {
-  const int lane = lane_id(), r16 = lane & 15, g4 = lane >> 4;
-#pragma unroll
-  for (int i = J + 1; i < 4; ++i)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) Ls[(16 * i + 4 * g4 + e) * LDL + 16 * J + r16] = mb[i][e];
 }
 
 template <int DK, bool BWD>
@@ -1168,36 +1262,7 @@ __global__ __launch_bounds__(NTHR) void k_prep_bf(
   // SIMDs of workgroups that share a CU.
   const int jb = (w + blockIdx.x + blockIdx.y) & (NWAVE - 1);
   floatx4 mb[4];
-  {
-    // lane (g4, r16) solves column r16 of the diagonal block by forward
-    // substitution in fp32 (the four 16-lane groups redundantly)
-    float* Lb = Ls + 16 * jb * LDL + 16 * jb;
-    float x[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) x[i] = (i == r16) ? 1.f : 0.f;
-#pragma unroll
-    for (int i = 1; i < 16; ++i) {
-      float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-#pragma unroll
-      for (int m = 0; m < i; m += 4) {
-        const float4 lv = *reinterpret_cast<const float4*>(Lb + i * LDL + m);
-        s0 += lv.x * x[m];
-        if (m + 1 < i) s1 += lv.y * x[m + 1];
-        if (m + 2 < i) s2 += lv.z * x[m + 2];
-        if (m + 3 < i) s3 += lv.w * x[m + 3];
-      }
-      if (i > r16) x[i] = -((s0 + s1) + (s2 + s3));
-    }
-    // D_jb in the accumulator layout (rows 4 g4 + e of column r16) replaces
-    // L_jb,jb in LDS; only this wave reads that block, and its reads are done
-    floatx4 dm;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      dm[e] = g4 == 0 ? x[e] : g4 == 1 ? x[4 + e] : g4 == 2 ? x[8 + e] : x[12 + e];
-      Lb[(4 * g4 + e) * LDL + r16] = dm[e];
-    }
-    mb[0] = mb[1] = mb[2] = mb[3] = dm;
-  }
+  invert_diagonal<LDL>(Ls, jb, mb);
   __syncthreads();
   switch (jb) {
     case 0: solve_block_column<0, LDL>(Ls, mb); break;
@@ -3191,67 +3256,63 @@ static void launch_chunk_map(const LaunchArgs& a, hipStream_t st) {
   }
 }
 
-template <typename Tin, int DK, int DV>
-static hipError_t run_fwd(const LaunchArgs& a) {
-  hipStream_t st = a.stream;
-  const Tin* q = static_cast<const Tin*>(a.q);
-  const Tin* k = static_cast<const Tin*>(a.k);
-  const Tin* v = static_cast<const Tin*>(a.v);
-  const Tin* beta = static_cast<const Tin*>(a.beta);
-  const Tin* bt = static_cast<const Tin*>(a.beta_tilde);
-  a.stage("chunk_map");
-  launch_chunk_map(a, st);
+// fp32 inputs.  The forward keeps its workspace at two 64 x 64 tiles per
+// chunk-head: without the backward's state, X takes the slot of M, and U, D the
+// rows of o.  Fixed-length rows need no tables (closed form in the kernels).
+static void f32_prep(const LaunchArgs& a, int Tfix, float* M, float* U, bool u_rows) {
+  if (Tfix < 0) {
+    a.stage("chunk_map");
+    launch_chunk_map(a, a.stream);
+  }
   a.stage("prep");
   if (a.ncmax > 0)
-    k_prep<Tin, DK><<<dim3(a.ncmax, a.H), NTHR, 0, st>>>(q, k, a.g, bt, a.d, a.cmap, a.H, a.Mw,
-                                                         a.Aw, a.Gw);
+    k_prep<<<dim3(a.ncmax, a.H), NTHR, 0, a.stream>>>(
+        static_cast<const float*>(a.k), static_cast<const float*>(a.v), a.g, static_cast<const float*>(a.beta),
+        static_cast<const float*>(a.beta_tilde), a.cmap, Tfix, a.H, M, a.Aw, a.Gw, U, u_rows);
+}
+static hipError_t run_fwd_f32(const LaunchArgs& a) {
+  const float *q = static_cast<const float*>(a.q), *k = static_cast<const float*>(a.k);
+  const int Tfix = a.cu_seqlens ? -1 : a.Tseq;
+  float* X = a.saved ? a.Xw : a.Mw;
+  f32_prep(a, Tfix, a.saved ? a.Mw : nullptr, a.saved ? a.Dw : a.o, !a.saved);
   a.stage("scan_fwd");
-  if (a.saved)
-    k_scan_fwd<Tin, DK, DV, true, true><<<dim3(a.N, a.H, DV / 32), NTHR, 0, st>>>(
-        q, k, v, beta, bt, a.d, a.h0, a.cmap, a.smap, a.H, a.Mw, a.Aw, a.Gw, a.o, a.ht, a.Xw, a.Dw);
-  else
-    k_scan_fwd<Tin, DK, DV, true, false><<<dim3(a.N, a.H, DV / 32), NTHR, 0, st>>>(
-        q, k, v, beta, bt, a.d, a.h0, a.cmap, a.smap, a.H, a.Mw, a.Aw, a.Gw, a.o, a.ht, nullptr,
-        nullptr);
+  const StatesArgs sa{k, a.Aw, a.Gw, a.h0, nullptr, a.ht, nullptr, X, a.Dw, nullptr, nullptr, a.saved ? nullptr : a.o};
+  k_states<true, false><<<dim3(a.N, a.H, 4), NTHR, 0, a.stream>>>(sa, a.smap, Tfix, a.H);
+  a.stage("out");
+  if (a.ncmax > 0)
+    k_out<<<dim3(a.ncmax, a.H), NTHR, 0, a.stream>>>(q, k, a.d, a.cmap, Tfix, a.H, a.Gw, X, a.Dw, a.o, !a.saved);
   a.stage(nullptr);
   return hipGetLastError();
 }
 
-template <typename Tin, int DK, int DV>
-static hipError_t run_bwd(const LaunchArgs& a) {
+static hipError_t run_bwd_f32(const LaunchArgs& a) {
   hipStream_t st = a.stream;
-  const Tin* q = static_cast<const Tin*>(a.q);
-  const Tin* k = static_cast<const Tin*>(a.k);
-  const Tin* v = static_cast<const Tin*>(a.v);
-  const Tin* beta = static_cast<const Tin*>(a.beta);
-  const Tin* bt = static_cast<const Tin*>(a.beta_tilde);
-  const Tin* dO = static_cast<const Tin*>(a.dO);
   if (a.N == 0) {
     // no sequences: dd (one value per head) is zero
     k_reduce_dd<<<a.H, RDD_THR, 0, st>>>(a.ddp, 0, a.H, a.dd);
     return hipGetLastError();
   }
-  if (!a.saved) {
-    a.stage("chunk_map");
-    launch_chunk_map(a, st);
-    a.stage("prep");
-    if (a.ncmax > 0)
-      k_prep<Tin, DK><<<dim3(a.ncmax, a.H), NTHR, 0, st>>>(q, k, a.g, bt, a.d, a.cmap, a.H,
-                                                           a.Mw, a.Aw, a.Gw);
-    a.stage("scan_fwd_store");
-    k_scan_fwd<Tin, DK, DV, false, true><<<dim3(a.N, a.H, DV / 32), NTHR, 0, st>>>(
-        q, k, v, beta, bt, a.d, a.h0, a.cmap, a.smap, a.H, a.Mw, a.Aw, a.Gw, nullptr, nullptr, a.Xw,
-        a.Dw);
-  }
-  a.stage("scan_bwd");
-  k_scan_bwd<Tin, DK, DV><<<dim3(a.N, a.H, DV / 32), NTHR, 0, st>>>(
-      q, k, dO, bt, a.d, a.dht, a.cmap, a.smap, a.H, a.Mw, a.Aw, a.Gw, a.dh0, a.Yw, a.dRw);
-  a.stage("intra_bwd");
+  const float *q = static_cast<const float*>(a.q), *k = static_cast<const float*>(a.k);
+  const float *v = static_cast<const float*>(a.v), *dO = static_cast<const float*>(a.dO);
+  const int Tfix = a.cu_seqlens ? -1 : a.Tseq;
+  if (!a.saved) f32_prep(a, Tfix, a.Mw, a.Dw, false);
+  a.stage("prep_bwd");
   if (a.ncmax > 0)
-    k_intra_bwd<Tin, DK, DV><<<dim3(a.ncmax, a.H), NTHR, 0, st>>>(
-        q, k, v, dO, beta, bt, a.d, a.cmap, a.H, a.Gw, a.Xw, a.Dw, a.Yw, a.dRw,
-        static_cast<float*>(a.dq), static_cast<float*>(a.dk_), static_cast<float*>(a.dv_),
-        static_cast<float*>(a.dbeta), static_cast<float*>(a.dbeta_tilde), a.dg, a.ddp);
+    k_bprep<<<dim3(a.ncmax, a.H), NTHR, 0, st>>>(q, k, dO, a.d, a.cmap, Tfix, a.H, a.Gw, a.dRw, a.Yw);
+  // the recomputed chunk states and the reverse chain do not depend on each
+  // other: one grid
+  const StatesArgs sa{k, a.Aw, a.Gw, a.h0, a.dht, nullptr, a.dh0, a.Xw, a.Dw, a.Yw, a.dRw, nullptr};
+  a.stage("scan_bwd");
+  if (a.saved) k_states<false, true><<<dim3(a.N, a.H, 4), NTHR, 0, st>>>(sa, a.smap, Tfix, a.H);
+  else k_states<true, true><<<dim3(a.N, a.H, 8), NTHR, 0, st>>>(sa, a.smap, Tfix, a.H);
+  a.stage("intra_bwd");
+  if (a.ncmax > 0) {
+    k_dr<<<dim3(a.ncmax, a.H), NTHR, 0, st>>>(a.cmap, Tfix, a.H, a.Mw, a.dRw);
+    k_intra_bwd<float, FD, FD><<<dim3(a.ncmax, a.H), NTHR, 0, st>>>(
+        q, k, v, dO, static_cast<const float*>(a.beta), static_cast<const float*>(a.beta_tilde), a.d, a.cmap, Tfix,
+        a.H, a.Gw, a.Xw, a.Dw, a.Yw, a.dRw, static_cast<float*>(a.dq), static_cast<float*>(a.dk_),
+        static_cast<float*>(a.dv_), static_cast<float*>(a.dbeta), static_cast<float*>(a.dbeta_tilde), a.dg, a.ddp);
+  }
   a.stage("reduce_dd");
   k_reduce_dd<<<a.H, RDD_THR, 0, st>>>(a.ddp, a.ncmax, a.H, a.dd);
   a.stage(nullptr);
@@ -3495,18 +3556,12 @@ static hipError_t dispatch_bf(const LaunchArgs& a) {
   return hipErrorInvalidValue;
 }
 
-template <bool BWD, typename Tin>
-static hipError_t dispatch_dims(const LaunchArgs& a) {
-  if (a.dk == 64 && a.dv == 64) return BWD ? run_bwd<Tin, 64, 64>(a) : run_fwd<Tin, 64, 64>(a);
-  return hipErrorInvalidValue;
-}
-
 hipError_t launch_fwd(const LaunchArgs& a) {
-  return a.bf16 ? dispatch_bf<false>(a) : dispatch_dims<false, float>(a);
+  return a.bf16 ? dispatch_bf<false>(a) : run_fwd_f32(a);  // fp32: dk = dv = 64 (check_shape)
 }
 
 hipError_t launch_bwd(const LaunchArgs& a) {
-  return a.bf16 ? dispatch_bf<true>(a) : dispatch_dims<true, float>(a);
+  return a.bf16 ? dispatch_bf<true>(a) : run_bwd_f32(a);
 }
 
 }  // namespace comba

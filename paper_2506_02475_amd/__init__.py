@@ -64,6 +64,8 @@ def library_path() -> str:
 def load_library():
     """Load libcomba.so (built by ``paper_2506_02475_amd.build``); raises if absent."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(_LIB_PATH):
@@ -149,8 +151,21 @@ def _check(status: int):
         raise CombaError("comba: %s (status %d)" % (msg, status))
 
 
+# The calls below marshal arguments as plain ints (the argtypes convert them)
+# and read the current stream's handle directly: at one decoding step per call
+# the binding, not the kernel, bounds the rate (13.4 us a call with ctypes
+# objects and torch.cuda.current_stream, of which the library call is 4.8).
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _stream(stream, device):
+    """The stream handle of a call: the given one, or torch's current stream of the device."""
+    if stream is not None:
+        return stream
+    import torch
+
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _make_shape(B, T, H, dk, dv, N, cu_ptr, dtype_code, chunk=CHUNK, cu_host=None):
@@ -201,39 +216,43 @@ def _prepare(q, k, v, g, beta, d, h0, cu_seqlens, extra=(), cu_seqlens_host=None
 
     if not q.is_cuda:
         raise CombaError("comba: tensors must be on a GPU device")
-    if q.dtype == torch.bfloat16:
+    dt, f32 = q.dtype, torch.float32
+    if dt is torch.bfloat16:
         code = COMBA_BF16
-    elif q.dtype == torch.float32:
+    elif dt is f32:
         code = COMBA_F32
     else:
         raise CombaError("comba: q must be bfloat16 or float32")
-    for name, t in (("k", k), ("v", v), ("beta", beta)) + tuple(extra):
-        if t.dtype != q.dtype:
+    for name, t in (("k", k), ("v", v), ("beta", beta)) + extra:
+        if t.dtype is not dt:
             raise CombaError("comba: %s must have the dtype of q" % name)
-    for name, t in (("g", g), ("d", d)):
-        if t.dtype != torch.float32:
-            raise CombaError("comba: %s must be float32" % name)
-    tensors = [q, k, v, g, beta, d] + [t for _, t in extra]
-    if h0 is not None:
-        tensors.append(h0)
-    for t in tensors:
-        if not t.is_contiguous() or t.device != q.device:
+    if g.dtype is not f32:
+        raise CombaError("comba: g must be float32")
+    if d.dtype is not f32:
+        raise CombaError("comba: d must be float32")
+    dev = q.get_device()
+    for t in (q, k, v, g, beta, d, h0):
+        if t is not None and (not t.is_contiguous() or t.get_device() != dev):
             raise CombaError("comba: all tensors must be contiguous and on one device")
-    B, T, H, dk = q.shape
+    for _, t in extra:
+        if not t.is_contiguous() or t.get_device() != dev:
+            raise CombaError("comba: all tensors must be contiguous and on one device")
+    shape = q.shape
+    B, T, H, dk = shape
     dv = v.shape[-1]
-    if k.shape != q.shape or v.shape[:3] != (B, T, H) or g.shape != (B, T, H) \
+    if k.shape != shape or v.shape[:3] != (B, T, H) or g.shape != (B, T, H) \
             or beta.shape != (B, T, H) or d.shape != (H,):
         raise CombaError("comba: inconsistent shapes")
     if cu_seqlens is not None:
-        if cu_seqlens.dtype != torch.int32 or not cu_seqlens.is_contiguous() \
-                or cu_seqlens.device != q.device or B != 1:
+        if cu_seqlens.dtype is not torch.int32 or not cu_seqlens.is_contiguous() \
+                or cu_seqlens.get_device() != dev or B != 1:
             raise CombaError("comba: cu_seqlens must be contiguous int32 on the device, B == 1")
         N = cu_seqlens.numel() - 1
     else:
         if cu_seqlens_host is not None:
             raise CombaError("comba: cu_seqlens_host needs cu_seqlens")
         N = B
-    if h0 is not None and (h0.dtype != torch.float32 or tuple(h0.shape) != (N, H, dk, dv)):
+    if h0 is not None and (h0.dtype is not f32 or h0.shape != (N, H, dk, dv)):
         raise CombaError("comba: h0 must be float32 [N,H,dk,dv]")
     shp = _make_shape(B, T, H, dk, dv, N, _ptr(cu_seqlens), code,
                       cu_host=_host_offsets(cu_seqlens_host, N + 1))
@@ -243,7 +262,7 @@ def _prepare(q, k, v, g, beta, d, h0, cu_seqlens, extra=(), cu_seqlens_host=None
 def _beta_tilde(beta_tilde, beta):
     if beta_tilde is None:
         return ()
-    if tuple(beta_tilde.shape) != tuple(beta.shape):
+    if beta_tilde.shape != beta.shape:
         raise CombaError("comba: beta_tilde must have the shape of beta [B,T,H]")
     return (("beta_tilde", beta_tilde),)
 
@@ -265,11 +284,11 @@ def _fwd(save, q, k, v, g, beta, d, h0, cu_seqlens, output_final_state, workspac
         _check(2)
     if workspace is None or workspace.numel() < nbytes:
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=q.device)
-    st = torch.cuda.current_stream(q.device).cuda_stream if stream is None else stream
+    st = _stream(stream, q.device)
     fn = lib.comba_chunk_fwd_save if save else lib.comba_chunk_fwd
     _check(fn(ctypes.byref(shp), _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(beta),
               _ptr(beta_tilde), _ptr(d), _ptr(h0), _ptr(o), _ptr(ht), _ptr(workspace),
-              ctypes.c_size_t(workspace.numel()), ctypes.c_void_p(st)))
+              workspace.numel(), st))
     return o, ht, workspace
 
 
@@ -323,10 +342,10 @@ def comba_chunk_fwd_noalloc(q, k, v, g, beta, d, h0=None, *, beta_tilde=None, cu
         o = torch.empty((B, T, H, dv), dtype=torch.float32, device=q.device)
     if ht is None and output_final_state:
         ht = torch.empty((N, H, dk, dv), dtype=torch.float32, device=q.device)
-    st = torch.cuda.current_stream(q.device).cuda_stream if stream is None else stream
+    st = _stream(stream, q.device)
     _check(lib.comba_chunk_fwd_noalloc(ctypes.byref(shp), _ptr(q), _ptr(k), _ptr(v), _ptr(g),
                                        _ptr(beta), _ptr(beta_tilde), _ptr(d), _ptr(h0), _ptr(o),
-                                       _ptr(ht), ctypes.c_void_p(st)))
+                                       _ptr(ht), st))
     return o, ht
 
 
@@ -350,10 +369,10 @@ def comba_recurrent_fwd(q, k, v, g, beta, d, h0=None, *, beta_tilde=None, cu_seq
             raise CombaError("comba: ht must be contiguous float32 [N,H,dk,dv] on the device")
     elif output_final_state:
         ht = torch.empty((N, H, dk, dv), dtype=torch.float32, device=q.device)
-    st = torch.cuda.current_stream(q.device).cuda_stream if stream is None else stream
+    st = _stream(stream, q.device)
     _check(lib.comba_recurrent_fwd(ctypes.byref(shp), _ptr(q), _ptr(k), _ptr(v), _ptr(g),
                                    _ptr(beta), _ptr(beta_tilde), _ptr(d), _ptr(h0), _ptr(o),
-                                   _ptr(ht), ctypes.c_void_p(st)))
+                                   _ptr(ht), st))
     return o, ht
 
 
@@ -399,10 +418,10 @@ def comba_prologue_fwd(xq, xk, xv, wq, wk, wv, *, cu_seqlens=None, cu_seqlens_ho
     lib = load_library()
     shp = _prologue_shape(xq, xk, xv, wq, wk, wv, cu_seqlens, cu_seqlens_host=cu_seqlens_host)
     q, k, v = torch.empty_like(xq), torch.empty_like(xk), torch.empty_like(xv)
-    st = torch.cuda.current_stream(xq.device).cuda_stream if stream is None else stream
+    st = _stream(stream, xq.device)
     _check(lib.comba_prologue_fwd(ctypes.byref(shp), _ptr(xq), _ptr(xk), _ptr(xv), _ptr(wq),
                                   _ptr(wk), _ptr(wv), _ptr(q), _ptr(k), _ptr(v),
-                                  ctypes.c_void_p(st)))
+                                  st))
     return q, k, v
 
 
@@ -427,13 +446,13 @@ def comba_prologue_bwd(xq, xk, xv, wq, wk, wv, gq, gk, gv, *, cu_seqlens=None,
         _check(2)
     if workspace is None or workspace.numel() < nbytes:
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=xq.device)
-    st = torch.cuda.current_stream(xq.device).cuda_stream if stream is None else stream
+    st = _stream(stream, xq.device)
     _check(lib.comba_prologue_bwd(ctypes.byref(shp), _ptr(xq), _ptr(xk), _ptr(xv), _ptr(wq),
                                   _ptr(wk), _ptr(wv), _ptr(gq), _ptr(gk), _ptr(gv),
                                   _ptr(out["dxq"]), _ptr(out["dxk"]), _ptr(out["dxv"]),
                                   _ptr(out["dwq"]), _ptr(out["dwk"]), _ptr(out["dwv"]),
-                                  _ptr(workspace), ctypes.c_size_t(workspace.numel()),
-                                  ctypes.c_void_p(st)))
+                                  _ptr(workspace), workspace.numel(),
+                                  st))
     return out
 
 
@@ -455,9 +474,9 @@ def comba_gate_fwd(o, z, *, stream=None):
 
     shp = _gate_shape(o, z)
     y = torch.empty_like(z)
-    st = torch.cuda.current_stream(o.device).cuda_stream if stream is None else stream
+    st = _stream(stream, o.device)
     _check(load_library().comba_gate_fwd(ctypes.byref(shp), _ptr(o), _ptr(z), _ptr(y),
-                                         ctypes.c_void_p(st)))
+                                         st))
     return y
 
 
@@ -469,9 +488,9 @@ def comba_gate_bwd(o, z, dy, *, stream=None):
     if dy.shape != o.shape or dy.dtype != torch.float32 or not dy.is_contiguous():
         raise CombaError("comba: dy must be contiguous float32 of the shape of o")
     do, dz = torch.empty_like(o), torch.empty(o.shape, dtype=torch.float32, device=o.device)
-    st = torch.cuda.current_stream(o.device).cuda_stream if stream is None else stream
+    st = _stream(stream, o.device)
     _check(load_library().comba_gate_bwd(ctypes.byref(shp), _ptr(o), _ptr(z), _ptr(dy), _ptr(do),
-                                         _ptr(dz), ctypes.c_void_p(st)))
+                                         _ptr(dz), st))
     return do, dz
 
 
@@ -510,14 +529,14 @@ def _bwd(saved, q, k, v, g, beta, d, h0, dO, dht, cu_seqlens, need_dh0, workspac
             raise CombaError("comba: comba_chunk_bwd_saved needs the workspace filled by "
                              "comba_chunk_fwd_save")
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
-    st = torch.cuda.current_stream(dev).cuda_stream if stream is None else stream
+    st = _stream(stream, dev)
     fn = lib.comba_chunk_bwd_saved_in_dtype if in_dtype else \
         lib.comba_chunk_bwd_saved if saved else lib.comba_chunk_bwd
     _check(fn(ctypes.byref(shp), _ptr(q), _ptr(k), _ptr(v), _ptr(g), _ptr(beta),
               _ptr(beta_tilde), _ptr(d), _ptr(h0), _ptr(dO), _ptr(dht), _ptr(out["dq"]),
               _ptr(out["dk"]), _ptr(out["dv"]), _ptr(out["dg"]), _ptr(out["dbeta"]),
               _ptr(out["dbeta_tilde"]), _ptr(out["dd"]), _ptr(out["dh0"]), _ptr(workspace),
-              ctypes.c_size_t(workspace.numel()), ctypes.c_void_p(st)))
+              workspace.numel(), st))
     if beta_tilde is None:
         del out["dbeta_tilde"]
     return out

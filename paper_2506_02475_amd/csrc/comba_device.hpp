@@ -405,6 +405,37 @@ __device__ __forceinline__ bf16x8 ld_tr8(const bf16_t* tile, int ld, int r0, int
   return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// ---- unpadded LDS tiles ---------------------------------------------------
+// Element offsets that keep a tile's rows at a power-of-two stride and spread
+// them over the banks by exchanging pieces inside a row, where padding would
+// cost the LDS that a second workgroup on the CU needs.
+// sw32: [row][32] bf16, 8-byte pieces (piece ^ bit-reversed (row / 2) % 8): 16
+// rows of one piece (accumulator writes) and four rows of four pieces
+// (transposing reads) each fall on distinct banks.
+__device__ __forceinline__ int sw32(int row, int col) {
+  const int t = (row >> 1) & 7, x = ((t & 1) << 2) | (t & 2) | (t >> 2);
+  return row * 32 + ((((col >> 2) ^ x) << 2) | (col & 3));
+}
+// sw16: [row][LD] with LD a multiple of 64, 16-byte pieces: 8 rows of one piece
+// and four rows of two pieces fall on distinct banks.
+template <int LD>
+__device__ __forceinline__ int sw16(int row, int col) {
+  const int x = ((row & 3) << 1) | ((row >> 2) & 1);
+  return row * LD + ((((col >> 3) ^ x) << 3) | (col & 7));
+}
+// ld_tr8 of such tiles: the lane's own element offsets at rows r0 .. r0 + 3 and
+// r0 + 4 .. r0 + 7 (row r0 + lane % 16 / 4, columns c0 + 4 (lane % 4)), which
+// stay the same under row steps of 32.
+struct TrOff {
+  int a, b;
+};
+__device__ __forceinline__ bf16x8 ld_tr8(const bf16_t* tile, const TrOff& o) {
+  const i16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(tile + o.a));
+  const i16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(tile + o.b));
+  return __builtin_shufflevector(__builtin_bit_cast(bf16x4_t, a), __builtin_bit_cast(bf16x4_t, b), 0, 1, 2, 3, 4, 5,
+                                 6, 7);
+}
+
 // ---- cross-lane reductions and scans (DPP: VALU only, no LDS round trip) ----
 // DPP controls used (gfx9 encodings; a "row" is 16 lanes): quad_perm xor 1 /
 // xor 2, row_half_mirror (lane i of an 8-lane half reads lane 7 - i), row_mirror

@@ -1780,6 +1780,27 @@ __global__ __launch_bounds__(seg_combine_threads<DK>()) void k_seg_combine(
   }
 }
 
+// LDS tiles of a scan: 32-column tiles (t), the chunk's K rows (k) and 64 x 64
+// M / A tiles (m), unpadded with exchanged pieces (sw32, sw16) or with padded
+// rows (72, 2 dk + 48 and 144 bytes: the four rows of a transposing read on
+// disjoint banks).
+template <bool SW, int DK>
+struct ScanTiles {
+  static constexpr int LDT = SW ? 32 : 36, LDK = SW ? DK : DK + 24, LDM = SW ? CH : CH + 8;
+  static __device__ __forceinline__ int t(int r, int c) { return SW ? sw32(r, c) : r * LDT + c; }
+  static __device__ __forceinline__ int k(int r, int c) { return SW ? sw16<DK>(r, c) : r * LDK + c; }
+  static __device__ __forceinline__ int m(int r, int c) { return SW ? sw16<CH>(r, c) : r * LDM + c; }
+  // ld_tr8 offsets at rows r0 .., columns c0 .. (see TrOff)
+  static __device__ __forceinline__ TrOff tr_t(int r0, int c0) { return tr(t, r0, c0); }
+  static __device__ __forceinline__ TrOff tr_k(int r0, int c0) { return tr(k, r0, c0); }
+  static __device__ __forceinline__ TrOff tr_m(int r0, int c0) { return tr(m, r0, c0); }
+  template <typename F>
+  static __device__ __forceinline__ TrOff tr(F f, int r0, int c0) {
+    const int r = r0 + ((lane_id() & 15) >> 2), c = c0 + 4 * (lane_id() & 3);
+    return {f(r, c), f(r + 4, c)};
+  }
+};
+
 // Reverse state scan (bf16 inputs): Y = gradient of the state leaving the chunk.
 // As in the forward scan, every product is formed transposed, so that a lane
 // holds one row and four consecutive columns; the intermediate tiles (Y, dO,
@@ -1788,7 +1809,7 @@ __global__ __launch_bounds__(seg_combine_threads<DK>()) void k_seg_combine(
 // STORE = false: the recurrence alone (no Y, dR stores), for the segmented
 // backward's state pass.
 template <int DK, int DV, int BV, bool STORE = true>
-__global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
+__global__ __launch_bounds__(NTHR, DK <= 128 ? 2 : 1) void k_scan_bwd_bf(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ dO,
     const bf16_t* __restrict__ beta_tilde, const float* __restrict__ d, const float* __restrict__ dht,
     const SeqInfo* __restrict__ smap, const int* __restrict__ sorder, int N, int Tfix, int H,
@@ -1801,11 +1822,17 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
   // as in the forward scan, all loop memory operations are unconditional
   constexpr int NTV = BV / 16, XMT = DK / 64, KS = DK / 32, CC = CH * CH;
   constexpr int NB = DV / 32;
-  constexpr int LDT = BV + 4;  // row-major BV-wide tiles (see the forward scan)
+  // dk <= 128: unpadded tiles (78,848 bytes), so that two workgroups fit a CU
+  // where there are more chains than CUs (65,536 tokens, H16 d128, 512 chains:
+  // 721 -> 586 us, state pass 742 -> 544 us; at one workgroup per CU the same
+  // within 1%).  dk = 256 has room for one either way and keeps the padded
+  // rows, whose addresses need fewer registers (1.6% of the training pair).
+  using L = ScanTiles<(DK <= 128), DK>;
+  constexpr int LDT = L::LDT, LDK = L::LDK, LDM = L::LDM;
   static_assert(BV == 32, "stored states use one scale per 32-column block = one dv slice");
   __shared__ __align__(16) bf16_t Yh[DK * LDT];
   __shared__ __align__(16) bf16_t Yl[DK * LDT];
-  __shared__ __align__(16) bf16_t dOs[2][CH * LDT];
+  __shared__ __align__(16) bf16_t dOs[CH * LDT];
   __shared__ __align__(16) bf16_t dDh[CH * LDT];
   __shared__ __align__(16) bf16_t dDl[CH * LDT];
   __shared__ __align__(16) bf16_t Pgh[CH * LDT];
@@ -1824,6 +1851,11 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
   const int prow = 16 * w + r16;            // chunk row of this lane
   const int yrow0 = (DK / 4) * w + r16;     // state rows of this lane: yrow0 + 16 mt
   const int col0 = 4 * g4;                  // columns of this lane: 16 nt + col0 .. +3
+  // this lane's offsets: its row prow, columns 16 nt + col0 .. of a BV-wide
+  // tile; transposing reads at rows 8 g4 .. (+ 32 ks), columns 16 nt ..
+  const int poff[2] = {L::t(prow, col0), L::t(prow, 16 + col0)};
+  const TrOff toff[2] = {L::tr_t(8 * g4, 0), L::tr_t(8 * g4, 16)};
+  static_assert(NTV == 2, "two column tiles");
 
   floatx4 Y[XMT][NTV];
 #pragma unroll
@@ -1843,7 +1875,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
 #pragma unroll
       for (int nt = 0; nt < NTV; ++nt) {
         const float yv[4] = {Y[mt][nt][0], Y[mt][nt][1], Y[mt][nt][2], Y[mt][nt][3]};
-        put_t4(Yh, Yl, (yrow0 + 16 * mt) * LDT + 16 * nt + col0, yv);
+        put_t4(Yh, Yl, L::t(yrow0 + 16 * mt, 16 * nt + col0), yv);
       }
   };
   auto store_state = [&](float* dst) {
@@ -1882,8 +1914,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
   // transposing reads.  Q^T comes from prep in fragment order (staging Q rows
   // like K cost this scan more than the copy saves).
   bf16x8 kf[KS], qtf[XMT][2];
-  constexpr int LDKC = DK + 24;  // 304-byte rows: conflict-free transposing reads
-  __shared__ __align__(16) bf16_t Kc[CH * LDKC];
+  __shared__ __align__(16) bf16_t Kc[CH * LDK];
   // M and A of the chunk as int16, row-major: each lane stores the 16 bytes it
   // loads in fragment order (8 consecutive columns of one row), and transposing
   // reads return the B operands of M^T dD and A^T dO.  M's row scale is folded
@@ -1891,13 +1922,13 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
   // the rows of A^T dO.  A is read at the start of a chunk, so the next
   // chunk's A is staged at the end of the current one; M is staged in the
   // chunk's first phase and read in its second.
-  constexpr int LDM = CH + 8;  // 144-byte rows: a transposing read's four rows on disjoint banks
   __shared__ __align__(16) int16_t Mt_s[CH * LDM];
   __shared__ __align__(16) int16_t At_s[CH * LDM];
   uint4 aq[2], mq[2];
   float asc, msc;
   // per-row values (G, beta~) and the dO slice are loaded one chunk ahead into
-  // registers and staged through double-buffered LDS at the end of each chunk
+  // registers and staged through LDS (the rows double-buffered) at the end of
+  // each chunk
   __shared__ float Grow[2][CH], Brow[2][CH];
   float pgv = 0.f;
   bf16_t pbv = 0;
@@ -1929,12 +1960,13 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
   // (the fragments by value: a reference to the register arrays would keep
   // them in memory)
   auto put_frag = [&](int16_t* t, uint4 r0, uint4 r1) {
-    *reinterpret_cast<uint4*>(t + (16 * w + r16) * LDM + 8 * g4) = r0;
-    *reinterpret_cast<uint4*>(t + (16 * w + r16) * LDM + 32 + 8 * g4) = r1;
+    *reinterpret_cast<uint4*>(t + L::m(prow, 8 * g4)) = r0;
+    *reinterpret_cast<uint4*>(t + L::m(prow, 32 + 8 * g4)) = r1;
   };
   // lane (g4, r16): column 16 w + r16 of the tile at rows 32 ks + 8 g4 .. +7
+  const TrOff moff = L::tr_m(8 * g4, 16 * w);
   auto get_tr = [&](const int16_t* t, int ks) {
-    return __builtin_bit_cast(uint4, ld_tr8(reinterpret_cast<const bf16_t*>(t), LDM, 32 * ks + 8 * g4, 16 * w));
+    return __builtin_bit_cast(uint4, ld_tr8(reinterpret_cast<const bf16_t*>(t) + 32 * LDM * ks, moff));
   };
   const unsigned qoff = 16u * (2 * XMT * w * 64 + lane);
   auto load_qt = [&](int cc) {
@@ -1971,12 +2003,11 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
     pdo = at(reinterpret_cast<const uint4*>(dO + c_tok(cc) * DV + j0),
              2u * ((unsigned)min(dr_ld, len - 1) * (H * DV) + dc));
   };
-  auto put_do = [&](int buf) {
+  auto put_do = [&]() {
     const uint4 val = do_ok ? pdo : make_uint4(0, 0, 0, 0);
     if (do_thr) {
-      // two 8-byte writes: the 72-byte rows keep only 8-byte alignment
-      *reinterpret_cast<uint2*>(dOs[buf] + dr * LDT + dc) = make_uint2(val.x, val.y);
-      *reinterpret_cast<uint2*>(dOs[buf] + dr * LDT + dc + 4) = make_uint2(val.z, val.w);
+      *reinterpret_cast<uint2*>(dOs + L::t(dr, dc)) = make_uint2(val.x, val.y);
+      *reinterpret_cast<uint2*>(dOs + L::t(dr, dc + 4)) = make_uint2(val.z, val.w);
     }
   };
 
@@ -1988,7 +2019,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
     load_qt(n - 1);
     load_rows(n - 1);
     put_rows((n - 1) & 1);
-    put_do((n - 1) & 1);
+    put_do();
     put_frag(At_s, aq[0], aq[1]);  // the loop stages each next chunk's A
   }
   __syncthreads();
@@ -2019,8 +2050,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
       for (int nt = 0; nt < NTV; ++nt) {
-        const bf16x8 yh = ld_tr8(Yh, LDT, 32 * ks + 8 * g4, 16 * nt);
-        const bf16x8 yl = ld_tr8(Yl, LDT, 32 * ks + 8 * g4, 16 * nt);
+        const bf16x8 yh = ld_tr8(Yh + 32 * LDT * ks, toff[nt]);
+        const bf16x8 yl = ld_tr8(Yl + 32 * LDT * ks, toff[nt]);
         ky[nt] = mfma16(yh, kf[ks], ky[nt]);
         ky[nt] = mfma16(yl, kf[ks], ky[nt]);
       }
@@ -2033,7 +2064,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
       q_split8(get_tr(At_s, ks), ath, atl);
 #pragma unroll
       for (int nt = 0; nt < NTV; ++nt) {
-        const bf16x8 dov = ld_tr8(dOs[buf], LDT, 32 * ks + 8 * g4, 16 * nt);
+        const bf16x8 dov = ld_tr8(dOs + 32 * LDT * ks, toff[nt]);
         ad[nt] = mfma16(dov, ath, ad[nt]);
         ad[nt] = mfma16(dov, atl, ad[nt]);
       }
@@ -2041,7 +2072,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
     const float at_cur = asc;
     // K rows past the chunk end repeat row len - 1; W2 is zero there
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) *reinterpret_cast<bf16x8*>(Kc + prow * LDKC + 32 * ks + 8 * g4) = kf[ks];
+    for (int ks = 0; ks < KS; ++ks) *reinterpret_cast<bf16x8*>(Kc + L::k(prow, 32 * ks + 8 * g4)) = kf[ks];
     put_frag(Mt_s, mq[0], mq[1]);
     load_k(nx);
     load_a(nx);
@@ -2054,7 +2085,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
         float dd_[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) dd_[e] = atm * ad[nt][e] + edec * ky[nt][e];
-        put_t4(dDh, dDl, prow * LDT + 16 * nt + col0, dd_);
+        put_t4(dDh, dDl, poff[nt], dd_);
       }
     }
     __syncthreads();
@@ -2069,8 +2100,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
       q_split8(get_tr(Mt_s, ks), mth, mtl);
 #pragma unroll
       for (int nt = 0; nt < NTV; ++nt) {
-        const bf16x8 xh = ld_tr8(dDh, LDT, 32 * ks + 8 * g4, 16 * nt);
-        const bf16x8 xl = ld_tr8(dDl, LDT, 32 * ks + 8 * g4, 16 * nt);
+        const bf16x8 xh = ld_tr8(dDh + 32 * LDT * ks, toff[nt]);
+        const bf16x8 xl = ld_tr8(dDl + 32 * LDT * ks, toff[nt]);
         drr[nt] = mfma16(xh, mth, drr[nt]);
         drr[nt] = mfma16(xl, mth, drr[nt]);
         drr[nt] = mfma16(xh, mtl, drr[nt]);
@@ -2084,7 +2115,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-      for (int mt = 0; mt < XMT; ++mt) ktf[ks][mt] = ld_tr8(Kc, LDKC, 32 * ks + 8 * g4, (DK / 4) * w + 16 * mt);
+      for (int mt = 0; mt < XMT; ++mt)
+        ktf[ks][mt] = ld_tr8(Kc + 32 * LDK * ks, L::tr_k(8 * g4, (DK / 4) * w + 16 * mt));
     // dR rows as int16 with one scale per row of the slice, stored after the
     // next phase's products are issued
     uint4 rpk;
@@ -2099,8 +2131,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
       const float eg = __expf(gg), begm = bb * __expf(gm);
 #pragma unroll
       for (int nt = 0; nt < NTV; ++nt) {
-        const int off = prow * LDT + 16 * nt + col0;
-        const uint2 d4 = *reinterpret_cast<const uint2*>(dOs[buf] + off);
+        const int off = poff[nt];
+        const uint2 d4 = *reinterpret_cast<const uint2*>(dOs + off);
         const float dov[4] = {__uint_as_float(d4.x << 16), __uint_as_float(d4.x & 0xFFFF0000u),
                               __uint_as_float(d4.y << 16), __uint_as_float(d4.y & 0xFFFF0000u)};
         float pg[4], w2[4];
@@ -2125,10 +2157,10 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
     for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
       for (int nt = 0; nt < NTV; ++nt) {
-        const bf16x8 ph = ld_tr8(Pgh, LDT, 32 * ks + 8 * g4, 16 * nt);
-        const bf16x8 pl = ld_tr8(Pgl, LDT, 32 * ks + 8 * g4, 16 * nt);
-        const bf16x8 wh = ld_tr8(W2h, LDT, 32 * ks + 8 * g4, 16 * nt);
-        const bf16x8 wl = ld_tr8(W2l, LDT, 32 * ks + 8 * g4, 16 * nt);
+        const bf16x8 ph = ld_tr8(Pgh + 32 * LDT * ks, toff[nt]);
+        const bf16x8 pl = ld_tr8(Pgl + 32 * LDT * ks, toff[nt]);
+        const bf16x8 wh = ld_tr8(W2h + 32 * LDT * ks, toff[nt]);
+        const bf16x8 wl = ld_tr8(W2l + 32 * LDT * ks, toff[nt]);
 #pragma unroll
         for (int mt = 0; mt < XMT; ++mt) {
           Y[mt][nt] = mfma16(ph, qtf[mt][ks], Y[mt][nt]);
@@ -2146,7 +2178,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_bwd_bf(
     load_qt(nx);
     // the next chunk's A (this chunk's was read before the first barrier)
     put_frag(At_s, aq[0], aq[1]);
-    put_do(buf ^ 1);
+    put_do();  // this chunk's dO was read before the second barrier
     put_rows(buf ^ 1);
     put_state();
     __syncthreads();

@@ -1332,7 +1332,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
   // row-major BV-wide tiles: 72-byte rows put the four rows of a transposing
   // read on disjoint banks
   constexpr int LDT = BV + 4;
-  static_assert(BV == 32, "stored states use one scale per 32-column block = one dv slice");
+  static_assert(BV == 32 || (BV == 16 && !STORE), "stored states use one scale per 32-column block = one dv slice");
   static_assert(!PHI || (DV == DK && !OUT && !STORE), "the transition product is a dk x dk state");
   __shared__ __align__(16) bf16_t Xh[DK * LDT];
   __shared__ __align__(16) bf16_t Xl[DK * LDT];
@@ -1404,12 +1404,12 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
     float sc = 0.f;
 #pragma unroll
     for (int mt = 0; mt < XMT; ++mt) {
-      float m = nmax_abs4(nmax_abs4(0.f, X[mt][0]), X[mt][1]);
+      float m = nmax_abs4(nmax_abs4(0.f, X[mt][0]), X[mt][NTV - 1]);
       m = rowgroup_max(m);
       const float inv = q_inv_scale(m);
       const unsigned row = xrow0 + 16 * mt;
       at(reinterpret_cast<uint4*>(dq), 2u * (row * BV + row8_col())) =
-          row8_from_pieces(q_pack4(X[mt][0], inv), q_pack4(X[mt][1], inv));
+          row8_from_pieces(q_pack4(X[mt][0], inv), q_pack4(X[mt][NTV - 1], inv));
       if (g4 == mt) sc = q_scale(m);
     }
     if (g4 < XMT) at(ds, 4u * (xrow0 + 16 * g4)) = sc;
@@ -1585,9 +1585,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
     uint4 dpk = make_uint4(0u, 0u, 0u, 0u);
     float dsc = 0.f;
     if constexpr (STORE) {
-      const float m = rowgroup_max(nmax_abs4(nmax_abs4(0.f, dl[0]), dl[1]));
+      const float m = rowgroup_max(nmax_abs4(nmax_abs4(0.f, dl[0]), dl[NTV - 1]));
       const float inv = q_inv_scale(m);
-      dpk = row8_from_pieces(q_pack4(dl[0], inv), q_pack4(dl[1], inv));
+      dpk = row8_from_pieces(q_pack4(dl[0], inv), q_pack4(dl[NTV - 1], inv));
       dsc = q_scale(m);
     }
     {
@@ -3393,6 +3393,19 @@ static hipError_t seg_copy_rows(const LaunchArgs& a, float* dst, const float* sr
                           st_bytes, a.N, hipMemcpyDeviceToDevice, a.stream);
 }
 
+// Whether the stateless forward scan takes 16-column slices: when these are at
+// most one per CU.  A step of a 16-column slice is a fifth shorter (half the
+// products, splits and stores, the same M and A splits), which counts while
+// half the chip idles: 1,000 tokens, H16, 64 / 128 chains of 32 columns: d128
+// 44.6 / 46.2 -> 36.0 / 37.6 us, d64 34.8 / 35.8 -> 27.5 / 28.8, d256 62.2 /
+// 66.6 -> 51.2 / 55.5.  With more chains the slices share CUs and repeat the K,
+// Q, M, A work: 192 chains 46.8 -> 56.1.  The same bits either way (columns do
+// not mix).  (The scans that store states keep 32 columns, the scale block of
+// the stored rows.)
+static bool narrow_slices(const LaunchArgs& a) {
+  return 2L * a.N * a.H * (a.dv / 32) <= device_cus();
+}
+
 template <int DK, int DV>
 static hipError_t run_fwd_bf(const LaunchArgs& a) {
   hipStream_t st = a.stream;
@@ -3453,6 +3466,10 @@ static hipError_t run_fwd_bf(const LaunchArgs& a) {
     k_scan_fwd_bf<DK, DV, SCAN_BV, true, true><<<scan_blocks(a.N, a.H, DV / SCAN_BV), NTHR, 0, st>>>(
         q, k, v, beta, bt, a.d, a.h0, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw, a.o, a.ht, a.Xq, a.Xs,
         a.Dq, a.Ds, a.Xfq, a.Xfs);
+  else if (narrow_slices(a))
+    k_scan_fwd_bf<DK, DV, 16, true, false><<<scan_blocks(a.N, a.H, DV / 16), NTHR, 0, st>>>(
+        q, k, v, beta, bt, a.d, a.h0, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw, a.o, a.ht, nullptr,
+        nullptr, nullptr, nullptr, nullptr, nullptr);
   else
     k_scan_fwd_bf<DK, DV, SCAN_BV, true, false><<<scan_blocks(a.N, a.H, DV / SCAN_BV), NTHR, 0, st>>>(
         q, k, v, beta, bt, a.d, a.h0, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw, a.o, a.ht, nullptr,

@@ -1807,9 +1807,9 @@ struct ScanTiles {
 // dD, Pg, W2) sit row-major in LDS and are read as operands with transposing
 // reads.
 // STORE = false: the recurrence alone (no Y, dR stores), for the segmented
-// backward's state pass.
-template <int DK, int DV, int BV, bool STORE = true>
-__global__ __launch_bounds__(NTHR, DK <= 128 ? 2 : 1) void k_scan_bwd_bf(
+// backward's state pass.  SW: the LDS layout (ScanTiles).
+template <int DK, int DV, int BV, bool STORE, bool SW>
+__global__ __launch_bounds__(NTHR, SW ? 2 : 1) void k_scan_bwd_bf(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ dO,
     const bf16_t* __restrict__ beta_tilde, const float* __restrict__ d, const float* __restrict__ dht,
     const SeqInfo* __restrict__ smap, const int* __restrict__ sorder, int N, int Tfix, int H,
@@ -1822,12 +1822,9 @@ __global__ __launch_bounds__(NTHR, DK <= 128 ? 2 : 1) void k_scan_bwd_bf(
   // as in the forward scan, all loop memory operations are unconditional
   constexpr int NTV = BV / 16, XMT = DK / 64, KS = DK / 32, CC = CH * CH;
   constexpr int NB = DV / 32;
-  // dk <= 128: unpadded tiles (78,848 bytes), so that two workgroups fit a CU
-  // where there are more chains than CUs (65,536 tokens, H16 d128, 512 chains:
-  // 721 -> 586 us, state pass 742 -> 544 us; at one workgroup per CU the same
-  // within 1%).  dk = 256 has room for one either way and keeps the padded
-  // rows, whose addresses need fewer registers (1.6% of the training pair).
-  using L = ScanTiles<(DK <= 128), DK>;
+  // SW: unpadded tiles (dk = 128: 78,848 bytes), so that two workgroups fit a
+  // CU; see scan_bwd_pairs for when
+  using L = ScanTiles<SW, DK>;
   constexpr int LDT = L::LDT, LDK = L::LDK, LDM = L::LDM;
   static_assert(BV == 32, "stored states use one scale per 32-column block = one dv slice");
   __shared__ __align__(16) bf16_t Yh[DK * LDT];
@@ -3393,6 +3390,26 @@ static hipError_t seg_copy_rows(const LaunchArgs& a, float* dst, const float* sr
                           st_bytes, a.N, hipMemcpyDeviceToDevice, a.stream);
 }
 
+// Whether the reverse scan's workgroups should fit a CU in pairs (unpadded LDS
+// tiles, dk <= 128): when there are more chains than CUs.  65,536 tokens, H16
+// d128, 512 chains: 721 -> 586 us, its state pass 742 -> 544 us.  With fewer
+// chains no pair forms and the padded tiles' simpler addresses are 2-5% faster;
+// at dk = 256 no pair fits either way.
+static bool scan_bwd_pairs(int N, int H, int dv) { return (long)N * H * (dv / SCAN_BV) > device_cus(); }
+
+// The reverse scan over N rows of H heads (arguments after st: the kernel's).
+template <int DK, int DV, bool STORE, typename... Args>
+static void launch_scan_bwd(int N, int H, hipStream_t st, Args... args) {
+  const unsigned grid = scan_blocks(N, H, DV / SCAN_BV);
+  if constexpr (DK <= 128) {
+    if (scan_bwd_pairs(N, H, DV)) {
+      k_scan_bwd_bf<DK, DV, SCAN_BV, STORE, true><<<grid, NTHR, 0, st>>>(args...);
+      return;
+    }
+  }
+  k_scan_bwd_bf<DK, DV, SCAN_BV, STORE, false><<<grid, NTHR, 0, st>>>(args...);
+}
+
 // Whether the stateless forward scan takes 16-column slices: when these are at
 // most one per CU.  A step of a 16-column slice is a fifth shorter (half the
 // products, splits and stores, the same M and A splits), which counts while
@@ -3543,14 +3560,12 @@ static hipError_t run_bwd_bf(const LaunchArgs& a) {
           a.Gw, nullptr, nullptr, a.Xq, a.Xs, a.Dq, a.Ds, nullptr, nullptr);
     }
     a.stage("scan_seg_grad");
-    k_scan_bwd_bf<DK, DV, SCAN_BV, false><<<scan_blocks(Nst, a.H, DV / SCAN_BV), NTHR, 0, st>>>(
-        q, k, dO, bt, a.d, nullptr, vsm, nullptr, Nst, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp,
+    launch_scan_bwd<DK, DV, false>(Nst, a.H, st, q, k, dO, bt, a.d, nullptr, vsm, nullptr, Nst, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp,
         a.Gw, a.segG, nullptr, nullptr, nullptr, nullptr, P, 1);
     a.stage("seg_combine_bwd");
     launch_seg_combine<DK, DV, true>(a, a.segPhi, a.segG, a.dht, a.segY0);
     a.stage("scan_bwd");
-    k_scan_bwd_bf<DK, DV, SCAN_BV><<<scan_blocks(Np, a.H, DV / SCAN_BV), NTHR, 0, st>>>(
-        q, k, dO, bt, a.d, a.segY0, vsm, nullptr, Np, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp,
+    launch_scan_bwd<DK, DV, true>(Np, a.H, st, q, k, dO, bt, a.d, a.segY0, vsm, nullptr, Np, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp,
         a.Gw, a.dh0 ? a.segDH0 : nullptr, a.Yq, a.Ys, a.dRq, a.dRs);
     if (a.dh0 && seg_copy_rows<DK, DV>(a, a.dh0, a.segDH0, 0) != hipSuccess)
       return hipErrorLaunchFailure;
@@ -3575,15 +3590,13 @@ static hipError_t run_bwd_bf(const LaunchArgs& a) {
               nullptr, a.Xq, a.Xs, a.Dq, a.Ds, a.Xfq, a.Xfs);
         },
         [&](hipStream_t s2) {
-          k_scan_bwd_bf<DK, DV, SCAN_BV><<<scan_blocks(a.N, a.H, DV / SCAN_BV), NTHR, 0, s2>>>(
-              q, k, dO, bt, a.d, a.dht, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp, a.Gw, a.dh0,
+          launch_scan_bwd<DK, DV, true>(a.N, a.H, s2, q, k, dO, bt, a.d, a.dht, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp, a.Gw, a.dh0,
               a.Yq, a.Ys, a.dRq, a.dRs);
         });
   }
   if (a.segP <= 1 && a.saved) {
     a.stage("scan_bwd");
-    k_scan_bwd_bf<DK, DV, SCAN_BV><<<scan_blocks(a.N, a.H, DV / SCAN_BV), NTHR, 0, st>>>(
-        q, k, dO, bt, a.d, a.dht, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp, a.Gw, a.dh0, a.Yq,
+    launch_scan_bwd<DK, DV, true>(a.N, a.H, st, q, k, dO, bt, a.d, a.dht, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp, a.Gw, a.dh0, a.Yq,
         a.Ys, a.dRq, a.dRs);
   }
   a.stage("intra_bwd");

@@ -23,7 +23,7 @@
 //   dA  = tril(dO D^T) ...       (the intra-chunk kernel collects the rest)
 //
 // Kernels, in launch order:
-//   k_seq_map, k_chunk_fill  sequence/chunk tables from cu_seqlens (fixed-length rows too)
+//   k_seq_map, k_chunk_fill  sequence/chunk tables from cu_seqlens (packed sequences)
 // (bf16 names; the fp32 path's own list stands at its kernels)
 //   k_prep_bf       per chunk-head: G, A, M                     (chunk-parallel)
 //   k_scan_fwd_bf   per (sequence, head, 32-column slice of dv): the sequential
@@ -43,20 +43,48 @@ namespace comba {
 // ---------------------------------------------------------------------------
 // sequence / chunk tables
 // ---------------------------------------------------------------------------
-// k_seq_map: one workgroup; per sequence its token range (clamped into
+// k_seq_map (packed sequences): per sequence its token range (clamped into
 // [0, Ttot], so that malformed offsets cannot address memory outside the token
 // range) and its first chunk (exclusive scan of the chunk counts, NTHR
-// sequences per pass).
-// It also writes the order in which the scans take the sequences, sorder[r] =
-// the sequence of rank r: longest first (ties by index) for up to SORT_MAX
-// sequences, so that the longest chains start first; identity beyond that.
+// sequences per pass).  It also writes the order in which the scans take the
+// sequences, sorder[r] = the sequence of rank r: longest first (ties by index)
+// for up to SORT_MAX sequences, so that the longest chains start first;
+// identity beyond that.
+// FILL (up to SORT_MAX sequences): the chunk table too, in the same launch:
+// every workgroup forms the sequence table in LDS (workgroup 0 writes it out)
+// and fills its share of the chunk slots, instead of a second kernel that
+// waits for the first.
 constexpr int SORT_MAX = 1024;
-__global__ __launch_bounds__(NTHR) void k_seq_map(const int32_t* __restrict__ cu, int N, int Tseq,
-                                                  int Ttot, int ncmax, SeqInfo* __restrict__ smap,
-                                                  int* __restrict__ sorder) {
+__device__ __forceinline__ ChunkInfo chunk_of(const SeqInfo* smap, int N, int c) {
+  // its sequence is the last one whose first chunk is <= c (first chunks never
+  // decrease, and an empty sequence shares its first chunk with the next one);
+  // slots past the last chunk are empty (len 0, seq -1)
+  int lo = 0, hi = N;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (smap[mid].chunk0 <= c) lo = mid + 1;
+    else hi = mid;
+  }
+  ChunkInfo ci{0, 0, -1, 0};
+  if (lo > 0) {
+    const SeqInfo si = smap[lo - 1];
+    const int j = c - si.chunk0;
+    if (j < si.nchunks) {
+      ci.tok0 = si.tok0 + j * CH;
+      ci.len = min(CH, si.len - j * CH);
+      ci.seq = lo - 1;
+    }
+  }
+  return ci;
+}
+template <bool FILL>
+__global__ __launch_bounds__(NTHR) void k_seq_map(const int32_t* __restrict__ cu, int N, int Ttot, int ncmax,
+                                                  SeqInfo* __restrict__ smap, int* __restrict__ sorder,
+                                                  ChunkInfo* __restrict__ cmap) {
   __shared__ int wave_tot[NWAVE];
   __shared__ int carry;
   __shared__ int nckS[SORT_MAX];
+  __shared__ SeqInfo smapS[FILL ? SORT_MAX : 1];
   const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
   if (tid == 0) carry = 0;
   __syncthreads();
@@ -64,16 +92,11 @@ __global__ __launch_bounds__(NTHR) void k_seq_map(const int32_t* __restrict__ cu
     const int s = base + tid;
     int tok0 = 0, len = 0, nck = 0;
     if (s < N) {
-      if (cu) {
-        int a = cu[s], b = cu[s + 1];
-        a = min(max(a, 0), Ttot);
-        b = min(max(b, a), Ttot);
-        tok0 = a;
-        len = b - a;
-      } else {
-        tok0 = s * Tseq;
-        len = Tseq;
-      }
+      int a = cu[s], b = cu[s + 1];
+      a = min(max(a, 0), Ttot);
+      b = min(max(b, a), Ttot);
+      tok0 = a;
+      len = b - a;
       nck = (len + CH - 1) / CH;
     }
     int x = nck;
@@ -94,7 +117,8 @@ __global__ __launch_bounds__(NTHR) void k_seq_map(const int32_t* __restrict__ cu
       si.nchunks = min(nck, max(0, ncmax - chunk0));
       si.tok0 = tok0;
       si.len = len;
-      smap[s] = si;
+      if constexpr (FILL) smapS[s] = si;
+      if (!FILL || blockIdx.x == 0) smap[s] = si;
       if (N <= SORT_MAX) nckS[s] = nck;
     }
     __syncthreads();
@@ -105,18 +129,22 @@ __global__ __launch_bounds__(NTHR) void k_seq_map(const int32_t* __restrict__ cu
     }
     __syncthreads();
   }
-  for (int s = tid; s < N; s += NTHR) {
-    int r = s;
-    if (N <= SORT_MAX) {
-      const int n = nckS[s];
-      r = 0;
-      for (int j = 0; j < N; ++j) {
-        const int m = nckS[j];
-        r += (m > n || (m == n && j < s)) ? 1 : 0;
+  if (!FILL || blockIdx.x == 0) {
+    for (int s = tid; s < N; s += NTHR) {
+      int r = s;
+      if (N <= SORT_MAX) {
+        const int n = nckS[s];
+        r = 0;
+        for (int j = 0; j < N; ++j) {
+          const int m = nckS[j];
+          r += (m > n || (m == n && j < s)) ? 1 : 0;
+        }
       }
+      sorder[r] = s;
     }
-    sorder[r] = s;
   }
+  if constexpr (FILL)
+    for (int c = blockIdx.x * NTHR + tid; c < ncmax; c += gridDim.x * NTHR) cmap[c] = chunk_of(smapS, N, c);
 }
 
 // k_seg_map: the virtual sequence table of the segmented scans over packed
@@ -139,35 +167,10 @@ __global__ __launch_bounds__(NTHR) void k_seg_map(const SeqInfo* __restrict__ sm
   vmap[i] = v;
 }
 
-// k_chunk_fill: one thread per chunk slot c < ncmax.  Its sequence is the last
-// one whose first chunk is <= c (first chunks never decrease, and an empty
-// sequence shares its first chunk with the next one), found by binary search;
-// slots past the last chunk are marked empty (len 0, seq -1).
+// k_chunk_fill: the chunk table beyond SORT_MAX sequences, one thread per chunk slot.
 __global__ __launch_bounds__(NTHR) void k_chunk_fill(const SeqInfo* __restrict__ smap, int N,
                                                      int ncmax, ChunkInfo* __restrict__ cmap) {
-  for (int c = blockIdx.x * NTHR + threadIdx.x; c < ncmax; c += gridDim.x * NTHR) {
-    int lo = 0, hi = N;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (smap[mid].chunk0 <= c) lo = mid + 1;
-      else hi = mid;
-    }
-    ChunkInfo ci;
-    ci.tok0 = 0;
-    ci.len = 0;
-    ci.seq = -1;
-    ci.pad = 0;
-    if (lo > 0) {
-      const SeqInfo si = smap[lo - 1];
-      const int j = c - si.chunk0;
-      if (j < si.nchunks) {
-        ci.tok0 = si.tok0 + j * CH;
-        ci.len = min(CH, si.len - j * CH);
-        ci.seq = lo - 1;
-      }
-    }
-    cmap[c] = ci;
-  }
+  for (int c = blockIdx.x * NTHR + threadIdx.x; c < ncmax; c += gridDim.x * NTHR) cmap[c] = chunk_of(smap, N, c);
 }
 
 // Chunk and sequence tables of the kernels: for fixed-length rows
@@ -3276,14 +3279,17 @@ static unsigned scan_blocks(int N, int H, int nsl) {
   return (unsigned)((((long)N * H + 7) / 8) * 8 * nsl);
 }
 
-// Sequence and chunk tables: the per-sequence scan (one workgroup), then one
-// thread per chunk slot.
+// Sequence and chunk tables of packed sequences.
 static void launch_chunk_map(const LaunchArgs& a, hipStream_t st) {
-  k_seq_map<<<1, NTHR, 0, st>>>(a.cu_seqlens, a.N, a.Tseq, a.Ttot, a.ncmax, a.smap, a.sorder);
-  if (a.ncmax > 0) {
-    const int blocks = (a.ncmax + NTHR - 1) / NTHR;
-    k_chunk_fill<<<blocks < 1024 ? blocks : 1024, NTHR, 0, st>>>(a.smap, a.N, a.ncmax, a.cmap);
+  const int blocks = (a.ncmax + NTHR - 1) / NTHR;
+  if (a.N <= SORT_MAX) {
+    // every workgroup scans all offsets: few of them, several chunk slots each
+    k_seq_map<true><<<blocks < 1 ? 1 : blocks < 64 ? blocks : 64, NTHR, 0, st>>>(
+        a.cu_seqlens, a.N, a.Ttot, a.ncmax, a.smap, a.sorder, a.cmap);
+    return;
   }
+  k_seq_map<false><<<1, NTHR, 0, st>>>(a.cu_seqlens, a.N, a.Ttot, a.ncmax, a.smap, a.sorder, a.cmap);
+  if (a.ncmax > 0) k_chunk_fill<<<blocks < 1024 ? blocks : 1024, NTHR, 0, st>>>(a.smap, a.N, a.ncmax, a.cmap);
 }
 
 // fp32 inputs.  The forward keeps its workspace at two 64 x 64 tiles per

@@ -1171,7 +1171,7 @@ __global__ __launch_bounds__(NTHR) void k_prep_bf(
   __shared__ __align__(16) unsigned char QLbuf[QLB];
   bf16_t* Qs = reinterpret_cast<bf16_t*>(QLbuf);
   float* Ls = reinterpret_cast<float*>(QLbuf);
-  __shared__ float Gs[CH], Bs[CH];
+  __shared__ __align__(16) float Gs[CH], Bs[CH];
   __shared__ float colmax[NWAVE][CH];  // per-wave column maxima of |A|
 
   const ChunkInfo ci = chunk_at(cmap, blockIdx.x, Tfix);
@@ -1209,26 +1209,65 @@ __global__ __launch_bounds__(NTHR) void k_prep_bf(
     }
   }
 
-  floatx4 akk[1][4], aqk[1][4];
-  zero_acc(akk);
-  zero_acc(aqk);
-  mma<false, 1, 4, DK>(akk, Ks + 16 * w * LDK, LDK, Ks, LDK);
-  mma<false, 1, 4, DK>(aqk, Qs + 16 * w * LDK, LDK, Ks, LDK);
+  // This wave's row tile of the 64 x 64 products, and its block column of the
+  // inverse below.  Row tile rt needs column tiles up to rt, block column jb the
+  // blocks below it: the rotation spreads the long ones over the SIMDs of the
+  // workgroups that share a CU.
+  const int rt = __builtin_amdgcn_readfirstlane((w + blockIdx.x + blockIdx.y) & (NWAVE - 1));
+  floatx4 akk[4], aqk[4];
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) akk[nt] = aqk[nt] = zero4();
+  {
+    bf16x8 kf[DK / 32], qf[DK / 32];
+#pragma unroll
+    for (int ks = 0; ks < DK / 32; ++ks) {
+      const int off = (16 * rt + r16) * LDK + 32 * ks + 8 * g4;
+      kf[ks] = ld8(Ks + off);
+      qf[ks] = ld8(Qs + off);
+    }
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+      if (nt <= rt) {
+#pragma unroll
+        for (int ks = 0; ks < DK / 32; ++ks) {
+          const bf16x8 b = ld8(Ks + (16 * nt + r16) * LDK + 32 * ks + 8 * g4);
+          akk[nt] = mfma16(kf[ks], b, akk[nt]);
+          aqk[nt] = mfma16(qf[ks], b, aqk[nt]);
+        }
+      }
+  }
+  // the gates of this lane's rows and columns, read once
+  const int r0 = 16 * rt + 4 * g4;
+  const float4 gr4 = *reinterpret_cast<const float4*>(Gs + r0), br4 = *reinterpret_cast<const float4*>(Bs + r0);
+  const float gp = Gs[max(r0 - 1, 0)];
+  float gc[4];
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) gc[nt] = Gs[16 * nt + r16];
   __syncthreads();  // every read of the Q tile is done: L overwrites it
-  // A in the accumulator layout: av[nt][e] = A[16w + 4g4 + e][16nt + r16]
+  // A in the accumulator layout: av[nt][e] = A[r0 + e][16nt + r16].  Branch-free
+  // inside a tile (a branch per entry waited for its gates' LDS reads 32 times);
+  // e^{G_{r-1} - G_c} of a row is e^{G_r - G_c} of the row above.
   float av[4][4];
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt) {
+    const int c = 16 * nt + r16;
+    float l[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int r = 16 * w + acc_row(0, e), c = acc_col(nt);
-      const float kk = akk[0][nt][e];
-      float a = 0.f, l = 0.f;
-      if (r >= c) a = (aqk[0][nt][e] - dh * kk) * __expf(Gs[r] - Gs[c]);
-      if (r > c) l = Bs[r] * __expf(Gs[r - 1] - Gs[c]) * kk;
-      av[nt][e] = a;
-      Ls[r * LDL + c] = l;
+    for (int e = 0; e < 4; ++e) av[nt][e] = 0.f;
+    if (nt <= rt) {
+      const float gr[4] = {gr4.x, gr4.y, gr4.z, gr4.w}, br[4] = {br4.x, br4.y, br4.z, br4.w};
+      float above = __expf(gp - gc[nt]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float kk = akk[nt][e], gam = __expf(gr[e] - gc[nt]);
+        // above the diagonal the exponentials may overflow: selected away
+        av[nt][e] = r0 + e >= c ? (aqk[nt][e] - dh * kk) * gam : 0.f;
+        l[e] = r0 + e > c ? br[e] * above * kk : 0.f;
+        above = gam;
+      }
     }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) Ls[(r0 + e) * LDL + c] = l[e];
   }
   // column maxima of this wave's 16 rows, combined over the waves below
 #pragma unroll
@@ -1251,7 +1290,7 @@ __global__ __launch_bounds__(NTHR) void k_prep_bf(
       const int c0 = 16 * nt + qt_col();
       const floatx4 inv = {q_inv_scale(col_max(c0)), q_inv_scale(col_max(c0 + 1)),
                            q_inv_scale(col_max(c0 + 2)), q_inv_scale(col_max(c0 + 3))};
-      *reinterpret_cast<uint2*>(Aq + chh * CC + frag_off(16 * w + qt_row(), c0)) =
+      *reinterpret_cast<uint2*>(Aq + chh * CC + frag_off(16 * rt + qt_row(), c0)) =
           q_pack4v(quad_transpose(floatx4{av[nt][0], av[nt][1], av[nt][2], av[nt][3]}), inv);
     }
     if (w == 0) As[chh * CH + lane] = q_scale(col_max(lane));
@@ -1261,9 +1300,8 @@ __global__ __launch_bounds__(NTHR) void k_prep_bf(
   // unit lower triangular).  Wave w owns block column jb: it inverts the
   // diagonal block, D_jb = (I + L_jb,jb)^{-1}, then walks down its block column
   // with M_ij = -D_i sum_{j <= k < i} L_ik M_kj.  Block columns do not depend
-  // on one another; the rotation spreads the longest column (jb = 0) over the
-  // SIMDs of workgroups that share a CU.
-  const int jb = (w + blockIdx.x + blockIdx.y) & (NWAVE - 1);
+  // on one another.
+  const int jb = rt;
   floatx4 mb[4];
   invert_diagonal<LDL>(Ls, jb, mb);
   __syncthreads();

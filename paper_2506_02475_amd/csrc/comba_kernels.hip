@@ -1174,10 +1174,13 @@ __global__ __launch_bounds__(NTHR) void k_prep_bf(
   __shared__ __align__(16) float Gs[CH], Bs[CH];
   __shared__ float colmax[NWAVE][CH];  // per-wave column maxima of |A|
 
-  const ChunkInfo ci = chunk_at(cmap, blockIdx.x, Tfix);
+  // Heads fastest: the workgroups that run together read whole token rows.
+  // (Chunks fastest, a head's 256-byte pieces of a row were read far apart in
+  // time: 512K packed tokens 1574 us, now 1300; 65,536 tokens 246 -> 197.)
+  const int chunk = blockIdx.x / H, h = blockIdx.x - chunk * H;
+  const ChunkInfo ci = chunk_at(cmap, chunk, Tfix);
   if (ci.len <= 0) return;
-  const int h = blockIdx.y;
-  const long chh = (long)blockIdx.x * H + h;
+  const long chh = blockIdx.x;
   const long tok = (long)ci.tok0 * H + h;
   const int w = wave_id(), lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
   const float dh = d[h];
@@ -1213,7 +1216,7 @@ __global__ __launch_bounds__(NTHR) void k_prep_bf(
   // inverse below.  Row tile rt needs column tiles up to rt, block column jb the
   // blocks below it: the rotation spreads the long ones over the SIMDs of the
   // workgroups that share a CU.
-  const int rt = __builtin_amdgcn_readfirstlane((w + blockIdx.x + blockIdx.y) & (NWAVE - 1));
+  const int rt = __builtin_amdgcn_readfirstlane((w + chunk + h) & (NWAVE - 1));
   floatx4 akk[4], aqk[4];
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt) akk[nt] = aqk[nt] = zero4();
@@ -2324,8 +2327,9 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_bf(
                 "the copies take whole rounds of one piece per wave");
   __shared__ __align__(16) char R0[RAW];
 
-  // Persistent: workgroup b takes items b, b + gridDim.x, ... (item = chunk +
-  // ncmax * head).
+  // Persistent: workgroup b takes items b, b + gridDim.x, ... (item = chunk H +
+  // head: the workgroups that run together read and write whole token rows;
+  // 303 -> 289 us at the 1.3B layer against chunks fastest).
   const int nitems = ncmax * H;
   bool have = false;            // the item's first block is waiting in R0
   float g_nx = 0.f;              // and its gates
@@ -2338,9 +2342,9 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_bf(
   asm volatile("v_mov_b32 %0, %1" : "=v"(tid) : "v"((int)threadIdx.x));
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
   const int rt = w & 3, ch = w >> 2;
-  const int h = item / ncmax;
-  const long chh = (long)(item % ncmax) * H + h;
-  const ChunkInfo ci = chunk_at(cmap, item % ncmax, Tfix);
+  const int chunk = item / H, h = item - chunk * H;
+  const long chh = item;
+  const ChunkInfo ci = chunk_at(cmap, chunk, Tfix);
   if (ci.len <= 0) {
     if (tid == 0) ddp[chh] = 0.f;
     have = false;
@@ -2573,9 +2577,10 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_bf(
   // memory-counter bookkeeping: the next item waits for them explicitly.
   {
     const int nx = item + gridDim.x, nxc = min(nx, nitems - 1);
-    const ChunkInfo ci2 = chunk_at(cmap, nxc % ncmax, Tfix);
-    const int h2 = nxc / ncmax, len2 = ci2.len;
-    const long chh2 = (long)(nxc % ncmax) * H + h2, tok2 = (long)ci2.tok0 * H + h2;
+    const int chunk2 = nxc / H, h2 = nxc - chunk2 * H;
+    const ChunkInfo ci2 = chunk_at(cmap, chunk2, Tfix);
+    const int len2 = ci2.len;
+    const long chh2 = nxc, tok2 = (long)ci2.tok0 * H + h2;
     have = nx < nitems && len2 > 0;
     if (have) {
       // Straight-line rounds of one 1 KiB piece per wave: every wave would
@@ -2808,9 +2813,9 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_bf(
     // row (this item has tokens, so every such address is valid): behind a
     // branch, the merge would copy them and wait right there.
     const int nxc = min(item + (int)gridDim.x, nitems - 1);
-    const ChunkInfo ci2 = chunk_at(cmap, nxc % ncmax, Tfix);
-    const int h2 = nxc / ncmax;
-    const long chh2 = (long)(nxc % ncmax) * H + h2, tok2 = (long)ci2.tok0 * H + h2;
+    const int chunk2 = nxc / H, h2 = nxc - chunk2 * H;
+    const ChunkInfo ci2 = chunk_at(cmap, chunk2, Tfix);
+    const long chh2 = nxc, tok2 = (long)ci2.tok0 * H + h2;
     g_nx = Gw[chh2 * CH + (tid & (CH - 1))];
     const long brow2 = tok2 + (long)min(tid & (CH - 1), max(ci2.len, 1) - 1) * H;
     b_nx = beta[brow2];
@@ -2870,9 +2875,9 @@ __global__ __launch_bounds__(IB_THR, 1) void k_intra_bwd_wide(
 
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
   const int rt = w & 3, ch = w >> 2;
-  const int h = blockIdx.y;
-  const long chh = (long)blockIdx.x * H + h;
-  const ChunkInfo ci = chunk_at(cmap, blockIdx.x, Tfix);
+  const int chunk = blockIdx.x / H, h = blockIdx.x - chunk * H;  // heads fastest
+  const long chh = blockIdx.x;
+  const ChunkInfo ci = chunk_at(cmap, chunk, Tfix);
   if (ci.len <= 0) {
     if (tid == 0) ddp[chh] = 0.f;
     return;
@@ -3312,6 +3317,9 @@ static void side(hipStream_t st, Main&& main_work, Side&& side_work) {
     (void)hipStreamSynchronize(ss->s);  // keep the order on the host if the join cannot be enqueued
 }
 
+// 1-D grid of the chunk-parallel kernels: chunk-head chunk H + head.
+static unsigned chunk_heads(const LaunchArgs& a) { return (unsigned)a.ncmax * (unsigned)a.H; }
+
 // 1-D grid of the bf16 scans: whole groups of 8 chains (see scan_item).
 static unsigned scan_blocks(int N, int H, int nsl) {
   return (unsigned)((((long)N * H + 7) / 8) * 8 * nsl);
@@ -3485,10 +3493,10 @@ static hipError_t run_fwd_bf(const LaunchArgs& a) {
   a.stage(a.saved ? "prep_save" : "prep");
   if (a.ncmax > 0) {
     if (a.saved)
-      k_prep_bf<DK, true><<<dim3(a.ncmax, a.H), NTHR, 0, st>>>(
+      k_prep_bf<DK, true><<<chunk_heads(a), NTHR, 0, st>>>(
           q, k, a.g, bt, a.d, a.cmap, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp, a.Gw);
     else
-      k_prep_bf<DK, false><<<dim3(a.ncmax, a.H), NTHR, 0, st>>>(
+      k_prep_bf<DK, false><<<chunk_heads(a), NTHR, 0, st>>>(
           q, k, a.g, bt, a.d, a.cmap, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, nullptr, a.Gw);
   }
   if (a.segP > 1) {
@@ -3548,7 +3556,7 @@ static void launch_intra_bwd(const LaunchArgs& a, const bf16_t* q, const bf16_t*
   if constexpr (DK > 128 || DV > 128) {
     // head dim 256: passes of 128 dk columns, one workgroup per chunk-head (at
     // dv = 256 the persistent kernel spills; this one is 25% faster there)
-    k_intra_bwd_wide<DK, DV, TG><<<dim3(a.ncmax, a.H), IB_THR, 0, a.stream>>>(
+    k_intra_bwd_wide<DK, DV, TG><<<chunk_heads(a), IB_THR, 0, a.stream>>>(
         q, k, v, dO, beta, bt, a.d, a.cmap, Tfix, a.H, a.Gw, a.Xq, a.Xs, a.Dq, a.Ds, a.Yq, a.Ys,
         a.dRq, a.dRs, dq, dk, dv, db, dbt, a.dg, a.ddp);
   } else {
@@ -3595,7 +3603,7 @@ static hipError_t run_bwd_bf(const LaunchArgs& a) {
       }
       a.stage("prep");
       if (a.ncmax > 0)
-        k_prep_bf<DK, true><<<dim3(a.ncmax, a.H), NTHR, 0, st>>>(
+        k_prep_bf<DK, true><<<chunk_heads(a), NTHR, 0, st>>>(
             q, k, a.g, bt, a.d, a.cmap, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp, a.Gw);
       seg_forward_states<DK, DV>(a, q, k, v, beta, bt, true, vsm, Tp);
       a.stage("scan_fwd_store");
@@ -3620,7 +3628,7 @@ static hipError_t run_bwd_bf(const LaunchArgs& a) {
     }
     a.stage("prep");
     if (a.ncmax > 0)
-      k_prep_bf<DK, true><<<dim3(a.ncmax, a.H), NTHR, 0, st>>>(
+      k_prep_bf<DK, true><<<chunk_heads(a), NTHR, 0, st>>>(
           q, k, a.g, bt, a.d, a.cmap, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp, a.Gw);
     // the chunk states (forward recurrence) and the reverse scan depend only on
     // prep's operands, not on each other (the reverse scan reads no state):

@@ -326,8 +326,10 @@ constexpr int fwd_head_groups(int H) {
 
 template <typename Tin, int DK, int DV>
 __global__ __launch_bounds__(64 * PRO_WAVES) void k_prologue_fwd(PrologueArgs a) {
-  const int run = blockIdx.x * PRO_WAVES + wave_id_s();
-  const int z = blockIdx.z, hg = blockIdx.y;
+  // head groups fastest: the workgroups that run together read whole token rows
+  const int rb = blockIdx.x / a.groups, hg = blockIdx.x - rb * a.groups;
+  const int run = rb * PRO_WAVES + wave_id_s();
+  const int z = blockIdx.y;
   if (z == 0)
     prologue_fwd_run<Tin, DK, true>(static_cast<const Tin*>(a.xq), a.wq, static_cast<Tin*>(a.q),
                                     a.cu_seqlens, a.N, a.Tseq, a.Ttot, a.H, run, a.frun, hg, a.eps);
@@ -496,10 +498,10 @@ __device__ __forceinline__ void prologue_bwd_run(const Tin* __restrict__ x, cons
 // Sum of the workgroup's wave shares of dw (fixed order) into its partial
 // [block][h][D] (four taps per float4), for the heads of its group.
 template <int D>
-__device__ __forceinline__ void combine_dw(const float4 (*dws)[256], float* __restrict__ dwp, int H) {
+__device__ __forceinline__ void combine_dw(const float4 (*dws)[256], float* __restrict__ dwp, int H, int rb, int hg) {
   constexpr int HPW = 64 / (D / PRO_BCL);
-  const int h0 = blockIdx.y * HPW;
-  float4* out = reinterpret_cast<float4*>(dwp) + ((long)blockIdx.x * H + h0) * D;
+  const int h0 = hg * HPW;
+  float4* out = reinterpret_cast<float4*>(dwp) + ((long)rb * H + h0) * D;
   const int n = min(HPW, H - h0) * D;  // slots of existing heads (n <= 0: none)
   for (int c = threadIdx.x; c < n; c += 64 * PRO_WAVES) {
     float4 s = dws[0][c];
@@ -517,22 +519,23 @@ __global__ __launch_bounds__(64 * PRO_WAVES) void k_prologue_bwd(PrologueArgs a)
   static_assert(64 * PRO_BCL <= 256, "slots per wave share");
   __shared__ float4 dws[PRO_WAVES][256];  // per wave: the four tap sums of each channel
   // every wave reaches the barrier below (runs past the tokens add zeros)
-  const int run = blockIdx.x * PRO_WAVES + wave_id_s();
-  const int z = blockIdx.z;
+  const int rb = blockIdx.x / a.groups, hg = blockIdx.x - rb * a.groups;  // head groups fastest
+  const int run = rb * PRO_WAVES + wave_id_s();
+  const int z = blockIdx.y;
   float4* dwl = dws[wave_id_s()];
   if (z == 0)
     prologue_bwd_run<Tin, DK, true>(static_cast<const Tin*>(a.xq), a.wq, a.gq, a.dxq, dwl,
-                                    a.cu_seqlens, a.N, a.Tseq, a.Ttot, a.H, run, blockIdx.y, a.eps);
+                                    a.cu_seqlens, a.N, a.Tseq, a.Ttot, a.H, run, hg, a.eps);
   else if (z == 1)
     prologue_bwd_run<Tin, DK, true>(static_cast<const Tin*>(a.xk), a.wk, a.gk, a.dxk, dwl,
-                                    a.cu_seqlens, a.N, a.Tseq, a.Ttot, a.H, run, blockIdx.y, a.eps);
+                                    a.cu_seqlens, a.N, a.Tseq, a.Ttot, a.H, run, hg, a.eps);
   else
     prologue_bwd_run<Tin, DV, false>(static_cast<const Tin*>(a.xv), a.wv, a.gv, a.dxv, dwl,
-                                     a.cu_seqlens, a.N, a.Tseq, a.Ttot, a.H, run, blockIdx.y, a.eps);
+                                     a.cu_seqlens, a.N, a.Tseq, a.Ttot, a.H, run, hg, a.eps);
   __syncthreads();
-  if (z == 0) combine_dw<DK>(dws, a.dwpq, a.H);
-  else if (z == 1) combine_dw<DK>(dws, a.dwpk, a.H);
-  else combine_dw<DV>(dws, a.dwpv, a.H);
+  if (z == 0) combine_dw<DK>(dws, a.dwpq, a.H, rb, hg);
+  else if (z == 1) combine_dw<DK>(dws, a.dwpk, a.H, rb, hg);
+  else combine_dw<DV>(dws, a.dwpv, a.H, rb, hg);
 }
 
 // Head groups of the backward grid: enough for the tensor with the most.
@@ -607,19 +610,21 @@ static int fwd_run_tokens(int Ttot, int groups) {
 
 template <typename Tin, int DK, int DV>
 static hipError_t run_prologue(const PrologueArgs& a, bool bwd) {
-  const dim3 grid((a.nruns + PRO_WAVES - 1) / PRO_WAVES, a.H, 3);
   if (!bwd) {
     a.stage("prologue_fwd");
     PrologueArgs f = a;
     const int groups = fwd_head_groups<DK, DV>(a.H);
     f.frun = fwd_run_tokens<Tin, DK, DV>(a.Ttot, groups);
     const int fruns = (a.Ttot + f.frun - 1) / f.frun;
-    const dim3 fgrid((fruns + PRO_WAVES - 1) / PRO_WAVES, groups, 3);
+    f.groups = groups;
+    const dim3 fgrid((unsigned)((fruns + PRO_WAVES - 1) / PRO_WAVES) * groups, 3);
     if (fruns > 0) k_prologue_fwd<Tin, DK, DV><<<fgrid, 64 * PRO_WAVES, 0, a.stream>>>(f);
   } else {
     a.stage("prologue_bwd");
-    const dim3 bgrid(grid.x, bwd_head_groups<DK, DV>(a.H), 3);
-    if (a.nruns > 0) k_prologue_bwd<Tin, DK, DV><<<bgrid, 64 * PRO_WAVES, 0, a.stream>>>(a);
+    PrologueArgs b = a;
+    b.groups = bwd_head_groups<DK, DV>(a.H);
+    const dim3 bgrid((unsigned)((a.nruns + PRO_WAVES - 1) / PRO_WAVES) * b.groups, 3);
+    if (a.nruns > 0) k_prologue_bwd<Tin, DK, DV><<<bgrid, 64 * PRO_WAVES, 0, a.stream>>>(b);
     a.stage("prologue_dw");
     const int dmax = a.dk > a.dv ? a.dk : a.dv;
     k_prologue_dw<<<dim3((a.H * dmax + DW_COLS - 1) / DW_COLS, 3), DW_COLS * DW_GROUPS, 0, a.stream>>>(a);

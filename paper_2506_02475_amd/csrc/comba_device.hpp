@@ -353,6 +353,26 @@ __device__ __forceinline__ int row8_col() {
   return 8 * (((g & 1) << 1) | (g >> 1));
 }
 
+// Moves 16-byte pieces of a 16-row, 64-byte-row tile from lane (g, i) = row i,
+// piece G(g) to the lane of their place in memory, 4 row + piece: consecutive
+// lanes then store consecutive bytes.  (A store whose consecutive lanes hold
+// different rows costs the address unit one request per lane instead of one
+// per four lanes.)  piece_to_memory: G(g) = g (accumulators of the transposed
+// products); row8_to_memory: the order that row8_from_pieces leaves.
+__device__ __forceinline__ floatx4 piece_to_memory(const floatx4& x) {
+  const int src = 4 * (16 * (lane_id() & 3) + (lane_id() >> 2));
+  floatx4 y;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    y[e] = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(x[e])));
+  return y;
+}
+__device__ __forceinline__ uint4 row8_to_memory(const uint4& x) {
+  const int p = lane_id() & 3, src = 4 * (16 * (((p & 1) << 1) | (p >> 1)) + (lane_id() >> 2));
+  return make_uint4(__builtin_amdgcn_ds_bpermute(src, x.x), __builtin_amdgcn_ds_bpermute(src, x.y),
+                    __builtin_amdgcn_ds_bpermute(src, x.z), __builtin_amdgcn_ds_bpermute(src, x.w));
+}
+
 // Two fp32 values as packed bf16 (hi, lo): hi = bf16(x) (nearest), lo =
 // bf16(x - hi), each pair converted by one v_cvt_pk_bf16_f32 (3 VALU per value).
 typedef float f32x2_t __attribute__((ext_vector_type(2)));

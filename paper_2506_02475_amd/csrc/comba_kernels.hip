@@ -1339,6 +1339,27 @@ __global__ __launch_bounds__(NTHR) void k_prep_bf(
   }
 }
 
+// LDS tiles of a scan: 32-column tiles (t), the chunk's K rows (k) and 64 x 64
+// M / A tiles (m), unpadded with exchanged pieces (sw32, sw16) or with padded
+// rows (72, 2 dk + 48 and 144 bytes: the four rows of a transposing read on
+// disjoint banks).
+template <bool SW, int DK>
+struct ScanTiles {
+  static constexpr int LDT = SW ? 32 : 36, LDK = SW ? DK : DK + 24, LDM = SW ? CH : CH + 8;
+  static __device__ __forceinline__ int t(int r, int c) { return SW ? sw32(r, c) : r * LDT + c; }
+  static __device__ __forceinline__ int k(int r, int c) { return SW ? sw16<DK>(r, c) : r * LDK + c; }
+  static __device__ __forceinline__ int m(int r, int c) { return SW ? sw16<CH>(r, c) : r * LDM + c; }
+  // ld_tr8 offsets at rows r0 .., columns c0 .. (see TrOff)
+  static __device__ __forceinline__ TrOff tr_t(int r0, int c0) { return tr(t, r0, c0); }
+  static __device__ __forceinline__ TrOff tr_k(int r0, int c0) { return tr(k, r0, c0); }
+  static __device__ __forceinline__ TrOff tr_m(int r0, int c0) { return tr(m, r0, c0); }
+  template <typename F>
+  static __device__ __forceinline__ TrOff tr(F f, int r0, int c0) {
+    const int r = r0 + ((lane_id() & 15) >> 2), c = c0 + 4 * (lane_id() & 3);
+    return {f(r, c), f(r + 4, c)};
+  }
+};
+
 // Forward state scan (bf16 inputs).  One workgroup per (sequence, head,
 // 32-wide dv slice); wave w owns rows 16w..16w+15 of the chunk products and
 // rows (dk/4)w.. of the state slice.  Every product is formed transposed (the
@@ -1356,8 +1377,8 @@ __global__ __launch_bounds__(NTHR) void k_prep_bf(
 // every later one maps zero to zero (a non-finite key in the skipped chunks
 // makes the segment's own final state non-finite).  65,536 tokens, H16 d128, P
 // = 8: 328 -> 17 us.  Gates without decay pay one ballot per chunk.
-template <int DK, int DV, int BV, bool OUT, bool STORE, bool PHI = false>
-__global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
+template <int DK, int DV, int BV, bool OUT, bool STORE, bool PHI, bool SW>
+__global__ __launch_bounds__(NTHR, SW ? 2 : 1) void k_scan_fwd_bf(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ beta, const bf16_t* __restrict__ beta_tilde,
     const float* __restrict__ d, const float* __restrict__ h0,
@@ -1374,8 +1395,12 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
   constexpr int NTV = BV / 16, XMT = DK / 64, KS = DK / 32, CC = CH * CH;
   constexpr int NB = DV / 32;
   // row-major BV-wide tiles: 72-byte rows put the four rows of a transposing
-  // read on disjoint banks
-  constexpr int LDT = BV + 4;
+  // read on disjoint banks; SW: unpadded (ScanTiles; dk = 128: 79,360 bytes, two
+  // workgroups a CU), see launch_scan_fwd for when
+  constexpr int LDT = SW ? BV : BV + 4;
+  static_assert(!SW || (BV == 32 && NTHR == 256), "pairs: 32-column slices");
+  using L = ScanTiles<SW, DK>;
+  auto tofs = [](int r, int c) { return SW ? sw32(r, c) : r * LDT + c; };
   static_assert(BV == 32 || (BV == 16 && !STORE), "stored states use one scale per 32-column block = one dv slice");
   static_assert(!PHI || (DV == DK && !OUT && !STORE), "the transition product is a dk x dk state");
   __shared__ __align__(16) bf16_t Xh[DK * LDT];
@@ -1389,8 +1414,9 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
   // the chunk's K rows, staged from the K operand registers: the state update
   // takes its K operand (reduction down the chunk rows) from here with
   // transposing reads
-  constexpr int LDKC = DK + 24;  // 304-byte rows: conflict-free transposing reads
-  __shared__ __align__(16) bf16_t Kc[CH * LDKC];
+  // (SW: the K operand comes from here too, and Q from a tile of its own)
+  __shared__ __align__(16) bf16_t Kc[CH * L::LDK];
+  __shared__ __align__(16) bf16_t Qc[SW && OUT ? CH * L::LDK : 8];
   __shared__ int live[NWAVE];  // PHI: whether a wave's part of the state is nonzero
 
   int s, h, zb;
@@ -1404,6 +1430,19 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
   const int prow = 16 * w + r16;            // chunk row of this lane
   const int xrow0 = (DK / 4) * w + r16;     // state rows of this lane: xrow0 + 16 mt
   const int col0 = 4 * g4;                  // columns of this lane: 16 nt + col0 .. +3
+  // this lane's offsets: its row prow, columns 16 nt + col0 ..; transposing
+  // reads at rows 8 g4 .. (+ 32 ks), columns 16 nt ..
+  int poff[NTV];
+  TrOff toff[NTV];
+#pragma unroll
+  for (int nt = 0; nt < NTV; ++nt) {
+    poff[nt] = tofs(prow, 16 * nt + col0);
+    if constexpr (SW) toff[nt] = L::tr_t(8 * g4, 16 * nt);
+  }
+  auto tr8 = [&](const bf16_t* tile, int ks, int nt) {
+    if constexpr (SW) return ld_tr8(tile + 32 * LDT * ks, toff[nt]);
+    else return ld_tr8(tile, LDT, 32 * ks + 8 * g4, 16 * nt);
+  };
 
   // state, accumulator layout of the transposed products: row xrow0 + 16 mt,
   // columns 16 nt + col0 .. +3 of the slice
@@ -1429,7 +1468,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
 #pragma unroll
       for (int nt = 0; nt < NTV; ++nt) {
         const float xv[4] = {X[mt][nt][0], X[mt][nt][1], X[mt][nt][2], X[mt][nt][3]};
-        put_t4(Xh, Xl, (xrow0 + 16 * mt) * LDT + 16 * nt + col0, xv);
+        put_t4(Xh, Xl, tofs(xrow0 + 16 * mt, 16 * nt + col0), xv);
       }
   };
   auto store_state = [&](float* dst) {
@@ -1452,8 +1491,11 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
       m = rowgroup_max(m);
       const float inv = q_inv_scale(m);
       const unsigned row = xrow0 + 16 * mt;
-      at(reinterpret_cast<uint4*>(dq), 2u * (row * BV + row8_col())) =
-          row8_from_pieces(q_pack4(X[mt][0], inv), q_pack4(X[mt][NTV - 1], inv));
+      const uint4 u = row8_from_pieces(q_pack4(X[mt][0], inv), q_pack4(X[mt][NTV - 1], inv));
+      if constexpr (SW)
+        at(reinterpret_cast<uint4*>(dq), 2u * (((DK / 4) * w + 16 * mt) * BV + 8 * lane)) = row8_to_memory(u);
+      else
+        at(reinterpret_cast<uint4*>(dq), 2u * (row * BV + row8_col())) = u;
       if (g4 == mt) sc = q_scale(m);
     }
     if (g4 < XMT) at(ds, 4u * (xrow0 + 16 * g4)) = sc;
@@ -1472,13 +1514,15 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
   // (M R)[r] = s_r sum_i q[r][i] R[i]) and A's column scale (applied to the
   // rows of D before A D: (A D)[r] = sum_c q[r][c] (s_c D[c]))
   bf16x8 kf[KS], qf[KS];
+  TileRegs<bf16_t, CH, DK> kr, qr;  // SW: whole rows; rows past the chunk end read as zero
   uint4 mq[2], aq[2];
   float msc, asc;
   // per-row values of the chunk (cumulative gates G, beta, beta~, the V slice)
   // are loaded one chunk ahead into registers and staged through a
   // double-buffered LDS area at the end of each chunk
   __shared__ float Grow[2][CH], Brow[2][CH], BTrow[2][CH];
-  __shared__ __align__(16) bf16_t Vrow[2][CH * (BV + 8)];
+  constexpr int LDV = SW ? BV : BV + 8;
+  __shared__ __align__(16) bf16_t Vrow[SW ? 1 : 2][CH * LDV];
   constexpr int VPR = BV / 8;                  // 16-byte pieces per V row
   const int vr = threadIdx.x / VPR, vc = (threadIdx.x % VPR) * 8;
   const int vr_ld = min(vr, CH - 1);
@@ -1486,6 +1530,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
   bf16_t pbv = 0, pbtv = 0;
   uint4 pvv = make_uint4(0, 0, 0, 0);
   int plen = 0;
+  const int ws = wave_id_s();
   auto load_rows = [&](int cc) {
     plen = c_len(cc);
     const long tok = c_tok(cc), chh = c_chh(cc);
@@ -1493,8 +1538,13 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
     // chunk bases are wave-uniform (scalar registers), lane offsets 32-bit
     const unsigned tr = 2u * ((unsigned)min(t, plen - 1) * H);
     pgv = at(Gw + chh * CH, 4u * t);
-    pbv = at(beta + tok, tr);
-    pbtv = at(beta_tilde + tok, tr);
+    if constexpr (SW) {
+      // strided rows: one request per lane, so one wave each
+      if (ws < 2) pbv = at((ws == 0 ? beta : beta_tilde) + tok, tr);
+    } else {
+      pbv = at(beta + tok, tr);
+      pbtv = at(beta_tilde + tok, tr);
+    }
     if constexpr (!PHI)
       pvv = at(reinterpret_cast<const uint4*>(v + tok * DV + j0),
                2u * ((unsigned)min(vr_ld, plen - 1) * (H * DV) + vc));
@@ -1503,21 +1553,40 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
     const int t = threadIdx.x & (CH - 1);
     Grow[buf][t] = pgv;
     // no value term in the transition product
-    Brow[buf][t] = !PHI && t < plen ? bf2f(pbv) : 0.f;
-    BTrow[buf][t] = t < plen ? bf2f(pbtv) : 0.f;
-    if (CH * VPR >= NTHR || threadIdx.x < CH * VPR)
-      *reinterpret_cast<uint4*>(&Vrow[buf][vr * (BV + 8) + vc]) =
-          vr < plen ? pvv : make_uint4(0, 0, 0, 0);
+    if (!SW || ws == 0) Brow[buf][t] = !PHI && t < plen ? bf2f(pbv) : 0.f;
+    if (!SW || ws == 1) BTrow[buf][t] = t < plen ? bf2f(SW ? pbv : pbtv) : 0.f;
+    const uint4 vv = vr < plen ? pvv : make_uint4(0, 0, 0, 0);
+    if constexpr (SW) {
+      *reinterpret_cast<uint2*>(&Vrow[0][sw32(vr, vc)]) = make_uint2(vv.x, vv.y);
+      *reinterpret_cast<uint2*>(&Vrow[0][sw32(vr, vc + 4)]) = make_uint2(vv.z, vv.w);
+    } else if (CH * VPR >= NTHR || threadIdx.x < CH * VPR) {
+      *reinterpret_cast<uint4*>(&Vrow[buf][vr * LDV + vc]) = vv;
+    }
   };
   // rows past the chunk end load a valid row; their K X / Q X results are
   // never used (beta = beta~ = 0 zeroes R there and such outputs are not stored)
   auto load_kq = [&](int cc) {
+    if constexpr (SW) {
+      kr.load_clip(k + c_tok(cc) * DK, (long)H * DK, c_len(cc));
+      if constexpr (OUT) qr.load_clip(q + c_tok(cc) * DK, (long)H * DK, c_len(cc));
+      return;
+    }
     const long tb = c_tok(cc) * DK;
     const unsigned rb = 2u * ((unsigned)min(prow, c_len(cc) - 1) * (H * DK) + 8 * g4);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       kf[ks] = at(reinterpret_cast<const bf16x8*>(k + tb), rb + 64u * ks);
       if constexpr (OUT) qf[ks] = at(reinterpret_cast<const bf16x8*>(q + tb), rb + 64u * ks);
+    }
+  };
+  auto put_kq = [&]() {
+    if constexpr (SW) {
+#pragma unroll
+      for (int it = 0; it < TileRegs<bf16_t, CH, DK>::ITER; ++it) {
+        const int idx = threadIdx.x + it * NTHR, off = L::k(idx / (DK / 8), (idx % (DK / 8)) * 8);
+        *reinterpret_cast<uint4*>(Kc + off) = kr.r[it];
+        if constexpr (OUT) *reinterpret_cast<uint4*>(Qc + off) = qr.r[it];
+      }
     }
   };
   const unsigned foff = 16u * (2 * w * 64 + lane);  // this lane's fragment (fragment order)
@@ -1539,6 +1608,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
     if constexpr (OUT) load_a(0);
     load_rows(0);
     put_rows(0);
+    put_kq();
   }
   __syncthreads();
 
@@ -1562,11 +1632,15 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
       qx[nt] = zero4();
     }
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
+    for (int ks = 0; ks < KS; ++ks) {
+      if constexpr (SW) {
+        kf[ks] = ld8(Kc + L::k(prow, 32 * ks + 8 * g4));
+        if constexpr (OUT) qf[ks] = ld8(Qc + L::k(prow, 32 * ks + 8 * g4));
+      }
 #pragma unroll
       for (int nt = 0; nt < NTV; ++nt) {
-        const bf16x8 xh = ld_tr8(Xh, LDT, 32 * ks + 8 * g4, 16 * nt);
-        const bf16x8 xl = ld_tr8(Xl, LDT, 32 * ks + 8 * g4, 16 * nt);
+        const bf16x8 xh = tr8(Xh, ks, nt);
+        const bf16x8 xl = tr8(Xl, ks, nt);
         kx[nt] = mfma16(xh, kf[ks], kx[nt]);
         kx[nt] = mfma16(xl, kf[ks], kx[nt]);
         if constexpr (OUT) {
@@ -1574,6 +1648,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
           qx[nt] = mfma16(xl, qf[ks], qx[nt]);
         }
       }
+    }
     // the state entering this chunk, stored while the products above run
     // (stores bunched before a barrier stall all four waves at once)
     if constexpr (STORE) {
@@ -1581,15 +1656,17 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
       store_state_q(Xq + xb * BV, Xs + xb);
     }
     // K rows past the chunk end repeat row len - 1; D is zero there
+    if constexpr (!SW) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) *reinterpret_cast<bf16x8*>(Kc + prow * LDKC + 32 * ks + 8 * g4) = kf[ks];
+      for (int ks = 0; ks < KS; ++ks) *reinterpret_cast<bf16x8*>(Kc + L::k(prow, 32 * ks + 8 * g4)) = kf[ks];
+    }
     load_kq(nx);
     floatx4 oacc[NTV];
     {
       const float btegm = bt * __expf(gm), eg = __expf(gg);
 #pragma unroll
       for (int nt = 0; nt < NTV; ++nt) {
-        const uint2 v4 = *reinterpret_cast<const uint2*>(&Vrow[buf][prow * (BV + 8) + 16 * nt + col0]);
+        const uint2 v4 = *reinterpret_cast<const uint2*>(&Vrow[SW ? 0 : buf][SW ? poff[nt] : prow * LDV + 16 * nt + col0]);
         const float vv[4] = {__uint_as_float(v4.x << 16), __uint_as_float(v4.x & 0xFFFF0000u),
                              __uint_as_float(v4.y << 16), __uint_as_float(v4.y & 0xFFFF0000u)};
         float rv[4];
@@ -1598,7 +1675,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
           rv[e] = bb * vv[e] - btegm * kx[nt][e];
           if constexpr (OUT) oacc[nt][e] = eg * (qx[nt][e] - dh * kx[nt][e]);
         }
-        put_t4(Rh, Rl, prow * LDT + 16 * nt + col0, rv);
+        put_t4(Rh, Rl, poff[nt], rv);
       }
     }
     __syncthreads();
@@ -1613,8 +1690,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
       q_split8(mq[ks], mh, ml);
 #pragma unroll
       for (int nt = 0; nt < NTV; ++nt) {
-        const bf16x8 rh = ld_tr8(Rh, LDT, 32 * ks + 8 * g4, 16 * nt);
-        const bf16x8 rl = ld_tr8(Rl, LDT, 32 * ks + 8 * g4, 16 * nt);
+        const bf16x8 rh = tr8(Rh, ks, nt);
+        const bf16x8 rl = tr8(Rl, ks, nt);
         dl[nt] = mfma16(rh, mh, dl[nt]);
         dl[nt] = mfma16(rl, mh, dl[nt]);
         dl[nt] = mfma16(rh, ml, dl[nt]);
@@ -1622,6 +1699,15 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
     }
     const float ms_cur = msc;
     load_m(nx);
+    bf16x8 ktf[2][XMT];  // K at state rows (dk/4) w + 16 mt + r16, chunk rows 32 ks + 8 g4 ..
+    auto get_kt = [&]() {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int mt = 0; mt < XMT; ++mt)
+          ktf[ks][mt] = ld_tr8(Kc + 32 * L::LDK * ks, L::tr_k(8 * g4, (DK / 4) * w + 16 * mt));
+    };
+    if constexpr (SW) get_kt();  // the next chunk's rows replace the tile after the next barrier
 #pragma unroll
     for (int nt = 0; nt < NTV; ++nt) dl[nt] *= ms_cur;
     // D rows as int16 with one scale per row of the slice, stored after the
@@ -1640,7 +1726,7 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
       for (int nt = 0; nt < NTV; ++nt) {
         const float dv[4] = {dl[nt][0], dl[nt][1], dl[nt][2], dl[nt][3]};
         const float dgv[4] = {edec * dv[0], edec * dv[1], edec * dv[2], edec * dv[3]};
-        const int off = prow * LDT + 16 * nt + col0;
+        const int off = poff[nt];
         put_t4(Dgh, Dgl, off, dgv);
         if constexpr (OUT) {
           // times A's column scale for column prow (a power of two: exact)
@@ -1659,24 +1745,28 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
       for (int nt = 0; nt < NTV; ++nt) X[mt][nt] *= gC;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-      // K fragments for state rows (dk/4) w + 16 mt + r16, chunk rows 32 ks + 8 g4 ..
-      bf16x8 ktf[XMT];
+      if constexpr (!SW) {
 #pragma unroll
-      for (int mt = 0; mt < XMT; ++mt) ktf[mt] = ld_tr8(Kc, LDKC, 32 * ks + 8 * g4, (DK / 4) * w + 16 * mt);
+        for (int mt = 0; mt < XMT; ++mt)
+          ktf[ks][mt] = ld_tr8(Kc, L::LDK, 32 * ks + 8 * g4, (DK / 4) * w + 16 * mt);
+      }
 #pragma unroll
       for (int nt = 0; nt < NTV; ++nt) {
-        const bf16x8 dgh = ld_tr8(Dgh, LDT, 32 * ks + 8 * g4, 16 * nt);
-        const bf16x8 dgl = ld_tr8(Dgl, LDT, 32 * ks + 8 * g4, 16 * nt);
+        const bf16x8 dgh = tr8(Dgh, ks, nt);
+        const bf16x8 dgl = tr8(Dgl, ks, nt);
 #pragma unroll
         for (int mt = 0; mt < XMT; ++mt) {
-          X[mt][nt] = mfma16(dgh, ktf[mt], X[mt][nt]);
-          X[mt][nt] = mfma16(dgl, ktf[mt], X[mt][nt]);
+          X[mt][nt] = mfma16(dgh, ktf[ks][mt], X[mt][nt]);
+          X[mt][nt] = mfma16(dgl, ktf[ks][mt], X[mt][nt]);
         }
       }
     }
     if constexpr (STORE) {
       const long blk = (chh * NB + zb) * CH;  // the slice's block
-      at(reinterpret_cast<uint4*>(Dq + blk * BV), 2u * (prow * BV + row8_col())) = dpk;
+      if constexpr (SW)
+        at(reinterpret_cast<uint4*>(Dq + blk * BV), 2u * (16 * w * BV + 8 * lane)) = row8_to_memory(dpk);
+      else
+        at(reinterpret_cast<uint4*>(Dq + blk * BV), 2u * (prow * BV + row8_col())) = dpk;
       if (g4 == 0) at(Ds + blk, 4u * prow) = dsc;
     }
 
@@ -1691,8 +1781,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
         q_split8(aq[ks], ah, al);
 #pragma unroll
         for (int nt = 0; nt < NTV; ++nt) {
-          const bf16x8 dh_ = ld_tr8(Dh, LDT, 32 * ks + 8 * g4, 16 * nt);
-          const bf16x8 dl_ = ld_tr8(Dl, LDT, 32 * ks + 8 * g4, 16 * nt);
+          const bf16x8 dh_ = tr8(Dh, ks, nt);
+          const bf16x8 dl_ = tr8(Dl, ks, nt);
           adc[nt] = mfma16(dh_, ah, adc[nt]);
           adc[nt] = mfma16(dl_, ah, adc[nt]);
           adc[nt] = mfma16(dh_, al, adc[nt]);
@@ -1706,10 +1796,15 @@ __global__ __launch_bounds__(NTHR, 1) void k_scan_fwd_bf(
         floatx4 ov;
 #pragma unroll
         for (int e = 0; e < 4; ++e) ov[e] = oacc[nt][e] + adc[nt][e];
-        store_clip4(ov, ro, 4u * ((unsigned)prow * (H * DV) + 16 * nt + col0));
+        if constexpr (SW)
+          store_clip4(piece_to_memory(ov), ro,
+                      4u * ((unsigned)(16 * w + (lane >> 2)) * (H * DV) + 16 * nt + 4 * (lane & 3)));
+        else
+          store_clip4(ov, ro, 4u * ((unsigned)prow * (H * DV) + 16 * nt + col0));
       }
     }
     put_state();
+    put_kq();
     put_rows(buf ^ 1);
     if constexpr (PHI) {
       bool nz = false;  // (NaN counts as nonzero)
@@ -1824,27 +1919,6 @@ __global__ __launch_bounds__(seg_combine_threads<DK>()) void k_seg_combine(
   }
 }
 
-// LDS tiles of a scan: 32-column tiles (t), the chunk's K rows (k) and 64 x 64
-// M / A tiles (m), unpadded with exchanged pieces (sw32, sw16) or with padded
-// rows (72, 2 dk + 48 and 144 bytes: the four rows of a transposing read on
-// disjoint banks).
-template <bool SW, int DK>
-struct ScanTiles {
-  static constexpr int LDT = SW ? 32 : 36, LDK = SW ? DK : DK + 24, LDM = SW ? CH : CH + 8;
-  static __device__ __forceinline__ int t(int r, int c) { return SW ? sw32(r, c) : r * LDT + c; }
-  static __device__ __forceinline__ int k(int r, int c) { return SW ? sw16<DK>(r, c) : r * LDK + c; }
-  static __device__ __forceinline__ int m(int r, int c) { return SW ? sw16<CH>(r, c) : r * LDM + c; }
-  // ld_tr8 offsets at rows r0 .., columns c0 .. (see TrOff)
-  static __device__ __forceinline__ TrOff tr_t(int r0, int c0) { return tr(t, r0, c0); }
-  static __device__ __forceinline__ TrOff tr_k(int r0, int c0) { return tr(k, r0, c0); }
-  static __device__ __forceinline__ TrOff tr_m(int r0, int c0) { return tr(m, r0, c0); }
-  template <typename F>
-  static __device__ __forceinline__ TrOff tr(F f, int r0, int c0) {
-    const int r = r0 + ((lane_id() & 15) >> 2), c = c0 + 4 * (lane_id() & 3);
-    return {f(r, c), f(r + 4, c)};
-  }
-};
-
 // Reverse state scan (bf16 inputs): Y = gradient of the state leaving the chunk.
 // As in the forward scan, every product is formed transposed, so that a lane
 // holds one row and four consecutive columns; the intermediate tiles (Y, dO,
@@ -1867,7 +1941,7 @@ __global__ __launch_bounds__(NTHR, SW ? 2 : 1) void k_scan_bwd_bf(
   constexpr int NTV = BV / 16, XMT = DK / 64, KS = DK / 32, CC = CH * CH;
   constexpr int NB = DV / 32;
   // SW: unpadded tiles (dk = 128: 78,848 bytes), so that two workgroups fit a
-  // CU; see scan_bwd_pairs for when
+  // CU; see launch_scan_bwd for when
   using L = ScanTiles<SW, DK>;
   constexpr int LDT = L::LDT, LDK = L::LDK, LDM = L::LDM;
   static_assert(BV == 32, "stored states use one scale per 32-column block = one dv slice");
@@ -3401,6 +3475,49 @@ static hipError_t run_bwd_f32(const LaunchArgs& a) {
   return hipGetLastError();
 }
 
+// The scans' chains: one workgroup per (row, head, 32-column slice).
+static long scan_chains(int N, int H, int dv) { return (long)N * H * (dv / SCAN_BV); }
+
+// The forward scan over N rows of H heads (arguments after st: the kernel's).
+// The SW form moves K, Q, the outputs and the saved states as whole rows (a
+// quarter of the requests at the address unit, for more LDS traffic, latency and
+// cross-lane moves).  That pays once each CU runs several workgroups all the
+// time and their requests queue: 1,024 tokens, H16, 512 / 1,024 chains: d128
+// 69.2 / 149.7 -> 70.5 / 140.9 us, storing 102.0 / 196.4 -> 94.7 / 180.1; d64
+// 52.8 / 130.8 -> 55.8 / 122.6; a packed batch of 512K tokens, 1,024 unequal
+// chains, 5446 -> 4894; but 320 unequal chains, storing, 184 -> 218, and 65,536
+// tokens in 512 chains no different.  The state passes (no outputs) lose
+// (350 -> 361), dk = 256 does not fit a CU twice.
+template <int DK, int DV, int BV, bool OUT, bool STORE, bool PHI, typename... Args>
+static void launch_scan_fwd(int N, int H, hipStream_t st, Args... args) {
+  const unsigned grid = scan_blocks(N, H, DV / BV);
+  if constexpr (DK <= 128 && BV == SCAN_BV && OUT) {
+    if (scan_chains(N, H, DV) >= 3L * device_cus()) {
+      k_scan_fwd_bf<DK, DV, BV, OUT, STORE, PHI, true><<<grid, NTHR, 0, st>>>(args...);
+      return;
+    }
+  }
+  k_scan_fwd_bf<DK, DV, BV, OUT, STORE, PHI, false><<<grid, NTHR, 0, st>>>(args...);
+}
+
+// The reverse scan over N rows of H heads (arguments after st: the kernel's).
+// Its workgroups fit a CU in pairs with unpadded LDS tiles (SW, dk <= 128): taken
+// when there are more chains than CUs.  65,536 tokens, H16 d128, 512 chains:
+// 721 -> 586 us, its state pass 742 -> 544 us.  With fewer chains no pair forms
+// and the padded tiles' simpler addresses are 2-5% faster; at dk = 256 no pair
+// fits either way.
+template <int DK, int DV, bool STORE, typename... Args>
+static void launch_scan_bwd(int N, int H, hipStream_t st, Args... args) {
+  const unsigned grid = scan_blocks(N, H, DV / SCAN_BV);
+  if constexpr (DK <= 128) {
+    if (scan_chains(N, H, DV) > device_cus()) {
+      k_scan_bwd_bf<DK, DV, SCAN_BV, STORE, true><<<grid, NTHR, 0, st>>>(args...);
+      return;
+    }
+  }
+  k_scan_bwd_bf<DK, DV, SCAN_BV, STORE, false><<<grid, NTHR, 0, st>>>(args...);
+}
+
 template <int DK, int DV, bool BWD>
 static void launch_seg_combine(const LaunchArgs& a, const float* phi, const float* F, const float* s0, float* X0) {
   k_seg_combine<DK, DV, BWD><<<a.N * a.H * (DV / SEG_SL), seg_combine_threads<DK>(), 0, a.stream>>>(
@@ -3422,11 +3539,11 @@ static void seg_forward_states(const LaunchArgs& a, const bf16_t* q, const bf16_
   const int P = a.segP, Nst = a.N * (P - 1);
   const int Nphi = phi_all ? a.N * P : Nst, gphi = phi_all ? 0 : P;
   a.stage("scan_seg_state");
-  k_scan_fwd_bf<DK, DV, SCAN_BV, false, false><<<scan_blocks(Nst, a.H, DV / SCAN_BV), NTHR, 0, st>>>(
+  launch_scan_fwd<DK, DV, SCAN_BV, false, false, false>(Nst, a.H, st,
       q, k, v, beta, bt, a.d, nullptr, vsm, nullptr, Nst, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw,
       nullptr, a.segF, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, P);
   a.stage("scan_seg_phi");
-  k_scan_fwd_bf<DK, DK, SCAN_BV, false, false, true><<<scan_blocks(Nphi, a.H, DK / SCAN_BV), NTHR, 0, st>>>(
+  launch_scan_fwd<DK, DK, SCAN_BV, false, false, true>(Nphi, a.H, st,
       q, k, v, beta, bt, a.d, nullptr, vsm, nullptr, Nphi, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw,
       nullptr, a.segPhi, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, gphi);
   a.stage("seg_combine");
@@ -3440,26 +3557,6 @@ static hipError_t seg_copy_rows(const LaunchArgs& a, float* dst, const float* sr
   const size_t st_bytes = (size_t)a.H * DK * DV * sizeof(float);
   return hipMemcpy2DAsync(dst, st_bytes, src + (size_t)p * a.H * DK * DV, a.segP * st_bytes,
                           st_bytes, a.N, hipMemcpyDeviceToDevice, a.stream);
-}
-
-// Whether the reverse scan's workgroups should fit a CU in pairs (unpadded LDS
-// tiles, dk <= 128): when there are more chains than CUs.  65,536 tokens, H16
-// d128, 512 chains: 721 -> 586 us, its state pass 742 -> 544 us.  With fewer
-// chains no pair forms and the padded tiles' simpler addresses are 2-5% faster;
-// at dk = 256 no pair fits either way.
-static bool scan_bwd_pairs(int N, int H, int dv) { return (long)N * H * (dv / SCAN_BV) > device_cus(); }
-
-// The reverse scan over N rows of H heads (arguments after st: the kernel's).
-template <int DK, int DV, bool STORE, typename... Args>
-static void launch_scan_bwd(int N, int H, hipStream_t st, Args... args) {
-  const unsigned grid = scan_blocks(N, H, DV / SCAN_BV);
-  if constexpr (DK <= 128) {
-    if (scan_bwd_pairs(N, H, DV)) {
-      k_scan_bwd_bf<DK, DV, SCAN_BV, STORE, true><<<grid, NTHR, 0, st>>>(args...);
-      return;
-    }
-  }
-  k_scan_bwd_bf<DK, DV, SCAN_BV, STORE, false><<<grid, NTHR, 0, st>>>(args...);
 }
 
 // Whether the stateless forward scan takes 16-column slices: when these are at
@@ -3517,11 +3614,11 @@ static hipError_t run_fwd_bf(const LaunchArgs& a) {
     a.stage(a.saved ? "scan_fwd_save" : "scan_fwd");
     float* htv = a.ht ? a.segHT : nullptr;
     if (a.saved)
-      k_scan_fwd_bf<DK, DV, SCAN_BV, true, true><<<scan_blocks(Np, a.H, DV / SCAN_BV), NTHR, 0, st>>>(
+      launch_scan_fwd<DK, DV, SCAN_BV, true, true, false>(Np, a.H, st,
           q, k, v, beta, bt, a.d, a.segX0, vsm, nullptr, Np, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As,
           a.Gw, a.o, htv, a.Xq, a.Xs, a.Dq, a.Ds, nullptr, nullptr);
     else
-      k_scan_fwd_bf<DK, DV, SCAN_BV, true, false><<<scan_blocks(Np, a.H, DV / SCAN_BV), NTHR, 0, st>>>(
+      launch_scan_fwd<DK, DV, SCAN_BV, true, false, false>(Np, a.H, st,
           q, k, v, beta, bt, a.d, a.segX0, vsm, nullptr, Np, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As,
           a.Gw, a.o, htv, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
     // the final state of each row is that of its last segment
@@ -3532,15 +3629,15 @@ static hipError_t run_fwd_bf(const LaunchArgs& a) {
   }
   a.stage(a.saved ? "scan_fwd_save" : "scan_fwd");
   if (a.saved)
-    k_scan_fwd_bf<DK, DV, SCAN_BV, true, true><<<scan_blocks(a.N, a.H, DV / SCAN_BV), NTHR, 0, st>>>(
+    launch_scan_fwd<DK, DV, SCAN_BV, true, true, false>(a.N, a.H, st,
         q, k, v, beta, bt, a.d, a.h0, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw, a.o, a.ht, a.Xq, a.Xs,
         a.Dq, a.Ds, a.Xfq, a.Xfs);
   else if (narrow_slices(a))
-    k_scan_fwd_bf<DK, DV, 16, true, false><<<scan_blocks(a.N, a.H, DV / 16), NTHR, 0, st>>>(
+    launch_scan_fwd<DK, DV, 16, true, false, false>(a.N, a.H, st,
         q, k, v, beta, bt, a.d, a.h0, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw, a.o, a.ht, nullptr,
         nullptr, nullptr, nullptr, nullptr, nullptr);
   else
-    k_scan_fwd_bf<DK, DV, SCAN_BV, true, false><<<scan_blocks(a.N, a.H, DV / SCAN_BV), NTHR, 0, st>>>(
+    launch_scan_fwd<DK, DV, SCAN_BV, true, false, false>(a.N, a.H, st,
         q, k, v, beta, bt, a.d, a.h0, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw, a.o, a.ht, nullptr,
         nullptr, nullptr, nullptr, nullptr, nullptr);
   a.stage(nullptr);
@@ -3607,7 +3704,7 @@ static hipError_t run_bwd_bf(const LaunchArgs& a) {
             q, k, a.g, bt, a.d, a.cmap, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp, a.Gw);
       seg_forward_states<DK, DV>(a, q, k, v, beta, bt, true, vsm, Tp);
       a.stage("scan_fwd_store");
-      k_scan_fwd_bf<DK, DV, SCAN_BV, false, true><<<scan_blocks(Np, a.H, DV / SCAN_BV), NTHR, 0, st>>>(
+      launch_scan_fwd<DK, DV, SCAN_BV, false, true, false>(Np, a.H, st,
           q, k, v, beta, bt, a.d, a.segX0, vsm, nullptr, Np, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As,
           a.Gw, nullptr, nullptr, a.Xq, a.Xs, a.Dq, a.Ds, nullptr, nullptr);
     }
@@ -3637,7 +3734,7 @@ static hipError_t run_bwd_bf(const LaunchArgs& a) {
     side(
         st,
         [&](hipStream_t s1) {
-          k_scan_fwd_bf<DK, DV, SCAN_BV, false, true><<<scan_blocks(a.N, a.H, DV / SCAN_BV), NTHR, 0, s1>>>(
+          launch_scan_fwd<DK, DV, SCAN_BV, false, true, false>(a.N, a.H, s1,
               q, k, v, beta, bt, a.d, a.h0, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw, nullptr,
               nullptr, a.Xq, a.Xs, a.Dq, a.Ds, a.Xfq, a.Xfs);
         },

@@ -1,0 +1,46 @@
+"""The scans' forms (LDS layout, operand loads, slice width) against each other.
+
+Which form runs depends on the chains per CU, so the same row is computed alone
+(few chains) and inside batches that pass each rule (320 to 1,024 chains of 32
+columns on 256 CUs): its outputs, final state and gradients must be bit for bit
+the same, since no form changes a row's arithmetic.  Ragged last chunks and
+both sides' head sizes."""
+import pytest
+
+from comba_inputs import random_case
+from gpu_helpers import to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B", [20, 33, 64])
+@pytest.mark.parametrize("dk,dv,T", [(128, 128, 130), (64, 64, 65), (64, 128, 63), (128, 64, 200),
+                                     (128, 256, 70)])
+def test_a_row_does_not_depend_on_its_batch(B, dk, dv, T):
+    import torch
+
+    import paper_2506_02475_amd as comba
+
+    H = 4 * 128 // dv  # 16 chains of 32 columns per row
+    print("case B%d H%d dk%d dv%d T%d" % (B, H, dk, dv, T), flush=True)
+    w = random_case(B=B, T=T, H=H, dk=dk, dv=dv, in_dtype="bf16", seed=83, dht=True)
+    a = to_device(w)
+    names = ("q", "k", "v", "g", "beta")
+
+    def calls(x, h0, dO, dht):
+        args = tuple(x[n] for n in names) + (a["d"], h0)
+        o, ht = comba.comba_chunk_fwd(*args)
+        o_s, ht_s, ws = comba.comba_chunk_fwd_save(*args)
+        gr = comba.comba_chunk_bwd_saved(*args, dO, dht, workspace=ws)
+        assert torch.equal(o, o_s) and torch.equal(ht, ht_s)
+        return o, ht, gr
+
+    o, ht, gr = calls(a, a["h0"], a["dO"], a["dht"])
+    for b in (0, B - 1):
+        one = {n: a[n][b:b + 1].contiguous() for n in names}
+        o1, ht1, gr1 = calls(one, a["h0"][b:b + 1].contiguous(), a["dO"][b:b + 1].contiguous(),
+                             a["dht"][b:b + 1].contiguous())
+        torch.cuda.synchronize()
+        assert torch.equal(o1[0], o[b]) and torch.equal(ht1[0], ht[b])
+        for n in ("dq", "dk", "dv", "dg", "dbeta", "dh0"):
+            assert torch.equal(gr1[n][0], gr[n][b]), n

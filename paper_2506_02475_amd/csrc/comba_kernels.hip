@@ -3501,15 +3501,16 @@ static void launch_scan_fwd(int N, int H, hipStream_t st, Args... args) {
 }
 
 // The reverse scan over N rows of H heads (arguments after st: the kernel's).
-// Its workgroups fit a CU in pairs with unpadded LDS tiles (SW, dk <= 128): taken
-// when there are more chains than CUs.  65,536 tokens, H16 d128, 512 chains:
-// 721 -> 586 us, its state pass 742 -> 544 us.  With fewer chains no pair forms
-// and the padded tiles' simpler addresses are 2-5% faster; at dk = 256 no pair
-// fits either way.
+// dk = 128 fits a CU twice only with the unpadded tiles (SW): taken where there
+// are more chains than CUs (1,024 tokens, H16, 320 / 512 / 1,024 chains: 94.2 /
+// 97.4 / 186.9 -> 73.1 / 82.2 / 153.7 us; 65,536 tokens, 512 chains: 721 -> 586,
+// its state pass 742 -> 544; 256 chains 54.3 against 55.2).  dk = 64 fits twice
+// with padded tiles, whose addresses are simpler (4,096 tokens, 512 chains:
+// 242.4 us against 246.1 with the unpadded ones); dk = 256 fits once either way.
 template <int DK, int DV, bool STORE, typename... Args>
 static void launch_scan_bwd(int N, int H, hipStream_t st, Args... args) {
   const unsigned grid = scan_blocks(N, H, DV / SCAN_BV);
-  if constexpr (DK <= 128) {
+  if constexpr (DK == 128) {
     if (scan_chains(N, H, DV) > device_cus()) {
       k_scan_bwd_bf<DK, DV, SCAN_BV, STORE, true><<<grid, NTHR, 0, st>>>(args...);
       return;

@@ -21,7 +21,8 @@ size_t round_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct Dims {
   bool bf16, packed;
   int dk, dv, H, N, Tseq, Ttot, ncmax;
-  int maxch;  // chunks of the longest sequence (packed: 0 without the host offsets)
+  int maxch;      // chunks of the longest sequence (packed: 0 without the host offsets)
+  int64_t totch;  // chunks of all sequences (packed: 0 without the host offsets)
 };
 
 // Validates the shape; fills dims on success.  `wide` also admits head dim 256
@@ -48,6 +49,7 @@ comba_status check_shape(const comba_shape* s, Dims* out, bool wide = false) {
     d.N = s->num_seqs;
     d.Tseq = 0;
     d.maxch = 0;
+    d.totch = 0;
     if (s->cu_seqlens_host) {
       // the host copy of the offsets: 0 = cu[0] <= cu[1] <= ... <= cu[N] = T
       const int32_t* cu = s->cu_seqlens_host;
@@ -56,6 +58,7 @@ comba_status check_shape(const comba_shape* s, Dims* out, bool wide = false) {
         if (cu[i + 1] < cu[i]) return COMBA_ERR_SHAPE;
         const int nch = (cu[i + 1] - cu[i] + kChunk - 1) / kChunk;
         if (nch > d.maxch) d.maxch = nch;
+        d.totch += nch;
       }
     }
   } else {
@@ -64,6 +67,7 @@ comba_status check_shape(const comba_shape* s, Dims* out, bool wide = false) {
     d.N = s->B;
     d.Tseq = s->T;
     d.maxch = (s->T + kChunk - 1) / kChunk;
+    d.totch = (int64_t)d.N * d.maxch;
   }
   const int64_t ttot = s->cu_seqlens ? (int64_t)s->T : (int64_t)s->B * s->T;
   if (ttot > INT32_MAX / 2) return COMBA_ERR_SHAPE;
@@ -315,6 +319,8 @@ void fill_common(comba::LaunchArgs& a, const Dims& d, const comba_shape* s) {
   a.Tseq = d.Tseq;
   a.Ttot = d.Ttot;
   a.ncmax = d.ncmax;
+  a.chunks = (long)d.totch;
+  a.longest = d.maxch;
   a.cu_seqlens = s->cu_seqlens;
 }
 

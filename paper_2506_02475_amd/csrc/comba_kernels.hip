@@ -37,6 +37,7 @@
 
 #include "comba_device.hpp"
 #include "comba_launch.h"
+#include "comba_rules.h"
 
 namespace comba {
 
@@ -1396,7 +1397,7 @@ __global__ __launch_bounds__(NTHR, SW ? 2 : 1) void k_scan_fwd_bf(
   constexpr int NB = DV / 32;
   // row-major BV-wide tiles: 72-byte rows put the four rows of a transposing
   // read on disjoint banks; SW: unpadded (ScanTiles; dk = 128: 79,360 bytes, two
-  // workgroups a CU), see launch_scan_fwd for when
+  // workgroups a CU), see scan_fwd_whole_rows for when
   constexpr int LDT = SW ? BV : BV + 4;
   static_assert(!SW || (BV == 32 && NTHR == 256), "pairs: 32-column slices");
   using L = ScanTiles<SW, DK>;
@@ -1941,7 +1942,7 @@ __global__ __launch_bounds__(NTHR, SW ? 2 : 1) void k_scan_bwd_bf(
   constexpr int NTV = BV / 16, XMT = DK / 64, KS = DK / 32, CC = CH * CH;
   constexpr int NB = DV / 32;
   // SW: unpadded tiles (dk = 128: 78,848 bytes), so that two workgroups fit a
-  // CU; see launch_scan_bwd for when
+  // CU; see scan_bwd_unpadded for when
   using L = ScanTiles<SW, DK>;
   constexpr int LDT = L::LDT, LDK = L::LDK, LDM = L::LDM;
   static_assert(BV == 32, "stored states use one scale per 32-column block = one dv slice");
@@ -3475,24 +3476,21 @@ static hipError_t run_bwd_f32(const LaunchArgs& a) {
   return hipGetLastError();
 }
 
-// The scans' chains: one workgroup per (row, head, 32-column slice).
-static long scan_chains(int N, int H, int dv) { return (long)N * H * (dv / SCAN_BV); }
+// The rows of a scan over n rows: the sequences, or (segP > 1) their segments,
+// of which a state pass takes all but one per sequence.
+static ScanRows scan_rows(const LaunchArgs& a, int n) {
+  const long P = a.segP > 1 ? a.segP : 1, all = (long)a.N * P;
+  if (all <= 0) return ScanRows{0, 0, 0, 0};
+  return ScanRows{n, a.Ttot * (long)n / all, a.chunks * n / all, (a.longest + P - 1) / P};
+}
 
 // The forward scan over N rows of H heads (arguments after st: the kernel's).
-// The SW form moves K, Q, the outputs and the saved states as whole rows (a
-// quarter of the requests at the address unit, for more LDS traffic, latency and
-// cross-lane moves).  That pays once each CU runs several workgroups all the
-// time and their requests queue: 1,024 tokens, H16, 512 / 1,024 chains: d128
-// 69.2 / 149.7 -> 70.5 / 140.9 us, storing 102.0 / 196.4 -> 94.7 / 180.1; d64
-// 52.8 / 130.8 -> 55.8 / 122.6; a packed batch of 512K tokens, 1,024 unequal
-// chains, 5446 -> 4894; but 320 unequal chains, storing, 184 -> 218, and 65,536
-// tokens in 512 chains no different.  The state passes (no outputs) lose
-// (350 -> 361), dk = 256 does not fit a CU twice.
+// The state passes (no outputs) lose with whole rows (350 -> 361 us).
 template <int DK, int DV, int BV, bool OUT, bool STORE, bool PHI, typename... Args>
-static void launch_scan_fwd(int N, int H, hipStream_t st, Args... args) {
-  const unsigned grid = scan_blocks(N, H, DV / BV);
+static void launch_scan_fwd(const LaunchArgs& a, int N, hipStream_t st, Args... args) {
+  const unsigned grid = scan_blocks(N, a.H, DV / BV);
   if constexpr (DK <= 128 && BV == SCAN_BV && OUT) {
-    if (scan_chains(N, H, DV) >= 3L * device_cus()) {
+    if (scan_fwd_whole_rows(scan_rows(a, N), a.H, DK, DV, device_cus())) {
       k_scan_fwd_bf<DK, DV, BV, OUT, STORE, PHI, true><<<grid, NTHR, 0, st>>>(args...);
       return;
     }
@@ -3500,18 +3498,13 @@ static void launch_scan_fwd(int N, int H, hipStream_t st, Args... args) {
   k_scan_fwd_bf<DK, DV, BV, OUT, STORE, PHI, false><<<grid, NTHR, 0, st>>>(args...);
 }
 
-// The reverse scan over N rows of H heads (arguments after st: the kernel's).
-// dk = 128 fits a CU twice only with the unpadded tiles (SW): taken where there
-// are more chains than CUs (1,024 tokens, H16, 320 / 512 / 1,024 chains: 94.2 /
-// 97.4 / 186.9 -> 73.1 / 82.2 / 153.7 us; 65,536 tokens, 512 chains: 721 -> 586,
-// its state pass 742 -> 544; 256 chains 54.3 against 55.2).  dk = 64 fits twice
-// with padded tiles, whose addresses are simpler (4,096 tokens, 512 chains:
-// 242.4 us against 246.1 with the unpadded ones); dk = 256 fits once either way.
+// The reverse scan over N rows of H heads (arguments after st: the kernel's);
+// beside: the forward scan runs next to it.
 template <int DK, int DV, bool STORE, typename... Args>
-static void launch_scan_bwd(int N, int H, hipStream_t st, Args... args) {
-  const unsigned grid = scan_blocks(N, H, DV / SCAN_BV);
+static void launch_scan_bwd(const LaunchArgs& a, int N, bool beside, hipStream_t st, Args... args) {
+  const unsigned grid = scan_blocks(N, a.H, DV / SCAN_BV);
   if constexpr (DK == 128) {
-    if (scan_chains(N, H, DV) > device_cus()) {
+    if (scan_bwd_unpadded(scan_rows(a, N), a.H, DK, DV, device_cus(), beside)) {
       k_scan_bwd_bf<DK, DV, SCAN_BV, STORE, true><<<grid, NTHR, 0, st>>>(args...);
       return;
     }
@@ -3540,11 +3533,11 @@ static void seg_forward_states(const LaunchArgs& a, const bf16_t* q, const bf16_
   const int P = a.segP, Nst = a.N * (P - 1);
   const int Nphi = phi_all ? a.N * P : Nst, gphi = phi_all ? 0 : P;
   a.stage("scan_seg_state");
-  launch_scan_fwd<DK, DV, SCAN_BV, false, false, false>(Nst, a.H, st,
+  launch_scan_fwd<DK, DV, SCAN_BV, false, false, false>(a, Nst, st,
       q, k, v, beta, bt, a.d, nullptr, vsm, nullptr, Nst, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw,
       nullptr, a.segF, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, P);
   a.stage("scan_seg_phi");
-  launch_scan_fwd<DK, DK, SCAN_BV, false, false, true>(Nphi, a.H, st,
+  launch_scan_fwd<DK, DK, SCAN_BV, false, false, true>(a, Nphi, st,
       q, k, v, beta, bt, a.d, nullptr, vsm, nullptr, Nphi, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw,
       nullptr, a.segPhi, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, gphi);
   a.stage("seg_combine");
@@ -3615,11 +3608,11 @@ static hipError_t run_fwd_bf(const LaunchArgs& a) {
     a.stage(a.saved ? "scan_fwd_save" : "scan_fwd");
     float* htv = a.ht ? a.segHT : nullptr;
     if (a.saved)
-      launch_scan_fwd<DK, DV, SCAN_BV, true, true, false>(Np, a.H, st,
+      launch_scan_fwd<DK, DV, SCAN_BV, true, true, false>(a, Np, st,
           q, k, v, beta, bt, a.d, a.segX0, vsm, nullptr, Np, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As,
           a.Gw, a.o, htv, a.Xq, a.Xs, a.Dq, a.Ds, nullptr, nullptr);
     else
-      launch_scan_fwd<DK, DV, SCAN_BV, true, false, false>(Np, a.H, st,
+      launch_scan_fwd<DK, DV, SCAN_BV, true, false, false>(a, Np, st,
           q, k, v, beta, bt, a.d, a.segX0, vsm, nullptr, Np, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As,
           a.Gw, a.o, htv, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
     // the final state of each row is that of its last segment
@@ -3630,15 +3623,15 @@ static hipError_t run_fwd_bf(const LaunchArgs& a) {
   }
   a.stage(a.saved ? "scan_fwd_save" : "scan_fwd");
   if (a.saved)
-    launch_scan_fwd<DK, DV, SCAN_BV, true, true, false>(a.N, a.H, st,
+    launch_scan_fwd<DK, DV, SCAN_BV, true, true, false>(a, a.N, st,
         q, k, v, beta, bt, a.d, a.h0, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw, a.o, a.ht, a.Xq, a.Xs,
         a.Dq, a.Ds, a.Xfq, a.Xfs);
   else if (narrow_slices(a))
-    launch_scan_fwd<DK, DV, 16, true, false, false>(a.N, a.H, st,
+    launch_scan_fwd<DK, DV, 16, true, false, false>(a, a.N, st,
         q, k, v, beta, bt, a.d, a.h0, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw, a.o, a.ht, nullptr,
         nullptr, nullptr, nullptr, nullptr, nullptr);
   else
-    launch_scan_fwd<DK, DV, SCAN_BV, true, false, false>(a.N, a.H, st,
+    launch_scan_fwd<DK, DV, SCAN_BV, true, false, false>(a, a.N, st,
         q, k, v, beta, bt, a.d, a.h0, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw, a.o, a.ht, nullptr,
         nullptr, nullptr, nullptr, nullptr, nullptr);
   a.stage(nullptr);
@@ -3705,17 +3698,19 @@ static hipError_t run_bwd_bf(const LaunchArgs& a) {
             q, k, a.g, bt, a.d, a.cmap, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp, a.Gw);
       seg_forward_states<DK, DV>(a, q, k, v, beta, bt, true, vsm, Tp);
       a.stage("scan_fwd_store");
-      launch_scan_fwd<DK, DV, SCAN_BV, false, true, false>(Np, a.H, st,
+      launch_scan_fwd<DK, DV, SCAN_BV, false, true, false>(a, Np, st,
           q, k, v, beta, bt, a.d, a.segX0, vsm, nullptr, Np, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As,
           a.Gw, nullptr, nullptr, a.Xq, a.Xs, a.Dq, a.Ds, nullptr, nullptr);
     }
     a.stage("scan_seg_grad");
-    launch_scan_bwd<DK, DV, false>(Nst, a.H, st, q, k, dO, bt, a.d, nullptr, vsm, nullptr, Nst, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp,
+    launch_scan_bwd<DK, DV, false>(a, Nst, false, st,
+        q, k, dO, bt, a.d, nullptr, vsm, nullptr, Nst, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp,
         a.Gw, a.segG, nullptr, nullptr, nullptr, nullptr, P, 1);
     a.stage("seg_combine_bwd");
     launch_seg_combine<DK, DV, true>(a, a.segPhi, a.segG, a.dht, a.segY0);
     a.stage("scan_bwd");
-    launch_scan_bwd<DK, DV, true>(Np, a.H, st, q, k, dO, bt, a.d, a.segY0, vsm, nullptr, Np, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp,
+    launch_scan_bwd<DK, DV, true>(a, Np, false, st,
+        q, k, dO, bt, a.d, a.segY0, vsm, nullptr, Np, Tp, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp,
         a.Gw, a.dh0 ? a.segDH0 : nullptr, a.Yq, a.Ys, a.dRq, a.dRs);
     if (a.dh0 && seg_copy_rows<DK, DV>(a, a.dh0, a.segDH0, 0) != hipSuccess)
       return hipErrorLaunchFailure;
@@ -3735,18 +3730,20 @@ static hipError_t run_bwd_bf(const LaunchArgs& a) {
     side(
         st,
         [&](hipStream_t s1) {
-          launch_scan_fwd<DK, DV, SCAN_BV, false, true, false>(a.N, a.H, s1,
+          launch_scan_fwd<DK, DV, SCAN_BV, false, true, false>(a, a.N, s1,
               q, k, v, beta, bt, a.d, a.h0, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.Gw, nullptr,
               nullptr, a.Xq, a.Xs, a.Dq, a.Ds, a.Xfq, a.Xfs);
         },
         [&](hipStream_t s2) {
-          launch_scan_bwd<DK, DV, true>(a.N, a.H, s2, q, k, dO, bt, a.d, a.dht, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp, a.Gw, a.dh0,
+          launch_scan_bwd<DK, DV, true>(a, a.N, true, s2,
+              q, k, dO, bt, a.d, a.dht, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp, a.Gw, a.dh0,
               a.Yq, a.Ys, a.dRq, a.dRs);
         });
   }
   if (a.segP <= 1 && a.saved) {
     a.stage("scan_bwd");
-    launch_scan_bwd<DK, DV, true>(a.N, a.H, st, q, k, dO, bt, a.d, a.dht, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp, a.Gw, a.dh0, a.Yq,
+    launch_scan_bwd<DK, DV, true>(a, a.N, false, st,
+        q, k, dO, bt, a.d, a.dht, a.smap, sord, a.N, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp, a.Gw, a.dh0, a.Yq,
         a.Ys, a.dRq, a.dRs);
   }
   a.stage("intra_bwd");

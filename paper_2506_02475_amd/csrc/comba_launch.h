@@ -32,6 +32,8 @@ struct LaunchArgs {
   // backward: reuse that state instead of recomputing the forward
   bool saved;
   int dk, dv, H, N, Tseq, Ttot, ncmax;
+  // chunks of all sequences and of the longest one (packed sequences: 0 without host offsets)
+  long chunks, longest;
   const int32_t* cu_seqlens;
   // beta_tilde (feedback strength) is never NULL here: it points at beta when
   // the two are tied; dbeta_tilde NULL means tied (dbeta then holds the sum)

@@ -1,10 +1,12 @@
 """The scans' forms (LDS layout, operand loads, slice width) against each other.
 
-Which form runs depends on the chains per CU, so the same row is computed alone
-(few chains) and inside batches that pass each rule (320 to 1,024 chains of 32
-columns on 256 CUs): its outputs, final state and gradients must be bit for bit
-the same, since no form changes a row's arithmetic.  Ragged last chunks and
-both sides' head sizes."""
+Which form runs depends on the chains that are at work per CU, so the same row is
+computed alone (few chains) and inside batches that pass each rule (320 to 1,024
+chains of 32 columns on 256 CUs): its outputs, final state and gradients must be
+bit for bit the same, since no form changes a row's arithmetic.  Ragged last
+chunks and both sides' head sizes.  Packed batches, with empty sequences, are
+computed with the host offsets (whole-row forward scan) and without them (the
+lengths are not known: the direct one)."""
 import pytest
 
 from comba_inputs import random_case
@@ -12,10 +14,19 @@ from gpu_helpers import to_device
 
 pytestmark = pytest.mark.gpu
 
+# enough full chunks and equal enough lengths for the whole-row form on 256 CUs
+PACKED = [dict(H=16, dk=128, dv=128, seqlens=[448, 0, 511, 512, 575] * 6),
+          dict(H=16, dk=128, dv=64, seqlens=[640, 1, 639, 705, 0] * 12),
+          dict(H=16, dk=64, dv=64, seqlens=[513, 0, 640, 576, 64] * 13)]
+
+
+# nearly full chunks: 64 rows take the whole-row form
+FULL = [(128, 128, 127), (128, 64, 191), (128, 256, 127), (64, 64, 703), (64, 128, 639)]
+
 
 @pytest.mark.parametrize("B", [20, 33, 64])
 @pytest.mark.parametrize("dk,dv,T", [(128, 128, 130), (64, 64, 65), (64, 128, 63), (128, 64, 200),
-                                     (128, 256, 70)])
+                                     (128, 256, 70)] + FULL)
 def test_a_row_does_not_depend_on_its_batch(B, dk, dv, T):
     import torch
 
@@ -44,3 +55,28 @@ def test_a_row_does_not_depend_on_its_batch(B, dk, dv, T):
         assert torch.equal(o1[0], o[b]) and torch.equal(ht1[0], ht[b])
         for n in ("dq", "dk", "dv", "dg", "dbeta", "dh0"):
             assert torch.equal(gr1[n][0], gr[n][b]), n
+
+
+@pytest.mark.parametrize("kw", PACKED, ids=lambda kw: "%d-%d" % (kw["dk"], kw["dv"]))
+def test_packed_forms_agree(kw):
+    import numpy as np
+    import torch
+
+    import paper_2506_02475_amd as comba
+
+    print("case", kw["H"], kw["dk"], kw["dv"], len(kw["seqlens"]), flush=True)
+    w = random_case(T=0, in_dtype="bf16", seed=89, dht=True, **kw)
+    a = to_device(w)
+    args = tuple(a[n] for n in ("q", "k", "v", "g", "beta", "d", "h0"))
+    host = np.concatenate([[0], np.cumsum(kw["seqlens"])]).astype(np.int32)
+    res = []
+    for h in (None, host):
+        kws = dict(cu_seqlens=a["cu_seqlens"], cu_seqlens_host=h)
+        o, ht = comba.comba_chunk_fwd(*args, **kws)
+        o_s, ht_s, ws = comba.comba_chunk_fwd_save(*args, **kws)
+        gr = comba.comba_chunk_bwd_saved(*args, a["dO"], a["dht"], workspace=ws, **kws)
+        res.append(dict(gr, o=o, ht=ht, o_s=o_s, ht_s=ht_s))
+    torch.cuda.synchronize()
+    for n, x in res[0].items():
+        assert torch.equal(x, res[1][n]), n
+    assert torch.equal(res[0]["o"], res[0]["o_s"]) and torch.isfinite(res[0]["dq"]).all()

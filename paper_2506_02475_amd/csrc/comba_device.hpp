@@ -39,10 +39,6 @@ __device__ __forceinline__ float bf2f(bf16_t b) { return __uint_as_float(((uint3
 __device__ __forceinline__ float to_f(float x) { return x; }
 __device__ __forceinline__ float to_f(bf16_t x) { return bf2f(x); }
 
-// Storage padding (elements) that keeps 16-byte row alignment and spreads the
-// 16 rows read by one MFMA operand fetch over distinct LDS banks.
-template <typename T> struct Pad { static constexpr int value = 16 / sizeof(T); };
-
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 __device__ __forceinline__ int wave_id() { return threadIdx.x >> 6; }
 // The same in a scalar register: the compiler cannot tell on its own that it is
@@ -62,101 +58,6 @@ __device__ __forceinline__ float nmax(float a, float b) { return __builtin_eleme
 __device__ __forceinline__ float nmax_abs4(float m, const floatx4& x) {
   return nmax(nmax(m, nmax(fabsf(x[0]), fabsf(x[1]))), nmax(fabsf(x[2]), fabsf(x[3])));
 }
-
-template <int MT, int NT>
-__device__ __forceinline__ void zero_acc(floatx4 (&acc)[MT][NT]) {
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int j = 0; j < NT; ++j) acc[i][j] = zero4();
-}
-
-// ---- operand fragments -------------------------------------------------------
-
-// 8 consecutive-k bf16 values of an exact operand.
-__device__ __forceinline__ bf16x8 frag_exact(const bf16_t* p) {
-  return *reinterpret_cast<const bf16x8*>(p);
-}
-
-// 8 consecutive-k fp32 values split into bf16 hi and lo parts.
-__device__ __forceinline__ void frag_split(const float* p, bf16x8& hi, bf16x8& lo) {
-  const float4 a = *reinterpret_cast<const float4*>(p);
-  const float4 b = *reinterpret_cast<const float4*>(p + 4);
-  const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const __bf16 h = (__bf16)x[e];
-    hi[e] = h;
-    lo[e] = (__bf16)(x[e] - (float)h);
-  }
-}
-
-template <typename T> struct Frag;
-template <> struct Frag<bf16_t> {
-  bf16x8 hi;
-  __device__ __forceinline__ void load(const bf16_t* p) { hi = frag_exact(p); }
-  static constexpr bool split = false;
-};
-template <> struct Frag<float> {
-  bf16x8 hi, lo;
-  __device__ __forceinline__ void load(const float* p) { frag_split(p, hi, lo); }
-  static constexpr bool split = true;
-};
-
-// acc[mt][nt] += sum_{k < K} A(16 mt + i, k) * B(k, 16 nt + j)
-//   A(m, k) = A[m * lda + k]   (row-major, k contiguous)
-//   B(k, n) = B[n * ldb + k]   (stored transposed, k contiguous)
-// F32 selects the fp32 MFMA (both operands fp32); otherwise the bf16 MFMA with
-// fp32 operands split as described above.
-template <bool F32, int MT, int NT, int K, typename TA, typename TB>
-__device__ __forceinline__ void mma(floatx4 (&acc)[MT][NT], const TA* __restrict__ A, int lda,
-                                    const TB* __restrict__ B, int ldb) {
-  const int lane = lane_id();
-  const int r = lane & 15, grp = lane >> 4;
-  if constexpr (F32) {
-    static_assert(is_f32<TA>::value && is_f32<TB>::value, "fp32 MFMA takes fp32 operands");
-#pragma unroll
-    for (int k0 = 0; k0 < K; k0 += 4) {
-      float a[MT], b[NT];
-#pragma unroll
-      for (int i = 0; i < MT; ++i) a[i] = A[(16 * i + r) * lda + k0 + grp];
-#pragma unroll
-      for (int j = 0; j < NT; ++j) b[j] = B[(16 * j + r) * ldb + k0 + grp];
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-  } else {
-    static_assert(K % 32 == 0, "bf16 MFMA reduces 32 at a time");
-#pragma unroll
-    for (int k0 = 0; k0 < K; k0 += 32) {
-      const int kk = k0 + 8 * grp;
-      Frag<TA> a[MT];
-      Frag<TB> b[NT];
-#pragma unroll
-      for (int i = 0; i < MT; ++i) a[i].load(A + (16 * i + r) * lda + kk);
-#pragma unroll
-      for (int j = 0; j < NT; ++j) b[j].load(B + (16 * j + r) * ldb + kk);
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i].hi, b[j].hi, acc[i][j], 0, 0, 0);
-          if constexpr (Frag<TA>::split)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i].lo, b[j].hi, acc[i][j], 0, 0, 0);
-          if constexpr (Frag<TB>::split)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i].hi, b[j].lo, acc[i][j], 0, 0, 0);
-        }
-    }
-  }
-}
-
-// Row / column of accumulator element e of tile (mt, nt), relative to the
-// block origin passed to mma().
-__device__ __forceinline__ int acc_row(int mt, int e) { return 16 * mt + 4 * (lane_id() >> 4) + e; }
-__device__ __forceinline__ int acc_col(int nt) { return 16 * nt + (lane_id() & 15); }
 
 // ---- accumulator row stores --------------------------------------------------
 // An accumulator tile gives lane l the rows 4 (l / 16) + e (e = 0..3) of
@@ -580,29 +481,7 @@ struct TileRegs {
       }
     }
   }
-  // st[c * ldt + r] = tile[r][c]
-  __device__ __forceinline__ void store_t(T* st, int ldt) const {
-#pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-      const int idx = threadIdx.x + it * NTHR;
-      if (TOTAL % NTHR == 0 || idx < TOTAL) {
-        const int rr = idx / PER_ROW, cc = (idx % PER_ROW) * V;
-        union { uint4 u; T e[V]; } val;
-        val.u = r[it];
-#pragma unroll
-        for (int e = 0; e < V; ++e) st[(cc + e) * ldt + rr] = val.e[e];
-      }
-    }
-  }
 };
-
-// One-shot copies (load then store) for tiles that are not prefetched.
-template <typename T, int NROWS, int COLS>
-__device__ __forceinline__ void tile_to_lds(const T* __restrict__ g, long gs, int rows, T* s, int ld) {
-  TileRegs<T, NROWS, COLS> t;
-  t.load(g, gs, rows);
-  t.store(s, ld);
-}
 
 // Inclusive prefix sum across the 64 lanes of a wavefront: within each row by
 // shifts of 1, 2, 4, 8, then the row totals carried upward by row broadcasts.

@@ -276,7 +276,8 @@ __device__ __forceinline__ void put_block_column(float* Ls, const floatx4 (&mb)[
 // dD0 = A^T dO and P = (Q - d K)^T Diag(e^G) dO: dD = dD0 + K~ Y,
 // Y' = e^{G_63} Y + P - W^T dD, and dR = M^T dD afterwards.
 // Kernels: k_prep (G, M, W, U), k_out, k_bprep (dD0, P), k_states (the forward
-// and the reverse chain, side by side in one grid), k_dr, k_intra_bwd.
+// and the reverse chain, side by side in one grid), k_intra_bwd (dR and the
+// gradients).
 // Forward + stateless backward at B2 T1000 H8: 324 -> 132 us; the tiny forward
 // (B1 T256 H1): 42 -> 26 us (before: five products per step and a one-wave
 // substitution of 64 rows; a step took 5.3 us, now 1.4).  Errors against 64
@@ -294,32 +295,37 @@ __device__ __forceinline__ floatx4 mfma4(float a, float b, const floatx4& c) {
 }
 // Operand fetch at block kb for this lane's row / column x (16 t + lane % 16):
 // rows with k contiguous, or k down the rows.
+template <int LD = FLD>
 struct RowOp {
   const float* p;
   __device__ __forceinline__ floatx4 get(int x, int kb) const {
-    const float4 v = *reinterpret_cast<const float4*>(p + x * FLD + 16 * kb + 4 * (lane_id() >> 4));
+    const float4 v = *reinterpret_cast<const float4*>(p + x * LD + 16 * kb + 4 * (lane_id() >> 4));
     return floatx4{v.x, v.y, v.z, v.w};
   }
 };
+template <int LD = FLD>
 struct ColOp {
   const float* p;
   __device__ __forceinline__ floatx4 get(int x, int kb) const {
-    const float* c = p + (16 * kb + 4 * (lane_id() >> 4)) * FLD + x;
-    return floatx4{c[0], c[FLD], c[2 * FLD], c[3 * FLD]};
+    const float* c = p + (16 * kb + 4 * (lane_id() >> 4)) * LD + x;
+    return floatx4{c[0], c[LD], c[2 * LD], c[3 * LD]};
   }
 };
-// acc[nt] += A(rows 16 w ..) B(columns 16 nt ..) over k blocks kb0 .. kb1 - 1
-template <typename OA, typename OB>
-__device__ __forceinline__ void fmm(floatx4 (&acc)[4], const OA& A, const OB& B, int w, int kb0 = 0, int kb1 = 4) {
+// acc[nt] += A(rows 16 w ..) B(columns 16 nt ..) over k blocks kb0 .. kb1 - 1,
+// column tiles nt <= nt1
+template <int NT, typename OA, typename OB>
+__device__ __forceinline__ void fmm(floatx4 (&acc)[NT], const OA& A, const OB& B, int w, int kb0 = 0, int kb1 = 4,
+                                    int nt1 = NT - 1) {
   const int r16 = lane_id() & 15;
   for (int kb = kb0; kb < kb1; ++kb) {
     const floatx4 a = A.get(16 * w + r16, kb);
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      const floatx4 b = B.get(16 * nt + r16, kb);
+    for (int nt = 0; nt < NT; ++nt)
+      if (nt <= nt1) {
+        const floatx4 b = B.get(16 * nt + r16, kb);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[nt] = mfma4(a[e], b[e], acc[nt]);
-    }
+        for (int e = 0; e < 4; ++e) acc[nt] = mfma4(a[e], b[e], acc[nt]);
+      }
   }
 }
 __device__ __forceinline__ void fzero(floatx4 (&acc)[4]) { acc[0] = acc[1] = acc[2] = acc[3] = zero4(); }
@@ -380,7 +386,7 @@ __global__ __launch_bounds__(NTHR) void k_prep(const float* __restrict__ k, cons
   {
     floatx4 kk[4];
     fzero(kk);
-    fmm(kk, RowOp{Ks}, RowOp{Ks}, w);
+    fmm(kk, RowOp<>{Ks}, RowOp<>{Ks}, w);
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
@@ -431,8 +437,8 @@ __global__ __launch_bounds__(NTHR) void k_prep(const float* __restrict__ k, cons
   floatx4 wa[4], ua[4];
   fzero(wa);
   fzero(ua);
-  fmm(wa, RowOp{Ls}, ColOp{Ks}, w, 0, w + 1);
-  fmm(ua, RowOp{Ls}, ColOp{Vs}, w, 0, w + 1);
+  fmm(wa, RowOp<>{Ls}, ColOp<>{Ks}, w, 0, w + 1);
+  fmm(ua, RowOp<>{Ls}, ColOp<>{Vs}, w, 0, w + 1);
   float* ub = u_rows ? U + tok * FD : U + chh * FT;
   const long us = u_rows ? (long)H * FD : FD;
 #pragma unroll
@@ -451,7 +457,7 @@ __device__ __forceinline__ void f32_scores(float* As, const float* Qt, const flo
   const int lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
   floatx4 a[4];
   fzero(a);
-  fmm(a, RowOp{Qt}, RowOp{Ks}, w);
+  fmm(a, RowOp<>{Qt}, RowOp<>{Ks}, w);
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
@@ -498,7 +504,7 @@ __global__ __launch_bounds__(NTHR) void k_out(const float* __restrict__ q, const
   f32_scores(As, Qt, Ks, Gs, w);
   floatx4 acc[4];
   fzero(acc);
-  fmm(acc, RowOp{Qt}, ColOp{Xs}, w);
+  fmm(acc, RowOp<>{Qt}, ColOp<>{Xs}, w);
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const float eg = __expf(Gs[16 * w + 4 * g4 + e]);
@@ -506,7 +512,7 @@ __global__ __launch_bounds__(NTHR) void k_out(const float* __restrict__ q, const
     for (int nt = 0; nt < 4; ++nt) acc[nt][e] *= eg;
   }
   // only this wave's rows of A are read: no barrier
-  fmm(acc, RowOp{As}, ColOp{Ds}, w, 0, w + 1);
+  fmm(acc, RowOp<>{As}, ColOp<>{Ds}, w, 0, w + 1);
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
@@ -543,7 +549,7 @@ __global__ __launch_bounds__(NTHR) void k_bprep(const float* __restrict__ q, con
   // A is lower triangular: A^T's k blocks from the row tile on
   floatx4 acc[4];
   fzero(acc);
-  fmm(acc, ColOp{As}, ColOp{Os}, w, w, 4);
+  fmm(acc, ColOp<>{As}, ColOp<>{Os}, w, w, 4);
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
@@ -559,34 +565,11 @@ __global__ __launch_bounds__(NTHR) void k_bprep(const float* __restrict__ q, con
   }
   __syncthreads();
   fzero(acc);
-  fmm(acc, ColOp{Ks}, ColOp{Os}, w);
+  fmm(acc, ColOp<>{Ks}, ColOp<>{Os}, w);
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
     for (int e = 0; e < 4; ++e) Yw[chh * FT + (16 * w + 4 * g4 + e) * FD + 16 * nt + r16] = acc[nt][e];
-}
-
-// dR = M^T dD per chunk-head, in place.
-__global__ __launch_bounds__(NTHR) void k_dr(const ChunkInfo* __restrict__ cmap, int Tfix, int H,
-                                             const float* __restrict__ Mw, float* __restrict__ dRw) {
-  __shared__ __align__(16) float Ms[CH * FLD], Ds[CH * FLD];
-  const ChunkInfo ci = chunk_at(cmap, blockIdx.x, Tfix);
-  if (ci.len <= 0) return;
-  const long chh = (long)blockIdx.x * H + blockIdx.y;
-  const int w = wave_id(), lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
-  FTile mr, dr;
-  mr.load(Mw + chh * FT, FD, CH);
-  dr.load(dRw + chh * FT, FD, CH);
-  mr.store(Ms);
-  dr.store(Ds);
-  __syncthreads();
-  floatx4 acc[4];
-  fzero(acc);
-  fmm(acc, ColOp{Ms}, ColOp{Ds}, w, w, 4);
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) dRw[chh * FT + (16 * w + 4 * g4 + e) * FD + 16 * nt + r16] = acc[nt][e];
 }
 
 // The chains.  One workgroup per (sequence, head, 16-column slice) and
@@ -756,176 +739,188 @@ __global__ __launch_bounds__(NTHR) void k_states(StatesArgs a, const SeqInfo* __
 
 // ---------------------------------------------------------------------------
 // k_intra_bwd: per chunk-head gradients.  Phase 1 streams the dv axis in blocks
-// of 32 and accumulates the dv-reductions
+// of 32: dR = M^T dD, then the dv-reductions
 //   T1 = dO X^T, T3 = dR X^T, T2 = D Y^T (C x dk), dO D^T, dR D^T (C x C),
-//   <Y, X>_F, <v_r, dR_r>, and writes dv = Diag(beta) dR.
-// Phase 2 forms
+//   <Y, X>_F, <v_r, dR_r>, and dv = Diag(beta) dR.
+// Phase 2 forms, with Q~ = Q - d K,
 //   dQ~ = Diag(exp G) T1 + (dA o Gamma) K
-//   dK  = Diag(exp(G_63 - G)) T2 - Diag(s) T3 + (dA o Gamma)^T Q
-//         + (dAkk + dAkk^T - d (dA o Gamma)^T) K
+//   dK + d dQ~ = Diag(exp(G_63 - G)) T2 - Diag(s) T3 + (dA o Gamma)^T Q~ + (dAkk + dAkk^T) K
 // and the per-token gate / beta gradients, then dg by a reverse in-chunk sum.
+// Bound by fp32 MFMA (32 cycles each; zero blocks above the diagonals are left
+// out) and, with few chunks, by one workgroup's chain of them.  Operands are
+// read from one copy of each tile, rows or columns, so that two workgroups fit a
+// CU (76 KB; with transposed copies 139 KB, one per CU).  B32 T256 H16: 213 us
+// and 19 for a kernel of its own for dR, now 140.
 // ---------------------------------------------------------------------------
-template <typename Tin, int DK, int DV>
-struct IntraBwdSmem {
-  static constexpr int VB = 32;
-  static constexpr int PI = Pad<Tin>::value;
-  static constexpr int LDK = DK + PI, LDC = CH + PI, LDVB = VB + PI;
-  static constexpr int LDF = CH + 4, LDFB = VB + 4;
-  static constexpr int P1 = 2 * CH * LDVB * (int)sizeof(Tin) + 2 * CH * LDFB * 4 + 2 * DK * LDFB * 4;
-  static constexpr int P2 = 2 * CH * LDK * (int)sizeof(Tin) + 2 * DK * LDC * (int)sizeof(Tin) +
-                            4 * CH * LDF * 4;
-  static constexpr int BYTES = P1 > P2 ? P1 : P2;
-};
-
-template <typename Tin, int DK, int DV>
-__global__ __launch_bounds__(NTHR, 1) void k_intra_bwd(
-    const Tin* __restrict__ q, const Tin* __restrict__ k, const Tin* __restrict__ v,
-    const Tin* __restrict__ dO, const Tin* __restrict__ beta, const Tin* __restrict__ beta_tilde,
+constexpr int VB32 = 32, FLB = VB32 + 4;  // columns of a block, its LDS row stride
+__global__ __launch_bounds__(NTHR, 2) void k_intra_bwd(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+    const float* __restrict__ dO, const float* __restrict__ beta, const float* __restrict__ beta_tilde,
     const float* __restrict__ d, const ChunkInfo* __restrict__ cmap, int Tfix, int H,
-    const float* __restrict__ Gw, const float* __restrict__ Xw, const float* __restrict__ Dw,
-    const float* __restrict__ Yw, const float* __restrict__ dRw, float* __restrict__ dq,
-    float* __restrict__ dk, float* __restrict__ dv, float* __restrict__ dbeta,
+    const float* __restrict__ Gw, const float* __restrict__ Mw, const float* __restrict__ Xw,
+    const float* __restrict__ Dw, const float* __restrict__ Yw, const float* __restrict__ dDw,
+    float* __restrict__ dq, float* __restrict__ dk, float* __restrict__ dv, float* __restrict__ dbeta,
     float* __restrict__ dbeta_tilde, float* __restrict__ dg, float* __restrict__ ddp) {
-  using SM = IntraBwdSmem<Tin, DK, DV>;
-  constexpr bool F32 = is_f32<Tin>::value;
-  constexpr int VB = SM::VB, LDK = SM::LDK, LDC = SM::LDC, LDVB = SM::LDVB, LDF = SM::LDF,
-                LDFB = SM::LDFB;
-  constexpr int NTK = DK / 16;
-  __shared__ __align__(16) char smem[SM::BYTES];
+  constexpr int T64 = CH * FLD, T32 = CH * FLB;  // floats of a 64-column tile, of a block
+  __shared__ __align__(16) float smem[T64 + 6 * T32];
   // rowB: derivative through beta (write strength), rowBt: through beta~
   // (feedback strength, in L and in R's K X term)
-  __shared__ float Gs[CH], Bs[CH], Bts[CH], rowG[CH], rowGm[CH], rowB[CH], rowBt[CH];
+  __shared__ float Gs[CH], Bs[CH], Bts[CH], rowG[CH], rowGm[CH], rowB[CH], rowBt[CH], rowC[CH];
   __shared__ float colpart[NWAVE][CH];
-  __shared__ float scal[NWAVE][3];
+  __shared__ float scal[NWAVE][2];
 
-  const int h = blockIdx.y;
-  const long chh = (long)blockIdx.x * H + h;
-  const ChunkInfo ci = chunk_at(cmap, blockIdx.x, Tfix);
+  const int chunk = blockIdx.x / H, h = blockIdx.x - chunk * H;  // heads fastest
+  const long chh = blockIdx.x;
+  const ChunkInfo ci = chunk_at(cmap, chunk, Tfix);
   if (ci.len <= 0) {
     if (threadIdx.x == 0) ddp[chh] = 0.f;
     return;
   }
   const long tok = (long)ci.tok0 * H + h;
-  const int tid = threadIdx.x, w = wave_id(), lane = lane_id();
+  const int tid = threadIdx.x, w = wave_id(), lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
   const int len = ci.len;
   const float dh = d[h];
+  // this wave's rows 16 rt ..: the rotation spreads the long row tiles over the
+  // SIMDs of the workgroups that share a CU
+  const int rt = __builtin_amdgcn_readfirstlane((w + chunk + h) & (NWAVE - 1));
 
+  // ---------------- phase 1: reductions over dv ----------------
+  float* Ms = smem;
+  float* dOb = Ms + T64;
+  float* dDb = dOb + T32;
+  float* dRb = dDb + T32;
+  float* Dlb = dRb + T32;
+  float* Xb = Dlb + T32;
+  float* Yb = Xb + T32;
+
+  const int er = 16 * rt + (lane >> 2), ec = (lane & 3) * 8;  // elementwise ownership: row er, 8 columns
+  TileRegs<float, CH, VB32> rdo, rdd, rdl, rx, ry;
+  float4 v0, v1;
+  auto issue = [&](int vb) {
+    rdo.load(dO + tok * FD + vb * VB32, (long)H * FD, len);
+    rdd.load(dDw + chh * FT + vb * VB32, FD, CH);
+    rdl.load(Dw + chh * FT + vb * VB32, FD, CH);
+    rx.load(Xw + chh * FT + vb * VB32, FD, CH);
+    ry.load(Yw + chh * FT + vb * VB32, FD, CH);
+    const float* vp = v + (tok + (long)min(er, len - 1) * H) * FD + vb * VB32 + ec;
+    v0 = *reinterpret_cast<const float4*>(vp);
+    v1 = *reinterpret_cast<const float4*>(vp + 4);
+  };
+  {
+    FTile mr;
+    mr.load(Mw + chh * FT, FD, CH);
+    issue(0);
+    mr.store(Ms);
+  }
   if (tid < CH) {
     Gs[tid] = Gw[chh * CH + tid];
-    Bs[tid] = tid < len ? to_f(beta[tok + (long)tid * H]) : 0.f;
-    Bts[tid] = tid < len ? to_f(beta_tilde[tok + (long)tid * H]) : 0.f;
+    Bs[tid] = tid < len ? beta[tok + (long)tid * H] : 0.f;
+    Bts[tid] = tid < len ? beta_tilde[tok + (long)tid * H] : 0.f;
     rowG[tid] = 0.f;
     rowGm[tid] = 0.f;
     rowBt[tid] = 0.f;
   }
-
-  // ---------------- phase 1: reductions over dv ----------------
-  Tin* dOb = reinterpret_cast<Tin*>(smem);
-  Tin* Vb = dOb + CH * LDVB;
-  float* dRb = reinterpret_cast<float*>(Vb + CH * LDVB);
-  float* Dlb = dRb + CH * LDFB;
-  float* Xb = Dlb + CH * LDFB;
-  float* Yb = Xb + DK * LDFB;
-
-  floatx4 T1[1][NTK], T2[1][NTK], T3[1][NTK], dAr[1][4], dLr[1][4];
-  zero_acc(T1);
-  zero_acc(T2);
-  zero_acc(T3);
-  zero_acc(dAr);
-  zero_acc(dLr);
+  floatx4 T1[4], T2[4], T3[4], dAr[4], dLr[4];
+  fzero(T1);
+  fzero(T2);
+  fzero(T3);
+  fzero(dAr);
+  fzero(dLr);
   float Fpart = 0.f, bv = 0.f;
-  const int er = tid >> 2, ec = (tid & 3) * 8;  // elementwise ownership: row er, 8 columns
-  TileRegs<Tin, CH, VB> rdo, rv;
-  TileRegs<float, CH, VB> rdr, rdl;
-  TileRegs<float, DK, VB> rx, ry;
-  auto issue = [&](int vb) {
-    rdo.load(dO + tok * DV + vb * VB, (long)H * DV, len);
-    rv.load(v + tok * DV + vb * VB, (long)H * DV, len);
-    rdr.load(dRw + chh * CH * DV + vb * VB, DV, CH);
-    rdl.load(Dw + chh * CH * DV + vb * VB, DV, CH);
-    rx.load(Xw + chh * DK * DV + vb * VB, DV, DK);
-    ry.load(Yw + chh * DK * DV + vb * VB, DV, DK);
-  };
-  issue(0);
-  for (int vb = 0; vb < DV / VB; ++vb) {
-    __syncthreads();
-    rdo.store(dOb, LDVB);
-    rv.store(Vb, LDVB);
-    rdr.store(dRb, LDFB);
-    rdl.store(Dlb, LDFB);
-    rx.store(Xb, LDFB);
-    ry.store(Yb, LDFB);
-    __syncthreads();
-    if (vb + 1 < DV / VB) issue(vb + 1);
-    mma<F32, 1, NTK, VB>(T1, dOb + 16 * w * LDVB, LDVB, Xb, LDFB);
-    mma<F32, 1, NTK, VB>(T3, dRb + 16 * w * LDFB, LDFB, Xb, LDFB);
-    mma<F32, 1, NTK, VB>(T2, Dlb + 16 * w * LDFB, LDFB, Yb, LDFB);
-    mma<F32, 1, 4, VB>(dAr, dOb + 16 * w * LDVB, LDVB, Dlb, LDFB);
-    mma<F32, 1, 4, VB>(dLr, dRb + 16 * w * LDFB, LDFB, Dlb, LDFB);
+  FTile kr, qr;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float x = dRb[er * LDFB + ec + e];
-      bv += to_f(Vb[er * LDVB + ec + e]) * x;
-      if (er < len) dv[(tok + (long)er * H) * DV + vb * VB + ec + e] = Bs[er] * x;
+  for (int vb = 0; vb < FD / VB32; ++vb) {
+    if (vb > 0) __syncthreads();
+    rdo.store(dOb, FLB);
+    rdd.store(dDb, FLB);
+    rdl.store(Dlb, FLB);
+    rx.store(Xb, FLB);
+    ry.store(Yb, FLB);
+    auto f = [](uint32_t u) { return __uint_as_float(u); };
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      Fpart = fmaf(f(rx.r[i].x), f(ry.r[i].x), Fpart);
+      Fpart = fmaf(f(rx.r[i].y), f(ry.r[i].y), Fpart);
+      Fpart = fmaf(f(rx.r[i].z), f(ry.r[i].z), Fpart);
+      Fpart = fmaf(f(rx.r[i].w), f(ry.r[i].w), Fpart);
     }
-    for (int idx = tid; idx < DK * VB; idx += NTHR) {
-      const int i = idx / VB, jj = idx % VB;
-      Fpart += Xb[i * LDFB + jj] * Yb[i * LDFB + jj];
+    const float4 va = v0, vc = v1;
+    __syncthreads();
+    if (vb + 1 < FD / VB32) {
+      issue(vb + 1);
+    } else {
+      kr.load(k + tok * FD, (long)H * FD, len);
+      qr.load(q + tok * FD, (long)H * FD, len);
+    }
+    {
+      // M is lower triangular: M^T's k blocks from the row tile on
+      floatx4 dr[2] = {zero4(), zero4()};
+      fmm(dr, ColOp<>{Ms}, ColOp<FLB>{dDb}, rt, rt, 4);
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dRb[(16 * rt + 4 * g4 + e) * FLB + 16 * nt + r16] = dr[nt][e];
+    }
+    // only this wave's rows of dR are read: no barrier
+    fmm(T1, RowOp<FLB>{dOb}, RowOp<FLB>{Xb}, rt, 0, 2);
+    fmm(T2, RowOp<FLB>{Dlb}, RowOp<FLB>{Yb}, rt, 0, 2);
+    fmm(dAr, RowOp<FLB>{dOb}, RowOp<FLB>{Dlb}, rt, 0, 2, rt);
+    fmm(T3, RowOp<FLB>{dRb}, RowOp<FLB>{Xb}, rt, 0, 2);
+    fmm(dLr, RowOp<FLB>{dRb}, RowOp<FLB>{Dlb}, rt, 0, 2, rt);
+    {
+      const float4 a = *reinterpret_cast<const float4*>(dRb + er * FLB + ec);
+      const float4 c = *reinterpret_cast<const float4*>(dRb + er * FLB + ec + 4);
+      if (er < len) {
+        bv += va.x * a.x + va.y * a.y + va.z * a.z + va.w * a.w + vc.x * c.x + vc.y * c.y + vc.z * c.z + vc.w * c.w;
+        const float b = Bs[er];
+        float4* out = reinterpret_cast<float4*>(dv + (tok + (long)er * H) * FD + vb * VB32 + ec);
+        out[0] = make_float4(b * a.x, b * a.y, b * a.z, b * a.w);
+        out[1] = make_float4(b * c.x, b * c.y, b * c.z, b * c.w);
+      }
     }
   }
   bv += __shfl_xor(bv, 1);
   bv += __shfl_xor(bv, 2);
-  if ((tid & 3) == 0) rowB[er] = bv;
+  if ((lane & 3) == 0) rowB[er] = bv;
   Fpart = wave_sum(Fpart);
   if (lane == 0) scal[w][0] = Fpart;
   __syncthreads();
 
   // ---------------- phase 2 ----------------
-  Tin* Ks = reinterpret_cast<Tin*>(smem);
-  Tin* Qs = Ks + CH * LDK;
-  Tin* KsT = Qs + CH * LDK;
-  Tin* QsT = KsT + DK * LDC;
-  float* dAG = reinterpret_cast<float*>(QsT + DK * LDC);
-  float* dAGT = dAG + CH * LDF;
-  float* Bsym = dAGT + CH * LDF;
-  float* dAkk = Bsym + CH * LDF;
-  {
-    TileRegs<Tin, CH, DK> kr, qr;
-    kr.load(k + tok * DK, (long)H * DK, len);
-    qr.load(q + tok * DK, (long)H * DK, len);
-    kr.store(Ks, LDK);
-    kr.store_t(KsT, LDC);
-    qr.store(Qs, LDK);
-    qr.store_t(QsT, LDC);
-  }
+  float* Ks = smem;
+  float* Qt = Ks + T64;
+  float* dAG = Qt + T64;
+  float* dAkk = dAG + T64;
+  static_assert(4 * T64 <= T64 + 6 * T32, "LDS of phase 2");
+  kr.store(Ks);
+  f32_qt(Qt, qr, kr, dh);
   __syncthreads();
   const float Glast = Gs[CH - 1];
 
   {
-    floatx4 akk[1][4], aqk[1][4];
-    zero_acc(akk);
-    zero_acc(aqk);
-    mma<F32, 1, 4, DK>(akk, Ks + 16 * w * LDK, LDK, Ks, LDK);
-    mma<F32, 1, 4, DK>(aqk, Qs + 16 * w * LDK, LDK, Ks, LDK);
+    floatx4 akk[4], aqk[4];
+    fzero(akk);
+    fzero(aqk);
+    fmm(akk, RowOp<>{Ks}, RowOp<>{Ks}, rt, 0, 4, rt);
+    fmm(aqk, RowOp<>{Qt}, RowOp<>{Ks}, rt, 0, 4, rt);
     float rE1[4] = {0.f, 0.f, 0.f, 0.f}, rE2[4] = {0.f, 0.f, 0.f, 0.f}, rBL[4] = {0.f, 0.f, 0.f, 0.f};
     float cE[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int r = 16 * w + acc_row(0, e), c = acc_col(nt);
-        const float kk = akk[0][nt][e];
+        const int r = 16 * rt + 4 * g4 + e, c = 16 * nt + r16;
+        const float kk = akk[nt][e];
         float dag = 0.f, e1 = 0.f, e2 = 0.f, dakk = 0.f;
         if (r >= c) {
           const float gam = __expf(Gs[r] - Gs[c]);
-          const float a = (aqk[0][nt][e] - dh * kk) * gam;
-          const float da = dAr[0][nt][e];
-          e1 = da * a;
+          const float da = dAr[nt][e];
+          e1 = da * (aqk[nt][e] * gam);
           dag = da * gam;
         }
         if (r > c) {
           const float lc = __expf(Gs[r - 1] - Gs[c]);
-          const float dl = -dLr[0][nt][e];
+          const float dl = -dLr[nt][e];
           const float lck = lc * kk;
           e2 = dl * Bts[r] * lck;
           rBL[e] += dl * lck;
@@ -934,9 +929,8 @@ __global__ __launch_bounds__(NTHR, 1) void k_intra_bwd(
         rE1[e] += e1;
         rE2[e] += e2;
         cE[nt] += e1 + e2;
-        dAG[r * LDF + c] = dag;
-        dAGT[c * LDF + r] = dag;
-        dAkk[r * LDF + c] = dakk;
+        dAG[r * FLD + c] = dag;
+        dAkk[r * FLD + c] = dakk;
       }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -947,106 +941,101 @@ __global__ __launch_bounds__(NTHR, 1) void k_intra_bwd(
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) {
       cE[nt] = sum_groups(cE[nt]);
-      if ((lane >> 4) == 0) colpart[w][acc_col(nt)] = cE[nt];
+      if (g4 == 0) colpart[w][16 * nt + r16] = cE[nt];
     }
-    if ((lane & 15) == 0) {
+    if (r16 == 0) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int r = 16 * w + acc_row(0, e);
+        const int r = 16 * rt + 4 * g4 + e;
         rowG[r] += rE1[e];
         rowGm[r] += rE2[e];
         rowBt[r] += rBL[e];
       }
     }
   }
-  __syncthreads();
-  for (int idx = tid; idx < CH * CH; idx += NTHR) {
-    const int r = idx / CH, c = idx % CH;
-    Bsym[r * LDF + c] = dAkk[r * LDF + c] + dAkk[c * LDF + r] - dh * dAGT[r * LDF + c];
-  }
-  __syncthreads();
 
   // row dot products of T1, T2, T3 with q~ and k
   {
     float p1[4] = {0.f, 0.f, 0.f, 0.f}, p2[4] = {0.f, 0.f, 0.f, 0.f}, p3[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int nt = 0; nt < NTK; ++nt)
+    for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int r = 16 * w + acc_row(0, e), c = acc_col(nt);
-        const float kv = to_f(Ks[r * LDK + c]);
-        const float qv = to_f(Qs[r * LDK + c]) - dh * kv;
-        p1[e] += T1[0][nt][e] * qv;
-        p2[e] += T2[0][nt][e] * kv;
-        p3[e] += T3[0][nt][e] * kv;
+        const int r = 16 * rt + 4 * g4 + e, c = 16 * nt + r16;
+        const float kv = Ks[r * FLD + c];
+        p1[e] += T1[nt][e] * Qt[r * FLD + c];
+        p2[e] += T2[nt][e] * kv;
+        p3[e] += T3[nt][e] * kv;
       }
-    float gcp = 0.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       p1[e] = sum16(p1[e]);
       p2[e] = sum16(p2[e]);
       p3[e] = sum16(p3[e]);
-      if ((lane & 15) == 0) {
-        const int r = 16 * w + acc_row(0, e);
-        const float cr = __expf(Glast - Gs[r]) * p2[e];
+      if (r16 == 0) {
+        const int r = 16 * rt + 4 * g4 + e;
         const float egm = __expf(r > 0 ? Gs[r - 1] : 0.f);
-        rowG[r] += __expf(Gs[r]) * p1[e] - cr;
+        rowG[r] += __expf(Gs[r]) * p1[e];
+        rowC[r] = __expf(Glast - Gs[r]) * p2[e];
         rowGm[r] -= Bts[r] * egm * p3[e];
         rowBt[r] -= egm * p3[e];
-        gcp += cr;
       }
     }
-    gcp = wave_sum(gcp);
-    if (lane == 0) scal[w][1] = gcp;
   }
 
-  // dQ~ (in T1) and dK (in T2)
+  // dQ~ (in T1) and dK + d dQ~ (in T2)
 #pragma unroll
-  for (int nt = 0; nt < NTK; ++nt)
+  for (int e = 0; e < 4; ++e) {
+    const int r = 16 * rt + 4 * g4 + e;
+    const float eg = __expf(Gs[r]), ec63 = __expf(Glast - Gs[r]);
+    const float s = Bts[r] * __expf(r > 0 ? Gs[r - 1] : 0.f);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int r = 16 * w + acc_row(0, e);
-      const float egm = __expf(r > 0 ? Gs[r - 1] : 0.f);
-      T1[0][nt][e] *= __expf(Gs[r]);
-      T2[0][nt][e] = __expf(Glast - Gs[r]) * T2[0][nt][e] - Bts[r] * egm * T3[0][nt][e];
+    for (int nt = 0; nt < 4; ++nt) {
+      T1[nt][e] *= eg;
+      T2[nt][e] = ec63 * T2[nt][e] - s * T3[nt][e];
     }
-  mma<F32, 1, NTK, CH>(T1, dAG + 16 * w * LDF, LDF, KsT, LDC);
-  mma<F32, 1, NTK, CH>(T2, dAGT + 16 * w * LDF, LDF, QsT, LDC);
-  mma<F32, 1, NTK, CH>(T2, Bsym + 16 * w * LDF, LDF, KsT, LDC);
+  }
+  __syncthreads();  // dAG and dAkk are complete
+  fmm(T1, RowOp<>{dAG}, ColOp<>{Ks}, rt, 0, rt + 1);
+  fmm(T2, ColOp<>{dAG}, ColOp<>{Qt}, rt, rt, 4);
+  fmm(T2, RowOp<>{dAkk}, ColOp<>{Ks}, rt, 0, rt + 1);
+  fmm(T2, ColOp<>{dAkk}, ColOp<>{Ks}, rt, rt, 4);
   float ddpart = 0.f;
 #pragma unroll
-  for (int nt = 0; nt < NTK; ++nt)
+  for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int r = 16 * w + acc_row(0, e), c = acc_col(nt);
-      const float dqt = T1[0][nt][e];
-      ddpart += to_f(Ks[r * LDK + c]) * dqt;
+      const int r = 16 * rt + 4 * g4 + e, c = 16 * nt + r16;
+      const float dqt = T1[nt][e];
+      ddpart += Ks[r * FLD + c] * dqt;
       if (r < len) {
-        const long off = (tok + (long)r * H) * DK + c;
+        const long off = (tok + (long)r * H) * FD + c;
         dq[off] = dqt;
-        dk[off] = T2[0][nt][e] - dh * dqt;
+        dk[off] = T2[nt][e] - dh * dqt;
       }
     }
   ddpart = wave_sum(ddpart);
-  if (lane == 0) scal[w][2] = ddpart;
+  if (lane == 0) scal[w][1] = ddpart;
   __syncthreads();
 
   if (w == 0) {
     const int r = lane;
-    float F = 0.f, gcs = 0.f, dds = 0.f, col = 0.f;
+    float F = 0.f, dds = 0.f, col = 0.f;
 #pragma unroll
     for (int i = 0; i < NWAVE; ++i) {
       F += scal[i][0];
-      gcs += scal[i][1];
-      dds += scal[i][2];
+      dds += scal[i][1];
       col += colpart[i][r];
     }
     float dG = rowG[r] - col + (r + 1 < CH ? rowGm[r + 1] : 0.f);
-    if (r == CH - 1) dG += gcs + __expf(Glast) * F;
-    // dg_r = sum_{r' >= r} dG_r' (reverse in-chunk cumulative sum)
+    if (r == CH - 1) dG += __expf(Glast) * F;
+    // dg_r = sum_{r' >= r} dG_r' (reverse in-chunk cumulative sum).  The terms of
+    // e^{G_63 - G_r} are -C_r in dG_r and their sum in dG_63, so they leave
+    // sum_{r' < r} C_r': formed as that, nothing cancels
     float x = __shfl(dG, 63 - lane);
     x = wave_prefix_sum(x);
-    const float dgr = __shfl(x, 63 - lane);
+    const float c = wave_prefix_sum(rowC[r]), before = __shfl(c, max(lane - 1, 0));
+    const float dgr = __shfl(x, 63 - lane) + (lane > 0 ? before : 0.f);
     if (r < len) {
       dg[tok + (long)r * H] = dgr;
       if (dbeta_tilde) {
@@ -3463,13 +3452,11 @@ static hipError_t run_bwd_f32(const LaunchArgs& a) {
   if (a.saved) k_states<false, true><<<dim3(a.N, a.H, 4), NTHR, 0, st>>>(sa, a.smap, Tfix, a.H);
   else k_states<true, true><<<dim3(a.N, a.H, 8), NTHR, 0, st>>>(sa, a.smap, Tfix, a.H);
   a.stage("intra_bwd");
-  if (a.ncmax > 0) {
-    k_dr<<<dim3(a.ncmax, a.H), NTHR, 0, st>>>(a.cmap, Tfix, a.H, a.Mw, a.dRw);
-    k_intra_bwd<float, FD, FD><<<dim3(a.ncmax, a.H), NTHR, 0, st>>>(
+  if (a.ncmax > 0)
+    k_intra_bwd<<<chunk_heads(a), NTHR, 0, st>>>(
         q, k, v, dO, static_cast<const float*>(a.beta), static_cast<const float*>(a.beta_tilde), a.d, a.cmap, Tfix,
-        a.H, a.Gw, a.Xw, a.Dw, a.Yw, a.dRw, static_cast<float*>(a.dq), static_cast<float*>(a.dk_),
+        a.H, a.Gw, a.Mw, a.Xw, a.Dw, a.Yw, a.dRw, static_cast<float*>(a.dq), static_cast<float*>(a.dk_),
         static_cast<float*>(a.dv_), static_cast<float*>(a.dbeta), static_cast<float*>(a.dbeta_tilde), a.dg, a.ddp);
-  }
   a.stage("reduce_dd");
   k_reduce_dd<<<a.H, RDD_THR, 0, st>>>(a.ddp, a.ncmax, a.H, a.dd);
   a.stage(nullptr);

@@ -364,10 +364,10 @@ __global__ __launch_bounds__(NTHR) void k_prep(const float* __restrict__ k, cons
                                                float* __restrict__ Gw, float* __restrict__ U, bool u_rows) {
   __shared__ __align__(16) float Ks[CH * FLD], Vs[CH * FLD], Ls[CH * FLD];
   __shared__ float Gs[CH], Bts[CH];
-  const ChunkInfo ci = chunk_at(cmap, blockIdx.x, Tfix);
+  const int chunk = blockIdx.x / H, h = blockIdx.x - chunk * H;  // heads fastest: whole token rows
+  const ChunkInfo ci = chunk_at(cmap, chunk, Tfix);
   if (ci.len <= 0) return;
-  const int h = blockIdx.y;
-  const long chh = (long)blockIdx.x * H + h, tok = (long)ci.tok0 * H + h;
+  const long chh = blockIdx.x, tok = (long)ci.tok0 * H + h;
   const int w = wave_id(), lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
   const long grow = tok + (long)min(lane, ci.len - 1) * H;
   const float g_in = g[grow], bt_in = beta_tilde[grow], b_in = beta[grow];
@@ -484,10 +484,10 @@ __global__ __launch_bounds__(NTHR) void k_out(const float* __restrict__ q, const
                                               bool d_rows) {
   __shared__ __align__(16) float Ks[CH * FLD], Qt[CH * FLD], Xs[CH * FLD], Ds[CH * FLD], As[CH * FLD];
   __shared__ float Gs[CH];
-  const ChunkInfo ci = chunk_at(cmap, blockIdx.x, Tfix);
+  const int chunk = blockIdx.x / H, h = blockIdx.x - chunk * H;  // heads fastest: whole token rows
+  const ChunkInfo ci = chunk_at(cmap, chunk, Tfix);
   if (ci.len <= 0) return;
-  const int h = blockIdx.y;
-  const long chh = (long)blockIdx.x * H + h, tok = (long)ci.tok0 * H + h;
+  const long chh = blockIdx.x, tok = (long)ci.tok0 * H + h;
   const int w = wave_id(), lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
   FTile kr, qr, xr, dr;
   kr.load(k + tok * FD, (long)H * FD, ci.len);
@@ -530,10 +530,10 @@ __global__ __launch_bounds__(NTHR) void k_bprep(const float* __restrict__ q, con
                                                 float* __restrict__ Yw) {
   __shared__ __align__(16) float Ks[CH * FLD], Qt[CH * FLD], Os[CH * FLD], As[CH * FLD];
   __shared__ float Gs[CH];
-  const ChunkInfo ci = chunk_at(cmap, blockIdx.x, Tfix);
+  const int chunk = blockIdx.x / H, h = blockIdx.x - chunk * H;  // heads fastest: whole token rows
+  const ChunkInfo ci = chunk_at(cmap, chunk, Tfix);
   if (ci.len <= 0) return;
-  const int h = blockIdx.y;
-  const long chh = (long)blockIdx.x * H + h, tok = (long)ci.tok0 * H + h;
+  const long chh = blockIdx.x, tok = (long)ci.tok0 * H + h;
   const int w = wave_id(), lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
   FTile kr, qr, dr;
   kr.load(k + tok * FD, (long)H * FD, ci.len);
@@ -727,13 +727,18 @@ __device__ __forceinline__ void f32_chain(const StatesArgs& a, const SeqInfo& si
 #pragma unroll
     for (int e = 0; e < 4; ++e) s1[soff + (row4 + e) * FD + c] = X[e];
 }
-// blockIdx.z: slice, then (BOTH) direction; REV alone runs the reverse chain.
+// Workgroups in the order of the bf16 scans (scan_item): the four slices of a
+// chain on one XCD at one time, since they read the same W and K; longest
+// sequences first.  blockIdx.z (FWD and REV): the direction.
 template <bool FWD, bool REV>
-__global__ __launch_bounds__(NTHR) void k_states(StatesArgs a, const SeqInfo* __restrict__ smap, int Tfix, int H) {
+__global__ __launch_bounds__(NTHR) void k_states(StatesArgs a, const SeqInfo* __restrict__ smap,
+                                                 const int* __restrict__ sorder, int N, int Tfix, int H) {
   __shared__ __align__(16) float XT[16 * FLD], DT[16 * FLD];
-  const int s = blockIdx.x, h = blockIdx.y, j0 = 16 * (blockIdx.z & 3);
+  const int L = blockIdx.y * gridDim.x + blockIdx.x, chain = (L >> 5) * 8 + (L & 7), j0 = 16 * ((L >> 3) & 3);
+  if (chain >= N * H) return;
+  const int rank = chain / H, h = chain - rank * H, s = sorder ? sorder[rank] : rank;
   const SeqInfo si = seq_at(smap, s, Tfix);
-  if (FWD && (!REV || blockIdx.z < 4)) f32_chain<false>(a, si, s, h, H, j0, XT, DT);
+  if (FWD && (!REV || blockIdx.z == 0)) f32_chain<false>(a, si, s, h, H, j0, XT, DT);
   else f32_chain<true>(a, si, s, h, H, j0, XT, DT);
 }
 
@@ -3412,9 +3417,15 @@ static void f32_prep(const LaunchArgs& a, int Tfix, float* M, float* U, bool u_r
   }
   a.stage("prep");
   if (a.ncmax > 0)
-    k_prep<<<dim3(a.ncmax, a.H), NTHR, 0, a.stream>>>(
+    k_prep<<<chunk_heads(a), NTHR, 0, a.stream>>>(
         static_cast<const float*>(a.k), static_cast<const float*>(a.v), a.g, static_cast<const float*>(a.beta),
         static_cast<const float*>(a.beta_tilde), a.cmap, Tfix, a.H, M, a.Aw, a.Gw, U, u_rows);
+}
+// Grid of k_states: whole groups of 8 chains, four slices each, in x and y (one
+// dimension alone holds fewer than 2^32 threads).
+static dim3 f32_chains(const LaunchArgs& a, int directions) {
+  const unsigned blocks = scan_blocks(a.N, a.H, 4), x = blocks < 65536u ? blocks : 65536u;
+  return dim3(x, (blocks + x - 1) / x, directions);
 }
 static hipError_t run_fwd_f32(const LaunchArgs& a) {
   const float *q = static_cast<const float*>(a.q), *k = static_cast<const float*>(a.k);
@@ -3423,10 +3434,11 @@ static hipError_t run_fwd_f32(const LaunchArgs& a) {
   f32_prep(a, Tfix, a.saved ? a.Mw : nullptr, a.saved ? a.Dw : a.o, !a.saved);
   a.stage("scan_fwd");
   const StatesArgs sa{k, a.Aw, a.Gw, a.h0, nullptr, a.ht, nullptr, X, a.Dw, nullptr, nullptr, a.saved ? nullptr : a.o};
-  k_states<true, false><<<dim3(a.N, a.H, 4), NTHR, 0, a.stream>>>(sa, a.smap, Tfix, a.H);
+  k_states<true, false><<<f32_chains(a, 1), NTHR, 0, a.stream>>>(sa, a.smap, a.cu_seqlens ? a.sorder : nullptr, a.N,
+                                                                 Tfix, a.H);
   a.stage("out");
   if (a.ncmax > 0)
-    k_out<<<dim3(a.ncmax, a.H), NTHR, 0, a.stream>>>(q, k, a.d, a.cmap, Tfix, a.H, a.Gw, X, a.Dw, a.o, !a.saved);
+    k_out<<<chunk_heads(a), NTHR, 0, a.stream>>>(q, k, a.d, a.cmap, Tfix, a.H, a.Gw, X, a.Dw, a.o, !a.saved);
   a.stage(nullptr);
   return hipGetLastError();
 }
@@ -3444,21 +3456,25 @@ static hipError_t run_bwd_f32(const LaunchArgs& a) {
   if (!a.saved) f32_prep(a, Tfix, a.Mw, a.Dw, false);
   a.stage("prep_bwd");
   if (a.ncmax > 0)
-    k_bprep<<<dim3(a.ncmax, a.H), NTHR, 0, st>>>(q, k, dO, a.d, a.cmap, Tfix, a.H, a.Gw, a.dRw, a.Yw);
+    k_bprep<<<chunk_heads(a), NTHR, 0, st>>>(q, k, dO, a.d, a.cmap, Tfix, a.H, a.Gw, a.dRw, a.Yw);
   // the recomputed chunk states and the reverse chain do not depend on each
   // other: one grid
   const StatesArgs sa{k, a.Aw, a.Gw, a.h0, a.dht, nullptr, a.dh0, a.Xw, a.Dw, a.Yw, a.dRw, nullptr};
   a.stage("scan_bwd");
-  if (a.saved) k_states<false, true><<<dim3(a.N, a.H, 4), NTHR, 0, st>>>(sa, a.smap, Tfix, a.H);
-  else k_states<true, true><<<dim3(a.N, a.H, 8), NTHR, 0, st>>>(sa, a.smap, Tfix, a.H);
+  const int* sord = a.cu_seqlens ? a.sorder : nullptr;
+  if (a.saved) k_states<false, true><<<f32_chains(a, 1), NTHR, 0, st>>>(sa, a.smap, sord, a.N, Tfix, a.H);
+  else k_states<true, true><<<f32_chains(a, 2), NTHR, 0, st>>>(sa, a.smap, sord, a.N, Tfix, a.H);
   a.stage("intra_bwd");
   if (a.ncmax > 0)
     k_intra_bwd<<<chunk_heads(a), NTHR, 0, st>>>(
         q, k, v, dO, static_cast<const float*>(a.beta), static_cast<const float*>(a.beta_tilde), a.d, a.cmap, Tfix,
         a.H, a.Gw, a.Mw, a.Xw, a.Dw, a.Yw, a.dRw, static_cast<float*>(a.dq), static_cast<float*>(a.dk_),
-        static_cast<float*>(a.dv_), static_cast<float*>(a.dbeta), static_cast<float*>(a.dbeta_tilde), a.dg, a.ddp);
-  a.stage("reduce_dd");
-  k_reduce_dd<<<a.H, RDD_THR, 0, st>>>(a.ddp, a.ncmax, a.H, a.dd);
+        static_cast<float*>(a.dv_), static_cast<float*>(a.dbeta), static_cast<float*>(a.dbeta_tilde), a.dg,
+        a.ncmax == 1 ? a.dd : a.ddp);
+  if (a.ncmax != 1) {  // one chunk: its partial is the sum
+    a.stage("reduce_dd");
+    k_reduce_dd<<<a.H, RDD_THR, 0, st>>>(a.ddp, a.ncmax, a.H, a.dd);
+  }
   a.stage(nullptr);
   return hipGetLastError();
 }

@@ -5,10 +5,11 @@ keeps its intermediates in the rows of the output, the training pair and the
 no-allocation entry point.  Against the fp64 oracle at the operator's bar for
 fp32 inputs (1e-5 of the largest entry: about 64 sums of 64 products, each with
 a rounding error of 2^-24)."""
+import numpy as np
 import pytest
 
 from comba_inputs import random_case
-from gpu_helpers import check_bwd, check_fwd, to_device
+from gpu_helpers import check_bwd, check_fwd, gpu_bwd, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +44,34 @@ def test_f32_tile_edges(kw, bt):
         assert torch.equal(ht, x)
     for name in gr:
         assert torch.equal(gr[name], gr_s[name]), name
+
+
+def test_one_empty_sequence():
+    # one chunk slot, empty: dd has one partial and it is zero
+    w = random_case(T=0, H=3, dk=64, dv=64, in_dtype="f32", seed=3, dht=True, seqlens=[0])
+    gr = gpu_bwd(w)
+    assert not gr["dd"].any() and np.array_equal(gr["dh0"], w.dht)
+
+
+def test_more_chains_than_one_grid_dimension():
+    """18,000 chains: the chains' grid has two dimensions (more than 65,536
+    workgroups); bit for bit the two halves of the batch."""
+    import torch
+
+    import paper_2506_02475_amd as comba
+
+    print("case 4500 rows, 4 heads", flush=True)
+    w = random_case(B=4500, T=2, H=4, dk=64, dv=64, in_dtype="f32", seed=7, dht=True)
+    a = to_device(w)
+    names = ("q", "k", "v", "g", "beta")
+
+    def call(i, j):
+        args = tuple(a[n][i:j].contiguous() for n in names) + (a["d"], a["h0"][i:j].contiguous())
+        o, ht = comba.comba_chunk_fwd(*args)
+        gr = comba.comba_chunk_bwd(*args, a["dO"][i:j].contiguous(), a["dht"][i:j].contiguous())
+        return dict({n: gr[n] for n in ("dq", "dk", "dv", "dg", "dbeta", "dh0")}, o=o, ht=ht)
+
+    whole, lo, hi = call(0, 4500), call(0, 2250), call(2250, 4500)
+    torch.cuda.synchronize()
+    for n, x in whole.items():
+        assert torch.equal(x, torch.cat([lo[n], hi[n]])), n

@@ -276,12 +276,12 @@ __device__ __forceinline__ void put_block_column(float* Ls, const floatx4 (&mb)[
 // dD0 = A^T dO and P = (Q - d K)^T Diag(e^G) dO: dD = dD0 + K~ Y,
 // Y' = e^{G_63} Y + P - W^T dD, and dR = M^T dD afterwards.
 // Kernels: k_prep (G, M, W, U), k_out, k_bprep (dD0, P), k_states (the forward
-// and the reverse chain, side by side in one grid), k_intra_bwd (dR and the
-// gradients).
-// Forward + stateless backward at B2 T1000 H8: 324 -> 132 us; the tiny forward
-// (B1 T256 H1): 42 -> 26 us (before: five products per step and a one-wave
-// substitution of 64 rows; a step took 5.3 us, now 1.4).  Errors against 64
-// bits are unchanged (2.4e-6 dg, 3.5e-7 o).
+// and the reverse chain, side by side in one grid), k_dr, k_intra_bwd.
+// Before (five products per step, a one-wave substitution of 64 rows; a step took
+// 5.3 us, now 1.4), now, forward and backward from the saved state: B2 T1000 H8
+// 109 + 135 us, now 41 + 62; B1 T256 H1 forward 42, now 25; B32 T256 H16 178 + 333,
+// now 144 + 254.  Errors against 64 bits (2-norm, o): 2.8e-7, as before; keys
+// correlated 0.99 with slow gates 5.6e-7 (before 4.8e-7).
 //
 // A product's k index runs 16 kb + 4 (lane / 16) + e at step e of block kb, so
 // that an operand with k contiguous is one 16-byte read for four steps.
@@ -311,22 +311,82 @@ struct ColOp {
     return floatx4{c[0], c[LD], c[2 * LD], c[3 * LD]};
   }
 };
-// acc[nt] += A(rows 16 w ..) B(columns 16 nt ..) over k blocks kb0 .. kb1 - 1,
-// column tiles nt <= nt1
+struct ColDiff {  // p - d q
+  const float *p, *q;
+  float d;
+  __device__ __forceinline__ floatx4 get(int x, int kb) const {
+    return ColOp<>{p}.get(x, kb) - d * ColOp<>{q}.get(x, kb);
+  }
+};
+// acc[nt] += A(rows 16 w ..) B(columns 16 nt ..) over k blocks kb0 .. kb1 - 1
 template <int NT, typename OA, typename OB>
-__device__ __forceinline__ void fmm(floatx4 (&acc)[NT], const OA& A, const OB& B, int w, int kb0 = 0, int kb1 = 4,
-                                    int nt1 = NT - 1) {
+__device__ __forceinline__ void fmm(floatx4 (&acc)[NT], const OA& A, const OB& B, int w, int kb0 = 0, int kb1 = 4) {
   const int r16 = lane_id() & 15;
   for (int kb = kb0; kb < kb1; ++kb) {
     const floatx4 a = A.get(16 * w + r16, kb);
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-      if (nt <= nt1) {
-        const floatx4 b = B.get(16 * nt + r16, kb);
+    for (int nt = 0; nt < NT; ++nt) {
+      const floatx4 b = B.get(16 * nt + r16, kb);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[nt] = mfma4(a[e], b[e], acc[nt]);
+      for (int e = 0; e < 4; ++e) acc[nt] = mfma4(a[e], b[e], acc[nt]);
+    }
+  }
+}
+// the same over NKB k blocks for two left operands with one right operand, read
+// once; column tiles nt <= nt1, one branch per tile
+template <int NKB, typename O1, typename O2, typename OB>
+__device__ __forceinline__ void fmm2(floatx4 (&acc1)[4], floatx4 (&acc2)[4], const O1& A1, const O2& A2, const OB& B,
+                                     int w, int nt1 = 3) {
+  const int r16 = lane_id() & 15;
+  floatx4 a1[NKB], a2[NKB];
+#pragma unroll
+  for (int kb = 0; kb < NKB; ++kb) {
+    a1[kb] = A1.get(16 * w + r16, kb);
+    a2[kb] = A2.get(16 * w + r16, kb);
+  }
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt)
+    if (nt <= nt1) {
+      floatx4 b[NKB];
+#pragma unroll
+      for (int kb = 0; kb < NKB; ++kb) b[kb] = B.get(16 * nt + r16, kb);
+#pragma unroll
+      for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc1[nt] = mfma4(a1[kb][e], b[kb][e], acc1[nt]);
+          acc2[nt] = mfma4(a2[kb][e], b[kb][e], acc2[nt]);
+        }
+    }
+}
+// Column tile w of a 64 x 64 product for one wave, all four row tiles, formed
+// transposed (acc[rt]: row 16 rt + lane % 16, columns 16 w + 4 (lane / 16) + e: a
+// lane stores 16 bytes of a row): every wave does the same work where the left
+// factor is triangular (k blocks kb <= rt, or kb >= rt).
+enum FShape { FULL, LOWER, UPPER };
+template <FShape S, typename OL, typename OR>
+__device__ __forceinline__ void fcol(floatx4 (&acc)[4], const OL& L, const OR& R, int w) {
+  const int r16 = lane_id() & 15;
+#pragma unroll
+  for (int kb = 0; kb < 4; ++kb) {
+    const floatx4 b = R.get(16 * w + r16, kb);
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt)
+      if (S == FULL || (S == LOWER ? kb <= rt : kb >= rt)) {
+        const floatx4 a = L.get(16 * rt + r16, kb);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[rt] = mfma4(b[e], a[e], acc[rt]);
       }
   }
+}
+// The ten tiles of a lower triangle, dealt to the waves: tile t = w, w + 4, w + 8
+// (scalar).
+struct LowTile {
+  int rt, nt;
+};
+__device__ __forceinline__ LowTile low_tile(int t) {
+  const int rt = t < 1 ? 0 : t < 3 ? 1 : t < 6 ? 2 : 3;
+  return {rt, t - rt * (rt + 1) / 2};
 }
 __device__ __forceinline__ void fzero(floatx4 (&acc)[4]) { acc[0] = acc[1] = acc[2] = acc[3] = zero4(); }
 // W is stored in the order its rows are consumed as the operand of W X: lane
@@ -383,17 +443,24 @@ __global__ __launch_bounds__(NTHR) void k_prep(const float* __restrict__ k, cons
   kr.store(Ks);
   vr.store(Vs);
   __syncthreads();
-  {
-    floatx4 kk[4];
-    fzero(kk);
-    fmm(kk, RowOp<>{Ks}, RowOp<>{Ks}, w);
+  // L, the tiles above the diagonal left out (nothing reads them)
+  const int ws = wave_id_s();
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
+  for (int i = 0; i < 3; ++i) {
+    if (ws + 4 * i >= 10) break;
+    const LowTile lt = low_tile(ws + 4 * i);
+    floatx4 kk = zero4();
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = 16 * w + 4 * g4 + e, c = 16 * nt + r16;
-        Ls[r * FLD + c] = r > c ? Bts[r] * __expf(Gs[r - 1] - Gs[c]) * kk[nt][e] : 0.f;
-      }
+    for (int kb = 0; kb < 4; ++kb) {
+      const floatx4 x = RowOp<>{Ks}.get(16 * lt.rt + r16, kb), y = RowOp<>{Ks}.get(16 * lt.nt + r16, kb);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) kk = mfma4(x[e], y[e], kk);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = 16 * lt.rt + 4 * g4 + e, c = 16 * lt.nt + r16;
+      Ls[r * FLD + c] = r > c ? Bts[r] * __expf(Gs[r - 1] - Gs[c]) * kk[e] : 0.f;
+    }
   }
   __syncthreads();
   // M by 16x16 blocks, one block column per wave (see the bf16 path's k_prep_bf)
@@ -430,65 +497,82 @@ __global__ __launch_bounds__(NTHR) void k_prep(const float* __restrict__ k, cons
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = (threadIdx.x >> 4) + 16 * i, c = (threadIdx.x & 15) * 4;
-      *reinterpret_cast<float4*>(Mw + chh * FT + row * FD + c) = *reinterpret_cast<const float4*>(Ls + row * FLD + c);
+      // blocks above the diagonal: zero
+      *reinterpret_cast<float4*>(Mw + chh * FT + row * FD + c) =
+          (c >> 4) <= i ? *reinterpret_cast<const float4*>(Ls + row * FLD + c) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
   }
-  // M is lower triangular: k blocks up to the row tile
   floatx4 wa[4], ua[4];
   fzero(wa);
   fzero(ua);
-  fmm(wa, RowOp<>{Ls}, ColOp<>{Ks}, w, 0, w + 1);
-  fmm(ua, RowOp<>{Ls}, ColOp<>{Vs}, w, 0, w + 1);
+  fcol<LOWER>(wa, RowOp<>{Ls}, ColOp<>{Ks}, w);
+  fcol<LOWER>(ua, RowOp<>{Ls}, ColOp<>{Vs}, w);
   float* ub = u_rows ? U + tok * FD : U + chh * FT;
   const long us = u_rows ? (long)H * FD : FD;
+  const int c0 = 16 * w + 4 * g4;
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int r = 16 * w + 4 * g4 + e, c = 16 * nt + r16;
-      Ww[chh * FT + wfrag(r, c)] = wa[nt][e];
-      if (!u_rows || r < ci.len) ub[r * us + c] = ua[nt][e];
-    }
+  for (int rt = 0; rt < 4; ++rt) {
+    const int r = 16 * rt + r16;
+    store4(Ww + chh * FT + wfrag(r, c0), wa[rt]);
+    if (!u_rows || r < ci.len) store4(ub + r * us + c0, ua[rt]);
+  }
 }
 
-// The masked scores A = (Q - d K) K^T o e^{G_r - G_c} (r >= c) into LDS; Qt
-// holds Q - d K.  Ends with the wave's own rows written (no barrier).
-__device__ __forceinline__ void f32_scores(float* As, const float* Qt, const float* Ks, const float* Gs, int w) {
-  const int lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
-  floatx4 a[4];
-  fzero(a);
-  fmm(a, RowOp<>{Qt}, RowOp<>{Ks}, w);
+// The masked scores A = (Q K^T - d K K^T) o e^{G_r - G_c} (r >= c): this wave's
+// tiles of the lower triangle, and their store.  Two products: rounding Q - d K
+// first is an error that similar keys add up (keys correlated 0.99, slow gates:
+// 1.6 times the error of o).
+__device__ __forceinline__ void f32_scores(floatx4 (&A)[3], const float* Qs, const float* Ks, const float* Gs,
+                                           float dh) {
+  const int lane = lane_id(), g4 = lane >> 4, r16 = lane & 15, ws = wave_id_s();
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
+  for (int i = 0; i < 3; ++i) {
+    if (ws + 4 * i >= 10) break;
+    const LowTile lt = low_tile(ws + 4 * i);
+    floatx4 aq = zero4(), ak = zero4();
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      const floatx4 x = RowOp<>{Qs}.get(16 * lt.rt + r16, kb), z = RowOp<>{Ks}.get(16 * lt.rt + r16, kb);
+      const floatx4 y = RowOp<>{Ks}.get(16 * lt.nt + r16, kb);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        aq = mfma4(x[e], y[e], aq);
+        ak = mfma4(z[e], y[e], ak);
+      }
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int r = 16 * w + 4 * g4 + e, c = 16 * nt + r16;
-      As[r * FLD + c] = r >= c ? a[nt][e] * __expf(Gs[r] - Gs[c]) : 0.f;
+      const int r = 16 * lt.rt + 4 * g4 + e, c = 16 * lt.nt + r16;
+      A[i][e] = r >= c ? (aq[e] - dh * ak[e]) * __expf(Gs[r] - Gs[c]) : 0.f;
     }
+  }
 }
-__device__ __forceinline__ void f32_qt(float* Qt, const FTile& qr, const FTile& kr, float dh) {
-  FTile t;
+__device__ __forceinline__ void f32_put_scores(float* As, const floatx4 (&A)[3]) {
+  const int lane = lane_id(), g4 = lane >> 4, r16 = lane & 15, ws = wave_id_s();
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-    t.r[i] = make_float4(qr.r[i].x - dh * kr.r[i].x, qr.r[i].y - dh * kr.r[i].y, qr.r[i].z - dh * kr.r[i].z,
-                         qr.r[i].w - dh * kr.r[i].w);
-  t.store(Qt);
+  for (int i = 0; i < 3; ++i) {
+    if (ws + 4 * i >= 10) break;
+    const LowTile lt = low_tile(ws + 4 * i);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) As[(16 * lt.rt + 4 * g4 + e) * FLD + 16 * lt.nt + r16] = A[i][e];
+  }
 }
 
-// O = Diag(e^G)(Q - d K) X + A D per chunk-head.  D comes from the rows of o
+// O = Diag(e^G)(Q X - d K X) + A D per chunk-head.  D comes from the rows of o
 // themselves (d_rows: left there by the scan) or from the workspace.
 __global__ __launch_bounds__(NTHR) void k_out(const float* __restrict__ q, const float* __restrict__ k,
                                               const float* __restrict__ d, const ChunkInfo* __restrict__ cmap,
                                               int Tfix, int H, const float* __restrict__ Gw,
                                               const float* __restrict__ Xw, const float* Dw, float* o,
                                               bool d_rows) {
-  __shared__ __align__(16) float Ks[CH * FLD], Qt[CH * FLD], Xs[CH * FLD], Ds[CH * FLD], As[CH * FLD];
+  __shared__ __align__(16) float Ks[CH * FLD], Qs[CH * FLD], Xs[CH * FLD], Ds[CH * FLD];
   __shared__ float Gs[CH];
   const int chunk = blockIdx.x / H, h = blockIdx.x - chunk * H;  // heads fastest: whole token rows
   const ChunkInfo ci = chunk_at(cmap, chunk, Tfix);
   if (ci.len <= 0) return;
   const long chh = blockIdx.x, tok = (long)ci.tok0 * H + h;
   const int w = wave_id(), lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
+  const float dh = d[h];
   FTile kr, qr, xr, dr;
   kr.load(k + tok * FD, (long)H * FD, ci.len);
   qr.load(q + tok * FD, (long)H * FD, ci.len);
@@ -497,29 +581,31 @@ __global__ __launch_bounds__(NTHR) void k_out(const float* __restrict__ q, const
   else dr.load(Dw + chh * FT, FD, CH);
   if (w == 0) Gs[lane] = Gw[chh * CH + lane];
   kr.store(Ks);
-  f32_qt(Qt, qr, kr, d[h]);
+  qr.store(Qs);
   xr.store(Xs);
   dr.store(Ds);
   __syncthreads();
-  f32_scores(As, Qt, Ks, Gs, w);
-  floatx4 acc[4];
+  floatx4 A[3], acc[4], kx[4];
+  f32_scores(A, Qs, Ks, Gs, dh);
   fzero(acc);
-  fmm(acc, RowOp<>{Qt}, ColOp<>{Xs}, w);
+  fzero(kx);
+  fcol<FULL>(acc, RowOp<>{Qs}, ColOp<>{Xs}, w);
+  fcol<FULL>(kx, RowOp<>{Ks}, ColOp<>{Xs}, w);
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float eg = __expf(Gs[16 * w + 4 * g4 + e]);
+  for (int rt = 0; rt < 4; ++rt) {
+    const float eg = __expf(Gs[16 * rt + r16]);
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) acc[nt][e] *= eg;
+    for (int e = 0; e < 4; ++e) acc[rt][e] = eg * (acc[rt][e] - dh * kx[rt][e]);
   }
-  // only this wave's rows of A are read: no barrier
-  fmm(acc, RowOp<>{As}, ColOp<>{Ds}, w, 0, w + 1);
+  __syncthreads();  // every read of K is done: A takes its place (two workgroups a CU)
+  f32_put_scores(Ks, A);
+  __syncthreads();
+  fcol<LOWER>(acc, RowOp<>{Ks}, ColOp<>{Ds}, w);
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int r = 16 * w + 4 * g4 + e;
-      if (r < ci.len) o[(tok + (long)r * H) * FD + 16 * nt + r16] = acc[nt][e];
-    }
+  for (int rt = 0; rt < 4; ++rt) {
+    const int r = 16 * rt + r16;
+    if (r < ci.len) store4(o + (tok + (long)r * H) * FD + 16 * w + 4 * g4, acc[rt]);
+  }
 }
 
 // dD0 = A^T dO and P = (Q - d K)^T Diag(e^G) dO per chunk-head, into the dR and Y slots.
@@ -528,48 +614,51 @@ __global__ __launch_bounds__(NTHR) void k_bprep(const float* __restrict__ q, con
                                                 const ChunkInfo* __restrict__ cmap, int Tfix, int H,
                                                 const float* __restrict__ Gw, float* __restrict__ dRw,
                                                 float* __restrict__ Yw) {
-  __shared__ __align__(16) float Ks[CH * FLD], Qt[CH * FLD], Os[CH * FLD], As[CH * FLD];
+  __shared__ __align__(16) float Ks[CH * FLD], Qs[CH * FLD], Os[CH * FLD], As[CH * FLD];
   __shared__ float Gs[CH];
   const int chunk = blockIdx.x / H, h = blockIdx.x - chunk * H;  // heads fastest: whole token rows
   const ChunkInfo ci = chunk_at(cmap, chunk, Tfix);
   if (ci.len <= 0) return;
   const long chh = blockIdx.x, tok = (long)ci.tok0 * H + h;
   const int w = wave_id(), lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
+  const float dh = d[h];
   FTile kr, qr, dr;
   kr.load(k + tok * FD, (long)H * FD, ci.len);
   qr.load(q + tok * FD, (long)H * FD, ci.len);
   dr.load(dO + tok * FD, (long)H * FD, ci.len);
   if (w == 0) Gs[lane] = Gw[chh * CH + lane];
   kr.store(Ks);
-  f32_qt(Qt, qr, kr, d[h]);
+  qr.store(Qs);
   dr.store(Os);
   __syncthreads();
-  f32_scores(As, Qt, Ks, Gs, w);
+  {
+    floatx4 A[3];
+    f32_scores(A, Qs, Ks, Gs, dh);
+    f32_put_scores(As, A);
+  }
   __syncthreads();
-  // A is lower triangular: A^T's k blocks from the row tile on
   floatx4 acc[4];
   fzero(acc);
-  fmm(acc, ColOp<>{As}, ColOp<>{Os}, w, w, 4);
+  fcol<UPPER>(acc, ColOp<>{As}, ColOp<>{Os}, w);
+  const int c0 = 16 * w + 4 * g4;
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) dRw[chh * FT + (16 * w + 4 * g4 + e) * FD + 16 * nt + r16] = acc[nt][e];
-  // rows of Q - d K scaled by e^G (K's tile is free: every wave is past the scores)
+  for (int rt = 0; rt < 4; ++rt) store4(dRw + chh * FT + (16 * rt + r16) * FD + c0, acc[rt]);
+  // rows of Q - d K scaled by e^G, over K's tile (every wave is past the scores)
   {
     const float eg = __expf(Gs[lane]);
 #pragma unroll
     for (int c = 16 * w; c < 16 * w + 16; c += 4) {
-      const float4 x = *reinterpret_cast<const float4*>(Qt + lane * FLD + c);
-      *reinterpret_cast<float4*>(Ks + lane * FLD + c) = make_float4(eg * x.x, eg * x.y, eg * x.z, eg * x.w);
+      const float4 x = *reinterpret_cast<const float4*>(Qs + lane * FLD + c);
+      float4* kp = reinterpret_cast<float4*>(Ks + lane * FLD + c);
+      const float4 y = *kp;
+      *kp = make_float4(eg * (x.x - dh * y.x), eg * (x.y - dh * y.y), eg * (x.z - dh * y.z), eg * (x.w - dh * y.w));
     }
   }
   __syncthreads();
   fzero(acc);
-  fmm(acc, ColOp<>{Ks}, ColOp<>{Os}, w);
+  fcol<FULL>(acc, ColOp<>{Ks}, ColOp<>{Os}, w);
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) Yw[chh * FT + (16 * w + 4 * g4 + e) * FD + 16 * nt + r16] = acc[nt][e];
+  for (int rt = 0; rt < 4; ++rt) store4(Yw + chh * FT + (16 * rt + r16) * FD + c0, acc[rt]);
 }
 
 // The chains.  One workgroup per (sequence, head, 16-column slice) and
@@ -747,15 +836,16 @@ __global__ __launch_bounds__(NTHR) void k_states(StatesArgs a, const SeqInfo* __
 // of 32: dR = M^T dD, then the dv-reductions
 //   T1 = dO X^T, T3 = dR X^T, T2 = D Y^T (C x dk), dO D^T, dR D^T (C x C),
 //   <Y, X>_F, <v_r, dR_r>, and dv = Diag(beta) dR.
-// Phase 2 forms, with Q~ = Q - d K,
+// Phase 2 forms
 //   dQ~ = Diag(exp G) T1 + (dA o Gamma) K
-//   dK + d dQ~ = Diag(exp(G_63 - G)) T2 - Diag(s) T3 + (dA o Gamma)^T Q~ + (dAkk + dAkk^T) K
+//   dK + d dQ~ = Diag(exp(G_63 - G)) T2 - Diag(s) T3 + (dA o Gamma)^T Q
+//                + (dAkk + dAkk^T - d (dA o Gamma)^T) K
 // and the per-token gate / beta gradients, then dg by a reverse in-chunk sum.
 // Bound by fp32 MFMA (32 cycles each; zero blocks above the diagonals are left
 // out) and, with few chunks, by one workgroup's chain of them.  Operands are
 // read from one copy of each tile, rows or columns, so that two workgroups fit a
-// CU (76 KB; with transposed copies 139 KB, one per CU).  B32 T256 H16: 213 us
-// and 19 for a kernel of its own for dR, now 140.
+// CU (74 KB; with transposed copies 139 KB, one per CU).  B32 T256 H16: 213 us
+// and 19 for a kernel of its own for dR, now GRAD_US.
 // ---------------------------------------------------------------------------
 constexpr int VB32 = 32, FLB = VB32 + 4;  // columns of a block, its LDS row stride
 __global__ __launch_bounds__(NTHR, 2) void k_intra_bwd(
@@ -785,8 +875,8 @@ __global__ __launch_bounds__(NTHR, 2) void k_intra_bwd(
   const int tid = threadIdx.x, w = wave_id(), lane = lane_id(), g4 = lane >> 4, r16 = lane & 15;
   const int len = ci.len;
   const float dh = d[h];
-  // this wave's rows 16 rt ..: the rotation spreads the long row tiles over the
-  // SIMDs of the workgroups that share a CU
+  // this wave's rows 16 rt ..: the rotation spreads the long row tiles (up to the
+  // diagonal) over the SIMDs of the workgroups that share a CU
   const int rt = __builtin_amdgcn_readfirstlane((w + chunk + h) & (NWAVE - 1));
 
   // ---------------- phase 1: reductions over dv ----------------
@@ -867,11 +957,9 @@ __global__ __launch_bounds__(NTHR, 2) void k_intra_bwd(
         for (int e = 0; e < 4; ++e) dRb[(16 * rt + 4 * g4 + e) * FLB + 16 * nt + r16] = dr[nt][e];
     }
     // only this wave's rows of dR are read: no barrier
-    fmm(T1, RowOp<FLB>{dOb}, RowOp<FLB>{Xb}, rt, 0, 2);
+    fmm2<2>(T1, T3, RowOp<FLB>{dOb}, RowOp<FLB>{dRb}, RowOp<FLB>{Xb}, rt);
     fmm(T2, RowOp<FLB>{Dlb}, RowOp<FLB>{Yb}, rt, 0, 2);
-    fmm(dAr, RowOp<FLB>{dOb}, RowOp<FLB>{Dlb}, rt, 0, 2, rt);
-    fmm(T3, RowOp<FLB>{dRb}, RowOp<FLB>{Xb}, rt, 0, 2);
-    fmm(dLr, RowOp<FLB>{dRb}, RowOp<FLB>{Dlb}, rt, 0, 2, rt);
+    fmm2<2>(dAr, dLr, RowOp<FLB>{dOb}, RowOp<FLB>{dRb}, RowOp<FLB>{Dlb}, rt, rt);
     {
       const float4 a = *reinterpret_cast<const float4*>(dRb + er * FLB + ec);
       const float4 c = *reinterpret_cast<const float4*>(dRb + er * FLB + ec + 4);
@@ -893,12 +981,12 @@ __global__ __launch_bounds__(NTHR, 2) void k_intra_bwd(
 
   // ---------------- phase 2 ----------------
   float* Ks = smem;
-  float* Qt = Ks + T64;
-  float* dAG = Qt + T64;
+  float* Qs = Ks + T64;
+  float* dAG = Qs + T64;
   float* dAkk = dAG + T64;
   static_assert(4 * T64 <= T64 + 6 * T32, "LDS of phase 2");
   kr.store(Ks);
-  f32_qt(Qt, qr, kr, dh);
+  qr.store(Qs);
   __syncthreads();
   const float Glast = Gs[CH - 1];
 
@@ -906,8 +994,7 @@ __global__ __launch_bounds__(NTHR, 2) void k_intra_bwd(
     floatx4 akk[4], aqk[4];
     fzero(akk);
     fzero(aqk);
-    fmm(akk, RowOp<>{Ks}, RowOp<>{Ks}, rt, 0, 4, rt);
-    fmm(aqk, RowOp<>{Qt}, RowOp<>{Ks}, rt, 0, 4, rt);
+    fmm2<4>(akk, aqk, RowOp<>{Ks}, RowOp<>{Qs}, RowOp<>{Ks}, rt, rt);
     float rE1[4] = {0.f, 0.f, 0.f, 0.f}, rE2[4] = {0.f, 0.f, 0.f, 0.f}, rBL[4] = {0.f, 0.f, 0.f, 0.f};
     float cE[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -920,7 +1007,7 @@ __global__ __launch_bounds__(NTHR, 2) void k_intra_bwd(
         if (r >= c) {
           const float gam = __expf(Gs[r] - Gs[c]);
           const float da = dAr[nt][e];
-          e1 = da * (aqk[nt][e] * gam);
+          e1 = da * ((aqk[nt][e] - dh * kk) * gam);
           dag = da * gam;
         }
         if (r > c) {
@@ -968,7 +1055,7 @@ __global__ __launch_bounds__(NTHR, 2) void k_intra_bwd(
       for (int e = 0; e < 4; ++e) {
         const int r = 16 * rt + 4 * g4 + e, c = 16 * nt + r16;
         const float kv = Ks[r * FLD + c];
-        p1[e] += T1[nt][e] * Qt[r * FLD + c];
+        p1[e] += T1[nt][e] * (Qs[r * FLD + c] - dh * kv);
         p2[e] += T2[nt][e] * kv;
         p3[e] += T3[nt][e] * kv;
       }
@@ -1002,9 +1089,9 @@ __global__ __launch_bounds__(NTHR, 2) void k_intra_bwd(
   }
   __syncthreads();  // dAG and dAkk are complete
   fmm(T1, RowOp<>{dAG}, ColOp<>{Ks}, rt, 0, rt + 1);
-  fmm(T2, ColOp<>{dAG}, ColOp<>{Qt}, rt, rt, 4);
+  fmm(T2, ColOp<>{dAG}, ColOp<>{Qs}, rt, rt, 4);
   fmm(T2, RowOp<>{dAkk}, ColOp<>{Ks}, rt, 0, rt + 1);
-  fmm(T2, ColOp<>{dAkk}, ColOp<>{Ks}, rt, rt, 4);
+  fmm(T2, ColDiff{dAkk, dAG, dh}, ColOp<>{Ks}, rt, rt, 4);
   float ddpart = 0.f;
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt)

@@ -8,8 +8,9 @@ a rounding error of 2^-24)."""
 import numpy as np
 import pytest
 
+import oracle
 from comba_inputs import random_case
-from gpu_helpers import check_bwd, check_fwd, gpu_bwd, to_device
+from gpu_helpers import check_bwd, check_fwd, gpu_bwd, gpu_fwd, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -75,3 +76,25 @@ def test_more_chains_than_one_grid_dimension():
     torch.cuda.synchronize()
     for n, x in whole.items():
         assert torch.equal(x, torch.cat([lo[n], hi[n]])), n
+
+
+@pytest.mark.parametrize("gate,corr,bar", [(0.01, 0.9, 5.8e-7), (0.01, 0.99, 6.6e-7),
+                                           (0.0, 0.99, 7.4e-7)])
+def test_similar_keys_and_slow_gates(gate, corr, bar):
+    """Where fp32 rounding adds up most: keys correlated with one another, states
+    that hardly decay.  The bar on o (2-norm) lies between the error of the
+    chunk form's products on Q and K themselves and that of products on a
+    rounded Q - d K, which the sums over similar keys do not average out."""
+    w = random_case(B=1, T=512, H=8, dk=64, dv=64, in_dtype="f32", seed=11, dht=True)
+    w.g *= np.float32(gate)
+    base = np.random.default_rng(12).standard_normal((1, 1, 8, 64)).astype(np.float32)
+    base /= np.linalg.norm(base, axis=-1, keepdims=True)
+    k = np.float32(np.sqrt(corr)) * base + np.float32(np.sqrt(1 - corr)) * w.k
+    w.k[...] = (k / np.linalg.norm(k, axis=-1, keepdims=True)).astype(np.float32)
+    o, ht = gpu_fwd(w)
+    ro, _ = oracle.step_fwd(w.q, w.k, w.v, w.g, w.beta, w.d, w.h0)
+    err = np.linalg.norm(o.astype(np.float64) - ro) / np.linalg.norm(ro)
+    print("2-norm error of o: %.3g" % err, flush=True)
+    check_fwd(w)
+    check_bwd(w)
+    assert err <= bar

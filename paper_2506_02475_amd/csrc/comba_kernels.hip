@@ -276,7 +276,8 @@ __device__ __forceinline__ void put_block_column(float* Ls, const floatx4 (&mb)[
 // dD0 = A^T dO and P = (Q - d K)^T Diag(e^G) dO: dD = dD0 + K~ Y,
 // Y' = e^{G_63} Y + P - W^T dD, and dR = M^T dD afterwards.
 // Kernels: k_prep (G, M, W, U), k_out, k_bprep (dD0, P), k_states (the forward
-// and the reverse chain, side by side in one grid), k_dr, k_intra_bwd.
+// and the reverse chain, side by side in one grid), k_intra_bwd (dR and the
+// gradients).
 // Before (five products per step, a one-wave substitution of 64 rows; a step took
 // 5.3 us, now 1.4), now, forward and backward from the saved state: B2 T1000 H8
 // 109 + 135 us, now 41 + 62; B1 T256 H1 forward 42, now 25; B32 T256 H16 178 + 333,
@@ -844,8 +845,8 @@ __global__ __launch_bounds__(NTHR) void k_states(StatesArgs a, const SeqInfo* __
 // Bound by fp32 MFMA (32 cycles each; zero blocks above the diagonals are left
 // out) and, with few chunks, by one workgroup's chain of them.  Operands are
 // read from one copy of each tile, rows or columns, so that two workgroups fit a
-// CU (74 KB; with transposed copies 139 KB, one per CU).  B32 T256 H16: 213 us
-// and 19 for a kernel of its own for dR, now GRAD_US.
+// CU (76 KB; with transposed copies 139 KB, one per CU).  B32 T256 H16: 213 us
+// and 19 for a kernel of its own for dR, now 140.
 // ---------------------------------------------------------------------------
 constexpr int VB32 = 32, FLB = VB32 + 4;  // columns of a block, its LDS row stride
 __global__ __launch_bounds__(NTHR, 2) void k_intra_bwd(
@@ -3815,7 +3816,9 @@ static hipError_t run_bwd_bf(const LaunchArgs& a) {
           q, k, a.g, bt, a.d, a.cmap, Tfix, a.H, a.Mq, a.Ms, a.Aq, a.As, a.QTp, a.Gw);
     // the chunk states (forward recurrence) and the reverse scan depend only on
     // prep's operands, not on each other (the reverse scan reads no state):
-    // side by side, one workgroup of each per CU (68 + 92 KiB of LDS)
+    // side by side, one workgroup of each per CU (at dk = 128, 66.5 KiB of LDS
+    // for the storing forward scan without outputs and 87.5 for the padded
+    // reverse scan, or 77 for the unpadded one)
     a.stage("scans");
     side(
         st,

@@ -37,7 +37,7 @@ __all__ = ["comba_chunk_fwd", "comba_chunk_bwd", "comba_chunk_fwd_save", "comba_
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libcomba.so")
-_HEADER = os.path.join(os.path.dirname(_PKG), "include", "comba.h")
+_INCLUDE = os.path.join(os.path.dirname(_PKG), "include")
 _lock = threading.Lock()
 _lib = None
 
@@ -138,9 +138,9 @@ def profile_read(capacity: int = 4096):
     return [(names[i].decode(), float(ms[i])) for i in range(n)]
 
 
-def exported_symbols():
-    """Function names declared in include/comba.h (the C ABI)."""
-    with open(_HEADER) as f:
+def exported_symbols(header: str = "comba.h"):
+    """Function names declared in a header of include/ (the C ABI: comba.h, comba_train.h)."""
+    with open(os.path.join(_INCLUDE, header)) as f:
         text = f.read()
     return sorted(set(re.findall(r"\b(comba_[a-z_]+)\s*\(", text)))
 
@@ -558,16 +558,24 @@ def comba_chunk_bwd_saved(q, k, v, g, beta, d, h0, dO, dht=None, *, workspace, b
                 beta_tilde, cu_seqlens_host)
 
 
+def comba_chunk_bwd_saved_in_dtype(q, k, v, g, beta, d, h0, dO, dht=None, *, workspace,
+                                   beta_tilde=None, cu_seqlens=None, cu_seqlens_host=None,
+                                   need_dh0=True, stream=None):
+    """comba_chunk_bwd_saved with dq, dk, dv, dbeta (and dbeta_tilde) in the inputs' dtype (the
+    fp32 values rounded to nearest even); dg, dd and dh0 stay fp32."""
+    return _bwd(True, q, k, v, g, beta, d, h0, dO, dht, cu_seqlens, need_dh0, workspace, stream,
+                beta_tilde, cu_seqlens_host, in_dtype=True)
+
+
 def _autograd_function():
     import torch
 
     class _ChunkComba(torch.autograd.Function):
         """The training pair as one differentiable op: comba_chunk_fwd_save in
-        the forward (its workspace kept for the backward), comba_chunk_bwd_saved
-        in the backward.  Gradients come back in the inputs' dtypes, written so
-        by the kernels (comba_chunk_bwd_saved_in_dtype); the
-        upstream gradient of o is rounded to the inputs' dtype (the kernels
-        take dO in in_dtype)."""
+        the forward (its workspace kept for the backward),
+        comba_chunk_bwd_saved_in_dtype in the backward, whose kernels write the
+        gradients in the inputs' dtypes; the upstream gradient of o is rounded
+        to the inputs' dtype (the kernels take dO in in_dtype)."""
 
         @staticmethod
         def forward(ctx, q, k, v, g, beta, d, h0, beta_tilde, cu_seqlens, cu_seqlens_host):
@@ -586,10 +594,11 @@ def _autograd_function():
                 do = torch.zeros(q.shape[:3] + (v.shape[-1],), dtype=torch.float32,
                                  device=q.device)
             need = ctx.needs_input_grad
-            gr = _bwd(True, q, k, v, g, beta, d, h0, do.to(q.dtype).contiguous(),
-                      None if dht is None else dht.float().contiguous(), cu_seqlens,
-                      h0 is not None and need[6], ws, None, beta_tilde, ctx.cu_seqlens_host,
-                      in_dtype=True)
+            gr = comba_chunk_bwd_saved_in_dtype(
+                q, k, v, g, beta, d, h0, do.to(q.dtype).contiguous(),
+                None if dht is None else dht.float().contiguous(), workspace=ws,
+                beta_tilde=beta_tilde, cu_seqlens=cu_seqlens,
+                cu_seqlens_host=ctx.cu_seqlens_host, need_dh0=h0 is not None and need[6])
 
             def cast(x, like, i):
                 return None if (x is None or not need[i]) else x.to(like.dtype)

@@ -421,3 +421,43 @@ def test_packed_batches_are_segmented_and_fp32_inputs_are_not(seg_env):
         plain = lib.comba_fwd_workspace_bytes(ctypes.byref(s))
         os.environ["COMBA_SCAN_SEGMENTS"] = "4"
         assert (lib.comba_fwd_workspace_bytes(ctypes.byref(s)) > plain) == grows
+
+
+def test_train_header_is_exported_and_bound():
+    assert comba.exported_symbols("comba_train.h") == ["comba_chunk_bwd_saved_in_dtype"]
+    assert hasattr(comba.load_library(), "comba_chunk_bwd_saved_in_dtype")
+    assert callable(comba.comba_chunk_bwd_saved_in_dtype)
+
+
+def test_backward_in_dtype_validates_before_launch():
+    # the refusals of comba_chunk_bwd_saved, with dbeta and dbeta_tilde aligned
+    # to their own elements (2 bytes with bf16 inputs); a one-byte workspace
+    # stops every call that passes them
+    lib = comba.load_library()
+    P = ctypes.c_void_p
+    names = ["q", "k", "v", "g", "beta", "beta_tilde", "d", "h0", "dO", "dht", "dq", "dk", "dv",
+             "dg", "dbeta", "dbeta_tilde", "dd", "dh0", "ws"]
+
+    def call(shp, **over):
+        p = {n: FAKE for n in names}
+        p.update(beta_tilde=None, dbeta_tilde=None, h0=None, dht=None, dh0=None)
+        p.update(over)
+        return lib.comba_chunk_bwd_saved_in_dtype(ctypes.byref(shp), *[P(p[n]) for n in names],
+                                                  ctypes.c_size_t(1), None)
+
+    s, s32 = shape(), shape(dk=64, dv=64, dtype=comba.COMBA_F32)
+    assert call(s) == call(s32) == EWS
+    assert call(shape(chunk=32)) == ESHAPE and call(shape(dtype=7)) == EDTYPE
+    for name in ("q", "dO", "dq", "dk", "dv", "dg", "dbeta", "dd", "ws"):
+        assert call(s, **{name: None}) == ENULL, name
+    assert call(s, beta_tilde=FAKE) == ENULL  # its gradient is required
+    assert call(s, beta_tilde=FAKE, dbeta_tilde=FAKE) == EWS
+    for name in ("dq", "dk", "dv", "h0", "dht", "dh0"):
+        assert call(s, **{name: FAKE + 8}) == EALIGN, name
+    for name in ("dg", "dd"):
+        assert call(s, **{name: FAKE + 2}) == EALIGN, name
+    for kw in (dict(dbeta=FAKE), dict(beta_tilde=FAKE, dbeta_tilde=FAKE)):
+        name = "dbeta_tilde" if "dbeta_tilde" in kw else "dbeta"
+        for off, bf, f32 in ((1, EALIGN, EALIGN), (2, EWS, EALIGN), (4, EWS, EWS)):
+            kw[name] = FAKE + off
+            assert call(s, **kw) == bf and call(s32, **kw) == f32, (name, off)

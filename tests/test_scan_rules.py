@@ -81,3 +81,6 @@ def test_the_batches_of_the_gpu_test_take_the_other_forms(rule):
     for kw in forms.PACKED:
         fwd, bwd = rule(kw["seqlens"], kw["H"], kw["dk"], kw["dv"])
         assert fwd and bwd == (kw["dk"] == 128), kw
+    assert rule([191] * 64, 4) == (True, True)  # test_non_finite_values_in_every_form
+    for dv, P in ((128, 8), (64, 16)):          # segments: all, and the state pass's
+        assert rule([8192 // P] * P, 16, 128, dv)[1] and rule([8192 // P] * (P - 1), 16, 128, dv)[1]

@@ -109,7 +109,7 @@ struct PrologueArgs {
   int dk, dv, H, N, Tseq, Ttot;
   int nruns;  // 64-token runs of the packed token axis (backward)
   int frun;   // tokens per run of the forward (set by its launcher)
-  int groups; // head groups of the grid (set by the launchers)
+  int blocks; // workgroups per head group (set by the launchers)
   float eps;
   const int32_t* cu_seqlens;
   const void *xq, *xk, *xv;     // pre-activations (in_dtype)

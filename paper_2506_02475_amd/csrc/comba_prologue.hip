@@ -197,7 +197,7 @@ __device__ __forceinline__ void prologue_fwd_run(const Tin* __restrict__ x, cons
   constexpr int C = PRO_FCL, PF = PRO_FPF, LPR = D / C, HPW = 64 / LPR;
   const int lane = lane_id();
   const int t0 = run * rlen, t1 = min(t0 + rlen, Ttot);
-  if (t0 >= Ttot || hgrp * HPW >= H) return;  // wave-uniform
+  if (t0 >= Ttot) return;  // wave-uniform
   const int h = hgrp * HPW + lane / LPR;
   const bool hv = h < H;  // lanes of heads past H compute on head H - 1 and store nothing
   const long ts = (long)H * D;  // token stride
@@ -317,19 +317,35 @@ __device__ __forceinline__ void prologue_fwd_run(const Tin* __restrict__ x, cons
   }
 }
 
-// Head groups of the forward grid: enough for the tensor with the most.
-template <int DK, int DV>
-constexpr int fwd_head_groups(int H) {
-  constexpr int D = DK > DV ? DK : DV, HPW = 64 / (D / PRO_FCL);
+// Head groups of a tensor with head size D, C channels per lane.
+template <int D, int C>
+__host__ __device__ constexpr int head_groups(int H) {
+  constexpr int HPW = 64 / (D / C);
   return (H + HPW - 1) / HPW;
+}
+// A workgroup's runs (block rb of PRO_WAVES runs) and head group: groups
+// fastest, so that the workgroups that run together read whole token rows.  By
+// the groups of the tensor itself: consecutive workgroups go to consecutive
+// XCDs, and with the larger tensor's groups for both head sizes the empty
+// workgroups of the other fell on the same XCDs every time (forward, 4 x
+// 4,096 tokens, dk 64 dv 128 H16 67.0 us, now 61.9; dk 128 dv 256 H8 65.2, now
+// 61.5).
+struct RunBlock {
+  int rb, hg;
+};
+template <int DK, int DV, int C>
+__device__ __forceinline__ RunBlock run_block(int z, int H) {
+  const int n = z == 2 ? head_groups<DV, C>(H) : head_groups<DK, C>(H);
+  const int rb = blockIdx.x / n;
+  return {rb, (int)blockIdx.x - rb * n};
 }
 
 template <typename Tin, int DK, int DV>
 __global__ __launch_bounds__(64 * PRO_WAVES) void k_prologue_fwd(PrologueArgs a) {
-  // head groups fastest: the workgroups that run together read whole token rows
-  const int rb = blockIdx.x / a.groups, hg = blockIdx.x - rb * a.groups;
-  const int run = rb * PRO_WAVES + wave_id_s();
   const int z = blockIdx.y;
+  const auto [rb, hg] = run_block<DK, DV, PRO_FCL>(z, a.H);
+  if (rb >= a.blocks) return;
+  const int run = rb * PRO_WAVES + wave_id_s();
   if (z == 0)
     prologue_fwd_run<Tin, DK, true>(static_cast<const Tin*>(a.xq), a.wq, static_cast<Tin*>(a.q),
                                     a.cu_seqlens, a.N, a.Tseq, a.Ttot, a.H, run, a.frun, hg, a.eps);
@@ -359,7 +375,7 @@ __device__ __forceinline__ void prologue_bwd_run(const Tin* __restrict__ x, cons
   const int lane = lane_id();
   const int t0 = run * PRO_RUN, t1 = min(t0 + PRO_RUN, Ttot);
   // this wave's share of dw: slot lane * C + i = (head in group) * D + channel
-  if (t0 >= Ttot || hgrp * HPW >= H) {  // no run: a zero share
+  if (t0 >= Ttot) {  // no run: a zero share
 #pragma unroll
     for (int i = 0; i < C; ++i) dwl[lane * C + i] = make_float4(0.f, 0.f, 0.f, 0.f);
     return;
@@ -502,7 +518,7 @@ __device__ __forceinline__ void combine_dw(const float4 (*dws)[256], float* __re
   constexpr int HPW = 64 / (D / PRO_BCL);
   const int h0 = hg * HPW;
   float4* out = reinterpret_cast<float4*>(dwp) + ((long)rb * H + h0) * D;
-  const int n = min(HPW, H - h0) * D;  // slots of existing heads (n <= 0: none)
+  const int n = min(HPW, H - h0) * D;  // slots of existing heads
   for (int c = threadIdx.x; c < n; c += 64 * PRO_WAVES) {
     float4 s = dws[0][c];
 #pragma unroll
@@ -518,10 +534,11 @@ template <typename Tin, int DK, int DV>
 __global__ __launch_bounds__(64 * PRO_WAVES) void k_prologue_bwd(PrologueArgs a) {
   static_assert(64 * PRO_BCL <= 256, "slots per wave share");
   __shared__ float4 dws[PRO_WAVES][256];  // per wave: the four tap sums of each channel
-  // every wave reaches the barrier below (runs past the tokens add zeros)
-  const int rb = blockIdx.x / a.groups, hg = blockIdx.x - rb * a.groups;  // head groups fastest
-  const int run = rb * PRO_WAVES + wave_id_s();
   const int z = blockIdx.y;
+  const auto [rb, hg] = run_block<DK, DV, PRO_BCL>(z, a.H);
+  if (rb >= a.blocks) return;
+  // every wave reaches the barrier below (runs past the tokens add zeros)
+  const int run = rb * PRO_WAVES + wave_id_s();
   float4* dwl = dws[wave_id_s()];
   if (z == 0)
     prologue_bwd_run<Tin, DK, true>(static_cast<const Tin*>(a.xq), a.wq, a.gq, a.dxq, dwl,
@@ -536,13 +553,6 @@ __global__ __launch_bounds__(64 * PRO_WAVES) void k_prologue_bwd(PrologueArgs a)
   if (z == 0) combine_dw<DK>(dws, a.dwpq, a.H, rb, hg);
   else if (z == 1) combine_dw<DK>(dws, a.dwpk, a.H, rb, hg);
   else combine_dw<DV>(dws, a.dwpv, a.H, rb, hg);
-}
-
-// Head groups of the backward grid: enough for the tensor with the most.
-template <int DK, int DV>
-constexpr int bwd_head_groups(int H) {
-  constexpr int D = DK > DV ? DK : DV, HPW = 64 / (D / PRO_BCL);
-  return (H + HPW - 1) / HPW;
 }
 
 // dw[i] = sum over the workgroups' partials (fixed order), for q, k and v.  A
@@ -613,17 +623,17 @@ static hipError_t run_prologue(const PrologueArgs& a, bool bwd) {
   if (!bwd) {
     a.stage("prologue_fwd");
     PrologueArgs f = a;
-    const int groups = fwd_head_groups<DK, DV>(a.H);
+    const int groups = head_groups<(DK > DV ? DK : DV), PRO_FCL>(a.H);
     f.frun = fwd_run_tokens<Tin, DK, DV>(a.Ttot, groups);
     const int fruns = (a.Ttot + f.frun - 1) / f.frun;
-    f.groups = groups;
-    const dim3 fgrid((unsigned)((fruns + PRO_WAVES - 1) / PRO_WAVES) * groups, 3);
+    f.blocks = (fruns + PRO_WAVES - 1) / PRO_WAVES;
+    const dim3 fgrid((unsigned)f.blocks * groups, 3);
     if (fruns > 0) k_prologue_fwd<Tin, DK, DV><<<fgrid, 64 * PRO_WAVES, 0, a.stream>>>(f);
   } else {
     a.stage("prologue_bwd");
     PrologueArgs b = a;
-    b.groups = bwd_head_groups<DK, DV>(a.H);
-    const dim3 bgrid((unsigned)((a.nruns + PRO_WAVES - 1) / PRO_WAVES) * b.groups, 3);
+    b.blocks = (a.nruns + PRO_WAVES - 1) / PRO_WAVES;
+    const dim3 bgrid((unsigned)b.blocks * head_groups<(DK > DV ? DK : DV), PRO_BCL>(a.H), 3);
     if (a.nruns > 0) k_prologue_bwd<Tin, DK, DV><<<bgrid, 64 * PRO_WAVES, 0, a.stream>>>(b);
     a.stage("prologue_dw");
     const int dmax = a.dk > a.dv ? a.dk : a.dv;

@@ -79,6 +79,13 @@ CASES = [
     # head counts that leave the forward's last group of heads partly empty
     ("bf16_d128_H5", dict(B=2, T=333, H=5, dk=128, dv=128, in_dtype="bf16")),
     ("bf16_d256_H3", dict(B=1, T=517, H=3, dk=256, dv=256, in_dtype="bf16")),
+    # unequal head sizes over several run blocks: the tensors have different
+    # numbers of head groups (forward and backward), the last one partly empty
+    ("bf16_dk128_dv64_H5", dict(B=2, T=333, H=5, dk=128, dv=64, in_dtype="bf16")),
+    ("bf16_dk256_dv128_H3", dict(B=1, T=1500, H=3, dk=256, dv=128, in_dtype="bf16")),
+    ("f32_dk64_dv128_H9", dict(B=1, T=517, H=9, dk=64, dv=128, in_dtype="f32")),
+    ("bf16_dk128_dv64_varlen", dict(H=3, dk=128, dv=64, in_dtype="bf16",
+                                    seqlens=[300, 0, 1, 257, 64])),
     # packed sequences: empty ones, sequences shorter than the taps, boundaries
     # inside a run and exactly at run edges
     ("bf16_varlen", dict(H=2, dk=128, dv=128, in_dtype="bf16",

@@ -110,6 +110,7 @@ struct PrologueArgs {
   int nruns;  // 64-token runs of the packed token axis (backward)
   int frun;   // tokens per run of the forward (set by its launcher)
   int blocks; // workgroups per head group (set by the launchers)
+  bool per_xcd; // order of the forward's workgroups (set by its launcher)
   float eps;
   const int32_t* cu_seqlens;
   const void *xq, *xk, *xv;     // pre-activations (in_dtype)

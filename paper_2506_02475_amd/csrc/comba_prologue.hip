@@ -323,27 +323,35 @@ __host__ __device__ constexpr int head_groups(int H) {
   constexpr int HPW = 64 / (D / C);
   return (H + HPW - 1) / HPW;
 }
-// A workgroup's runs (block rb of PRO_WAVES runs) and head group: groups
-// fastest, so that the workgroups that run together read whole token rows.  By
-// the groups of the tensor itself: consecutive workgroups go to consecutive
-// XCDs, and with the larger tensor's groups for both head sizes the empty
-// workgroups of the other fell on the same XCDs every time (forward, 4 x
-// 4,096 tokens, dk 64 dv 128 H16 67.0 us, now 61.9; dk 128 dv 256 H8 65.2, now
-// 61.5).
+// A workgroup's runs (block rb of PRO_WAVES runs) and head group, so that the
+// workgroups that run together read whole token rows.  By the groups n of the
+// tensor itself: consecutive workgroups go to consecutive XCDs, and with the
+// larger tensor's groups for both head sizes the empty workgroups of the other
+// fell on the same XCDs every time (forward, 4 x 4,096 tokens, dk 64 dv 128 H16
+// 67.0 us, now 61.9; dk 128 dv 256 H8 65.2, now 61.5).
+//  - per_xcd false: groups fastest; a row's pieces go to different XCDs.
+//  - per_xcd true: in sets of up to eight blocks, blocks fastest: a row's pieces
+//    go to one XCD.  For the short runs of small calls (see run_prologue).
 struct RunBlock {
-  int rb, hg;
+  int rb, hg;  // rb >= blocks: nothing to do
 };
 template <int DK, int DV, int C>
-__device__ __forceinline__ RunBlock run_block(int z, int H) {
-  const int n = z == 2 ? head_groups<DV, C>(H) : head_groups<DK, C>(H);
-  const int rb = blockIdx.x / n;
-  return {rb, (int)blockIdx.x - rb * n};
+__device__ __forceinline__ RunBlock run_block(int z, int H, int blocks, bool per_xcd) {
+  const int n = z == 2 ? head_groups<DV, C>(H) : head_groups<DK, C>(H), b = blockIdx.x;
+  if (!per_xcd) {
+    const int rb = b / n;
+    return {rb, b - rb * n};
+  }
+  const int t = b / (8 * n), r = b - 8 * n * t, m = min(8, blocks - 8 * t);
+  if (m <= 0 || r >= m * n) return {blocks, 0};
+  const int hg = r / m;
+  return {8 * t + r - m * hg, hg};
 }
 
 template <typename Tin, int DK, int DV>
 __global__ __launch_bounds__(64 * PRO_WAVES) void k_prologue_fwd(PrologueArgs a) {
   const int z = blockIdx.y;
-  const auto [rb, hg] = run_block<DK, DV, PRO_FCL>(z, a.H);
+  const auto [rb, hg] = run_block<DK, DV, PRO_FCL>(z, a.H, a.blocks, a.per_xcd);
   if (rb >= a.blocks) return;
   const int run = rb * PRO_WAVES + wave_id_s();
   if (z == 0)
@@ -535,7 +543,7 @@ __global__ __launch_bounds__(64 * PRO_WAVES) void k_prologue_bwd(PrologueArgs a)
   static_assert(64 * PRO_BCL <= 256, "slots per wave share");
   __shared__ float4 dws[PRO_WAVES][256];  // per wave: the four tap sums of each channel
   const int z = blockIdx.y;
-  const auto [rb, hg] = run_block<DK, DV, PRO_BCL>(z, a.H);
+  const auto [rb, hg] = run_block<DK, DV, PRO_BCL>(z, a.H, a.blocks, false);
   if (rb >= a.blocks) return;
   // every wave reaches the barrier below (runs past the tokens add zeros)
   const int run = rb * PRO_WAVES + wave_id_s();
@@ -627,6 +635,12 @@ static hipError_t run_prologue(const PrologueArgs& a, bool bwd) {
     f.frun = fwd_run_tokens<Tin, DK, DV>(a.Ttot, groups);
     const int fruns = (a.Ttot + f.frun - 1) / f.frun;
     f.blocks = (fruns + PRO_WAVES - 1) / PRO_WAVES;
+    // Runs of up to 16 tokens (the data of such calls stays in the caches): a
+    // row's pieces on one XCD.  Groups fastest / one XCD, us: fp32 rows of 1,024
+    // values, 2,000 / 4,000 / 6,000 tokens (runs of 8 / 16 / 24) 10.8 / 22.6 / 24.2
+    // -> 10.3 / 16.7 / 24.2 (chunks fastest 18.3 at 4,097); bf16, 4,000 tokens
+    // 14.3 -> 13.4; longer runs lose: bf16 rows of 2,048, 16,000 tokens 87.4 -> 90.4.
+    f.per_xcd = f.frun <= 2 * PRO_FPF;
     const dim3 fgrid((unsigned)f.blocks * groups, 3);
     if (fruns > 0) k_prologue_fwd<Tin, DK, DV><<<fgrid, 64 * PRO_WAVES, 0, a.stream>>>(f);
   } else {

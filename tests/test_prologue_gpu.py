@@ -84,6 +84,8 @@ CASES = [
     ("bf16_dk128_dv64_H5", dict(B=2, T=333, H=5, dk=128, dv=64, in_dtype="bf16")),
     ("bf16_dk256_dv128_H3", dict(B=1, T=1500, H=3, dk=256, dv=128, in_dtype="bf16")),
     ("f32_dk64_dv128_H9", dict(B=1, T=517, H=9, dk=64, dv=128, in_dtype="f32")),
+    # runs of more than 16 tokens (the other order of the forward's workgroups)
+    ("bf16_dk64_dv128_H13_long", dict(B=1, T=6100, H=13, dk=64, dv=128, in_dtype="bf16")),
     ("bf16_dk128_dv64_varlen", dict(H=3, dk=128, dv=64, in_dtype="bf16",
                                     seqlens=[300, 0, 1, 257, 64])),
     # packed sequences: empty ones, sequences shorter than the taps, boundaries

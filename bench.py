@@ -206,7 +206,11 @@ def kernel_roofline(kernel, avg_ms, method, design=None, traffic=None, mfma_coun
     return roof
 
 
-def kernel_source_sha(files=("comba_kernels.hip", "comba_device.hpp")):
+# what decides the chunk kernels' work: their code and the rules that choose their forms
+KERNEL_SOURCES = ("comba_kernels.hip", "comba_device.hpp", "comba_rules.h")
+
+
+def kernel_source_sha(files=KERNEL_SOURCES):
     h = hashlib.sha256()
     for f in files:
         with open(os.path.join(ROOT, "paper_2506_02475_amd", "csrc", f), "rb") as fh:
@@ -218,7 +222,7 @@ DECODE_SOURCES = ("comba_recurrent.hip", "comba_device.hpp")
 
 
 def measured_traffic(kernel, summary="traffic_counters_l1p3b_fwdbwd.md",
-                     sources=("comba_kernels.hip", "comba_device.hpp")):
+                     sources=KERNEL_SOURCES):
     """HBM bytes per launch of a kernel stage from the committed rocprofv3
     FETCH_SIZE / WRITE_SIZE summary (scaled by a plain copy of known size), if
     the counters were taken on the current kernel source; else None."""
@@ -238,7 +242,7 @@ def measured_traffic(kernel, summary="traffic_counters_l1p3b_fwdbwd.md",
 
 
 def measured_mfma(kernel, summary="mfma_counters_l1p3b_fwdbwd.md",
-                  sources=("comba_kernels.hip", "comba_device.hpp")):
+                  sources=KERNEL_SOURCES):
     """MFMA flops per launch of a kernel stage counted by rocprofv3
     (SQ_INSTS_VALU_MFMA_MOPS_*, every MFMA the kernel issues, split products
     and recomputation included), from the committed summary, if it was taken
